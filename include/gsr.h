@@ -201,7 +201,14 @@ typedef struct {
  *                             ellipse reaches (bit 4 row + column), for the
  *                             backward
  *   sort_sel    uint32[1]
- *   pair_emit   uint32[P]     emission index of each sorted pair
+ *   pair_emit   uint32[P]     emission index of each sorted pair; or, in
+ *                             calls that order their records before pairing
+ *                             them (P >= 2 R, and P >= 2^20 with more than
+ *                             4096 tiles or P >= 2^21), uint32[R][2]: each
+ *                             record's first tile x | y << 16 and tile box
+ *                             width | height << 16 in its view (0: culled),
+ *                             from which the backward has the index.  Not
+ *                             written by a shared depth order
  *   ranges      uint32[X][2]  [start, end) of each tile's pairs
  *   pixel_state float[Q][4]   transmittance left behind the last blended
  *                             splat, then the composited colour before the

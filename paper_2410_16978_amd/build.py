@@ -22,6 +22,7 @@ SOURCES = {
     "project.hip": ["-ffp-contract=off"],
     "pairs.hip": [],
     "sort.hip": [],
+    "order.hip": [],
     "blend.hip": ["-ffp-contract=off"],
     "project_bwd.hip": [],
     "loss.hip": [],

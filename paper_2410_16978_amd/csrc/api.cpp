@@ -79,40 +79,72 @@ struct PipeBufs {
   uint32_t* last = nullptr;
   uint32_t* counters = nullptr;
   uint32_t* sel = nullptr;
-  // a shared depth order (Gaussians sorted before they are paired): their
-  // keys and record ids (double-buffered), the sort's control block and
-  // look-back words, words [count, selector after the depth passes,
-  // selector after the unit passes], and the emission sequence
-  uint64_t* gk_a = nullptr;
-  uint64_t* gk_b = nullptr;
-  uint32_t* gv_a = nullptr;
-  uint32_t* gv_b = nullptr;
-  SortCtl* gctl = nullptr;
-  uint32_t* gstatus = nullptr;
-  uint32_t* gwords = nullptr;
-  uint32_t* seq_rec = nullptr;
-  uint32_t* n_tiles_seq = nullptr;
-  uint4* tile_box_seq = nullptr;
+  // order-first (order.hip): the record sort, the pairs, and the control
+  // words (cleared in one range: tickets, digit counts, unit words, the
+  // look-back words of the record passes and the emission)
+  uint2* boxes = nullptr;  // null: in the state's pair_emit
+  uint32_t* sort_keys = nullptr;  // [2][S]
+  uint32_t* sort_vals = nullptr;  // [2][S]
+  uint32_t* pair_tiles = nullptr;  // [2][P]
+  uint32_t* pair_counts = nullptr;  // [blocks][256], [256]
+  uint32_t* order_ctl = nullptr;
+  size_t order_ctl_words = 0;
 };
 
-// Passes of the Gaussian sort of a shared depth order: 4 over the depth
-// bits, then 1 or 2 over the sort unit.
-constexpr int kOrderDepthPasses = 4;
-int order_unit_passes(uint32_t n_units) { return n_units <= 1 ? 0 : (n_units <= 256 ? 1 : 2); }
+// Sizes of a call that orders its records before it pairs them.
+struct OrderPlan {
+  bool on = false;
+  bool own_boxes = false;  // tile boxes in the workspace, not in the state's pair_emit
+  size_t S = 0;            // sort slots: records of all sort units
+  size_t rec_blocks = 0, seq_blocks = 0;
+  uint32_t seq_tile = 0;   // emit_tile of the call's records
+  bool small = true;       // every unit has at most kRecSmall records
+};
+
+// Whether a call orders its records before it pairs them (one that shares an
+// order always does).  Ordering first moves about 12 bytes a record four
+// times and 6 a pair twice, where the per-tile path moves 12 a pair twice (up
+// to 4096 tiles once) and then sorts every tile; its 12 launches cost about
+// 30 us more than the other's on small calls.  Measured, per-tile against
+// order-first, whole frames: beyond 4096 tiles 197 / 192 us at 1.0M pairs and
+// 158 / 169 at 0.5M (1100 x 1000), 1141 / 860 at 12.5M (2 x 1M records); up
+// to 4096 tiles 165 / 190 at 1.0M, 247 / 241 at 2.0M and 870 / 621 at 10M
+// (1024 x 1024).  Below two pair slots a record the record passes outweigh
+// the pairs (and the boxes of all records, which the backward reads from the
+// pair_emit array, would not fit there).
+constexpr uint32_t kOrderMinPairs = 1u << 20;
+bool order_first(uint64_t X, uint32_t P, uint64_t R) {
+  return P >= (tile_sort12(X, P) ? 2 * kOrderMinPairs : kOrderMinPairs) && (uint64_t)P >= 2 * R;
+}
+
+// Words of the order-first path that are zero on entry.
+size_t order_ctl_words(const OrderPlan& op, size_t n_views) {
+  return 8 + n_views * (2 + 4 * 256) + 2 * op.seq_blocks + 4 * 256 * op.rec_blocks;
+}
 
 size_t carve(Carver& c, PipeBufs& b, size_t n_views, size_t R, size_t P, size_t n_req, bool batch,
-             size_t X, size_t Q, bool backward, size_t R_sort = 0) {
+             size_t X, size_t Q, bool backward, const OrderPlan& op) {
   b.views = c.take<ViewD>(std::max<size_t>(n_views, 1));
   b.req_rec = c.take<uint32_t>(n_req + 1);
   b.n_tiles = c.take<uint32_t>(std::max<size_t>(R, 1));
   b.scan_status = c.take<uint64_t>(scan_tiles((uint32_t)R));
-  b.tile_box = c.take<uint4>(std::max<size_t>(R, 1));
-  b.keys_a = c.take<uint64_t>(std::max<size_t>(P, 1));
-  b.keys_b = c.take<uint64_t>(std::max<size_t>(P, 1));
-  b.rec_of = c.take<uint32_t>(std::max<size_t>(P, 1));
   b.ctl = c.take<SortCtl>(1);
-  b.status = c.take<uint32_t>(std::max(sort_status_words((uint32_t)P),
-                                        tile_sort12(X, (uint32_t)P) ? tile_sort12_status_words((uint32_t)P) : 0));
+  if (op.on) {
+    if (op.own_boxes) b.boxes = c.take<uint2>(std::max<size_t>(R, 1));
+    b.sort_keys = c.take<uint32_t>(2 * std::max<size_t>(op.S, 1));
+    b.sort_vals = c.take<uint32_t>(2 * std::max<size_t>(op.S, 1));
+    b.pair_tiles = c.take<uint32_t>(2 * (std::max<size_t>(P, 1) + 4));
+    b.pair_counts = c.take<uint32_t>(256 * ((size_t)pair_pass_blocks((uint32_t)P) + 1));
+    b.order_ctl_words = order_ctl_words(op, n_views);
+    b.order_ctl = c.take<uint32_t>(b.order_ctl_words);
+  } else {
+    b.tile_box = c.take<uint4>(std::max<size_t>(R, 1));
+    b.keys_a = c.take<uint64_t>(std::max<size_t>(P, 1));
+    b.keys_b = c.take<uint64_t>(std::max<size_t>(P, 1));
+    b.rec_of = c.take<uint32_t>(std::max<size_t>(P, 1));
+    b.status = c.take<uint32_t>(std::max(sort_status_words((uint32_t)P),
+                                          tile_sort12(X, (uint32_t)P) ? tile_sort12_status_words((uint32_t)P) : 0));
+  }
   b.class_list = c.take<uint32_t>(kTileClasses * std::max<size_t>(X, 1));
   if (backward) {
     b.g_pair = c.take<float>(12 * (std::max<size_t>(P, 1) + 1));  // + one zero entry, index P
@@ -130,18 +162,6 @@ size_t carve(Carver& c, PipeBufs& b, size_t n_views, size_t R, size_t P, size_t 
     b.last = c.take<uint32_t>(std::max<size_t>(Q, 1));
     b.counters = c.take<uint32_t>(4);
     b.sel = c.take<uint32_t>(1);
-  }
-  if (R_sort) {
-    b.gk_a = c.take<uint64_t>(R_sort);
-    b.gk_b = c.take<uint64_t>(R_sort);
-    b.gv_a = c.take<uint32_t>(R_sort);
-    b.gv_b = c.take<uint32_t>(R_sort);
-    b.gctl = c.take<SortCtl>(1);
-    b.gstatus = c.take<uint32_t>(sort_status_words((uint32_t)R_sort));
-    b.gwords = c.take<uint32_t>(4);
-    b.seq_rec = c.take<uint32_t>(std::max<size_t>(R, 1));
-    b.n_tiles_seq = c.take<uint32_t>(std::max<size_t>(R, 1));
-    b.tile_box_seq = c.take<uint4>(std::max<size_t>(R, 1));
   }
   return c.off + kAlign;
 }
@@ -180,7 +200,7 @@ hipError_t upload_views(ViewD* dst, const ViewD* src, int n_views, WordUpload& u
 
 hipError_t clear_workspace(const PipeBufs& b, uint32_t* counters, bool sticky_flags, uint32_t* ranges, size_t X,
                            size_t R, uint32_t P, uint32_t* sel, hipStream_t s, const WordUpload* up,
-                           uint32_t* batch_tile = nullptr, size_t n_batches = 0, uint32_t n_sort = 0) {
+                           uint32_t* batch_tile = nullptr, size_t n_batches = 0) {
   ClearSet cs{};
   cs.p[0] = reinterpret_cast<uint32_t*>(b.ctl);
   cs.n[0] = sizeof(SortCtl) / 4;
@@ -191,7 +211,10 @@ hipError_t clear_workspace(const PipeBufs& b, uint32_t* counters, bool sticky_fl
   cs.p[3] = reinterpret_cast<uint32_t*>(b.scan_status);
   cs.n[3] = 2 * (size_t)scan_tiles((uint32_t)R);
   // look-back words of the tile passes, and the sorted-buffer selector
-  if (tile_sort12(X, P)) {  // block counts: written before they are read, no clearing
+  if (b.order_ctl) {
+    cs.p[4] = b.order_ctl;
+    cs.n[4] = b.order_ctl_words;
+  } else if (tile_sort12(X, P)) {  // block counts: written before they are read, no clearing
     cs.p[4] = nullptr;
     cs.n[4] = 0;
   } else {
@@ -207,52 +230,76 @@ hipError_t clear_workspace(const PipeBufs& b, uint32_t* counters, bool sticky_fl
     cs.p[cs.n_ranges] = batch_tile;
     cs.n[cs.n_ranges++] = n_batches;
   }
-  if (b.gctl) {  // the Gaussian sort's control block, look-back words and selectors
-    cs.p[cs.n_ranges] = reinterpret_cast<uint32_t*>(b.gctl);
-    cs.n[cs.n_ranges++] = sizeof(SortCtl) / 4;
-    cs.p[cs.n_ranges] = b.gstatus;
-    cs.n[cs.n_ranges++] = sort_status_words(n_sort);
-    cs.p[cs.n_ranges] = b.gwords;
-    cs.n[cs.n_ranges++] = 4;
-  }
   return launch_clear_multi(cs, s, up);
 }
 
-// The sort fields of view d from its view state: a shared order puts the
-// sort camera's depth row in the view (a unit) or points it at its lead.
-void set_sort_fields(ViewD& d, const gsr_view_state& vs, uint32_t mode, uint32_t unit, uint32_t off, uint32_t lead) {
-  d.sort_mode = mode;
-  d.sort_unit = unit;
-  d.sort_off = off;
-  d.sort_lead = lead;
-  if (mode == kSortCamera) {
-    d.sort_r[0] = vs.sort_cam.R[6];
-    d.sort_r[1] = vs.sort_cam.R[7];
-    d.sort_r[2] = vs.sort_cam.R[8];
-    d.sort_t = vs.sort_cam.t[2];
+// The order-first fields of a call's views, in view order: unit by unit the
+// slots and pass blocks of its records, view by view its emission blocks.
+// lead[v] is v for a view that owns its unit's order, else the view whose
+// order it follows; cam[v] (nullable entries) the sort camera of a unit
+// that shares one; n[v] the records of the view's model.
+void plan_order(OrderPlan& op, std::vector<ViewD>& views, const std::vector<int>& lead,
+                const std::vector<const gsr_camera*>& cam, const std::vector<uint32_t>& n) {
+  for (size_t v = 0; v < views.size(); ++v) {
+    ViewD& d = views[v];
+    d.sort_off = (uint32_t)op.S;
+    d.sort_n = n[v];
+    d.sort_blk = (uint32_t)op.rec_blocks;
+    d.seq_blk = (uint32_t)op.seq_blocks;
+    d.sort_lead = (uint32_t)lead[v];
+    op.seq_blocks += div_up(n[v], op.seq_tile);
+    if (lead[v] != (int)v) {
+      d.sort_mode = kSortFollow;
+      continue;
+    }
+    d.sort_mode = cam[v] ? kSortCamera : kSortOwn;
+    if (cam[v]) {
+      for (int j = 0; j < 3; ++j) d.sort_r[j] = cam[v]->R[6 + j];
+      d.sort_t = cam[v]->t[2];
+    }
+    op.S += n[v];
+    op.small = op.small && n[v] <= kRecSmall;
+    op.rec_blocks += div_up(n[v], kRecTile);
   }
 }
 
-// The order stages of a call whose Gaussians are depth-sorted before they
-// are paired, up to the pair count: the Gaussian sort (records written by
-// the projection into gk_a / gv_a), then the emission sequence and its
-// tile-count scan into `offsets` (total into counters).
-hipError_t order_before_pairs(const PipeBufs& b, ViewD* views_dev, int n_views, uint32_t R, uint32_t n_sort,
-                              uint32_t n_units, uint32_t* offsets, uint32_t* counters, uint32_t P, hipStream_t s) {
-  uint32_t* sel = &b.gwords[1];
-  HIP_TRY_E(launch_sort(b.gk_a, b.gk_b, b.gv_a, b.gv_b, b.gwords, n_sort, 0, kOrderDepthPasses, b.gctl->hist,
-                        b.gstatus, b.gctl->pass_ctr, &b.gwords[1], counters + kCntError, s));
-  const int up = order_unit_passes(n_units);
-  if (up > 0) {
-    HIP_TRY_E(launch_sort(b.gk_a, b.gk_b, b.gv_a, b.gv_b, b.gwords, n_sort, kOrderDepthPasses, kOrderDepthPasses + up,
-                          b.gctl->hist, b.gstatus, b.gctl->pass_ctr, &b.gwords[2], counters + kCntError, s,
-                          &b.gwords[1]));
-    sel = &b.gwords[2];
-  }
-  HIP_TRY_E(launch_seq_build(views_dev, n_views, R, b.gk_a, b.gk_b, b.gv_a, b.gv_b, sel, n_sort, b.n_tiles,
-                             b.tile_box, b.seq_rec, b.n_tiles_seq, b.tile_box_seq, counters, s));
-  HIP_TRY_E(launch_scan(b.n_tiles_seq, offsets, b.scan_status, &b.ctl->scan_ticket, R, counters, P, s));
-  return hipSuccess;
+OrderBufs order_bufs(const PipeBufs& b, const OrderPlan& op, int n_views, size_t X, uint32_t P, const uint2* boxes,
+                     uint32_t* pair_vals, uint32_t* counters, uint32_t* ranges, uint32_t* sel) {
+  OrderBufs o;
+  std::memset(&o, 0, sizeof(o));
+  o.views = b.views;
+  o.n_views = n_views;
+  o.n_tiles = (uint32_t)X;
+  o.rec_blocks = (uint32_t)op.rec_blocks;
+  o.seq_blocks = (uint32_t)op.seq_blocks;
+  o.seq_tile = op.seq_tile;
+  o.small = op.small;
+  o.keys_a = b.sort_keys;
+  o.keys_b = b.sort_keys + std::max<size_t>(op.S, 1);
+  o.vals_a = b.sort_vals;
+  o.vals_b = b.sort_vals + std::max<size_t>(op.S, 1);
+  o.boxes = boxes;
+  o.counters = counters;
+  o.cap = P;
+  o.tile_a = b.pair_tiles;
+  o.tile_b = b.pair_tiles + ((std::max<size_t>(P, 1) + 3) & ~(size_t)3);
+  o.rec_a = pair_vals;
+  o.rec_b = pair_vals + P;
+  o.ranges = ranges;
+  o.sel = sel;
+  uint32_t* w = b.order_ctl;  // the 64-bit words first (8-byte aligned)
+  o.emit_status = reinterpret_cast<uint64_t*>(w);
+  w += 2 * op.seq_blocks;
+  o.tickets = w;
+  w += 8;
+  o.unit = w;
+  w += 2 * (size_t)n_views;
+  o.rec_hist = w;
+  w += 4 * 256 * (size_t)n_views;
+  o.rec_status = w;
+  o.pair_counts = b.pair_counts;
+  o.tile_total = b.pair_counts + 256 * (size_t)pair_pass_blocks(P);
+  return o;
 }
 
 bool model_ok(const gsr_model* m) {
@@ -282,6 +329,21 @@ bool camera_ok(const gsr_camera& c) {
 bool view_ok(const gsr_view_state& v) {
   if (v.mip_2d != 0 && (v.mip_2d != 1 || !(v.mip_2d_var > 0.f) || !std::isfinite(v.mip_2d_var))) return false;
   return v.n_clip >= 0 && v.n_clip <= GSR_MAX_CLIP && (v.sort_shared == 0 || v.sort_shared == 1);
+}
+
+// Order-first sizes of a call of n_views views of one model.
+OrderPlan single_plan(int64_t n, int n_views, uint64_t X, uint32_t P, bool shared) {
+  OrderPlan op;
+  op.on = shared || order_first(X, P, (uint64_t)n * n_views);
+  if (!op.on) return op;
+  op.own_boxes = shared;  // a forward that shares an order has no backward
+  const int units = shared ? 1 : n_views;
+  op.S = (size_t)units * n;
+  op.rec_blocks = (size_t)units * div_up((uint32_t)n, kRecTile);
+  op.small = (uint64_t)n <= kRecSmall;
+  op.seq_tile = emit_tile((uint64_t)n * n_views);
+  op.seq_blocks = (size_t)n_views * div_up((uint32_t)n, op.seq_tile);
+  return op;
 }
 
 uint32_t tiles_of(const gsr_camera& c) {
@@ -465,8 +527,12 @@ size_t gsr_workspace_size(int32_t n, int32_t n_views, int32_t width, int32_t hei
   Carver c(nullptr);
   PipeBufs b;
   const size_t X = (size_t)n_views * (size_t)((width + kTile - 1) / kTile) * (size_t)((height + kTile - 1) / kTile);
-  return carve(c, b, (size_t)n_views, (size_t)n * n_views, pair_capacity, 0, false, X, 0, true,
-               shared_order ? (size_t)std::max(n, 1) : 0);
+  const size_t own = carve(c, b, (size_t)n_views, (size_t)n * n_views, pair_capacity, 0, false, X, 0, true,
+                           single_plan(n, n_views, X, pair_capacity, false));
+  if (!shared_order) return own;
+  Carver cs(nullptr);
+  return std::max(own, carve(cs, b, (size_t)n_views, (size_t)n * n_views, pair_capacity, 0, false, X, 0, true,
+                             single_plan(n, n_views, X, pair_capacity, true)));
 }
 
 gsr_status gsr_adam_step(int32_t n, int32_t sh_degree, uint32_t trainable_layers, const uint8_t* layer,
@@ -531,14 +597,12 @@ gsr_status forward_impl(const gsr_model* model, int32_t n_views, const gsr_camer
   const uint64_t X = (uint64_t)tiles_per_view * n_views;
   if (X >= kBatchTileMask || state->batch_capacity < gsr_batch_capacity(P, (uint32_t)X)) return GSR_EINVAL;
   const size_t plane = (size_t)W * H;
-  // one depth order for all views: the Gaussians are sorted by their depth in
-  // views[0].sort_cam before they are paired
+  // one depth order for all views: by the depth in views[0].sort_cam
   const bool shared = views[0].sort_shared != 0;
-  const uint32_t n_sort = shared ? std::max(n, 1u) : 0u;
+  OrderPlan op = single_plan(n, n_views, X, P, shared);
   Carver c(ws);
   PipeBufs b;
-  if (carve(c, b, n_views, R, P, 0, false, X, 0, backward_layout, n_sort) > ws_bytes)
-    return GSR_ENOSPACE;
+  if (carve(c, b, n_views, R, P, 0, false, X, 0, backward_layout, op) > ws_bytes) return GSR_ENOSPACE;
 
   std::vector<ViewD> hv(n_views);
   std::vector<int> ids(n_views);
@@ -550,26 +614,41 @@ gsr_status forward_impl(const gsr_model* model, int32_t n_views, const gsr_camer
     d.alpha = alpha + plane * v;
     d.pix = state->pixel_state + 4 * plane * v;
     d.last = state->last + plane * v;
-    if (shared) set_sort_fields(d, views[0], v == 0 ? kSortCamera : kSortFollow, 0, 0, 0);
     hv[v] = d;
     ids[v] = v;
+  }
+  uint2* boxes = nullptr;
+  if (op.on) {
+    boxes = op.own_boxes ? b.boxes : reinterpret_cast<uint2*>(state->pair_emit);
+    std::vector<int> lead(ids);
+    std::vector<const gsr_camera*> cam(n_views, nullptr);
+    if (shared) {
+      std::fill(lead.begin(), lead.end(), 0);
+      cam[0] = &views[0].sort_cam;
+      hv[0].sort_whole = n_views <= kMaxJobViews;  // (one projection job)
+    }
+    OrderPlan made = op;
+    made.S = made.rec_blocks = made.seq_blocks = 0;
+    plan_order(made, hv, lead, cam, std::vector<uint32_t>(n_views, n));
   }
   WordUpload up;
   HIP_TRY(upload_views(b.views, hv.data(), n_views, up, s));
   HIP_TRY(clear_workspace(b, state->counters, true, state->ranges, X, R, P, state->sort_sel, s, &up,
-                          state->batch_map + X + 1, state->batch_capacity, n_sort));
-  if (shared) HIP_TRY(launch_set_u32(&b.gwords[0], n_sort, s));
+                          state->batch_map + X + 1, state->batch_capacity));
   const ModelD md = make_model(*model);
   {
     StageScope sc(timer, GSR_STAGE_PROJECT, s);
     for (const JobD& j : make_jobs(md, ids))
-      HIP_TRY(launch_project(j, b.views, state->records, b.n_tiles, b.tile_box, shared ? b.gk_a : nullptr,
-                             shared ? b.gv_a : nullptr, state->counters, s));
+      HIP_TRY(launch_project(j, b.views, state->records, b.n_tiles, b.tile_box, boxes, b.sort_keys, state->counters,
+                             s));
   }
+  OrderBufs o;
+  if (op.on)
+    o = order_bufs(b, op, n_views, X, P, boxes, state->pair_vals, state->counters, state->ranges, state->sort_sel);
   {
     StageScope sc(timer, GSR_STAGE_SCAN, s);
-    if (shared)
-      HIP_TRY(order_before_pairs(b, b.views, n_views, R, n_sort, 1, state->offsets, state->counters, P, s));
+    if (op.on)
+      HIP_TRY(launch_order_scan(o, b.n_tiles, state->offsets, b.scan_status, &b.ctl->scan_ticket, R, s));
     else
       HIP_TRY(launch_scan(b.n_tiles, state->offsets, b.scan_status, &b.ctl->scan_ticket, R, state->counters, P, s));
   }
@@ -586,48 +665,53 @@ gsr_status forward_impl(const gsr_model* model, int32_t n_views, const gsr_camer
       return GSR_ENOSPACE;
     }
   }
-  {
-    StageScope sc(timer, GSR_STAGE_DUPLICATE, s);
-    if (shared)
-      HIP_TRY(launch_duplicate(b.n_tiles_seq, state->offsets, b.tile_box_seq, R, state->counters, P, b.keys_a,
-                               state->pair_vals, b.rec_of, s, b.seq_rec));
-    else
-      HIP_TRY(launch_duplicate(b.n_tiles, state->offsets, b.tile_box, R, state->counters, P, b.keys_a,
-                               state->pair_vals, b.rec_of, s));
-  }
-  if (debug && (debug->keys_emit || debug->vals_emit)) {
-    if (debug->keys_emit) HIP_TRY(hipMemcpyAsync(debug->keys_emit, b.keys_a, 8ull * P, hipMemcpyDeviceToDevice, s));
-    if (debug->vals_emit) HIP_TRY(hipMemcpyAsync(debug->vals_emit, b.rec_of, 4ull * P, hipMemcpyDeviceToDevice, s));
-  }
-  {
-    StageScope sc(timer, GSR_STAGE_SORT, s);
-    if (tile_sort12(X, P))
-      HIP_TRY(launch_tile_sort12(b.keys_a, b.keys_b, state->pair_vals, state->pair_vals + P, state->counters, P,
-                                 (uint32_t)X, b.ctl->hist12, b.status, state->ranges, b.ctl->tile_class,
-                                 b.class_list, state->sort_sel, state->counters + kCntError, s));
-    else
-      HIP_TRY(launch_sort(b.keys_a, b.keys_b, state->pair_vals, state->pair_vals + P, state->counters, P,
-                          kDepthPasses, tile_pass_end(X), b.ctl->hist, b.status, b.ctl->pass_ctr,
-                          state->sort_sel, state->counters + kCntError, s));
-  }
-  {
-    StageScope sc(timer, GSR_STAGE_RANGES, s);
-    if (!tile_sort12(X, P)) {  // (the one-pass grouping writes the ranges and classes itself)
-      HIP_TRY(launch_ranges(b.keys_a, b.keys_b, state->sort_sel, state->counters, P, (uint32_t)X, state->ranges, s));
+  if (op.on) {
+    {
+      StageScope sc(timer, GSR_STAGE_SORT, s);
+      HIP_TRY(launch_order(o, s));
+    }
+    {
+      StageScope sc(timer, GSR_STAGE_RANGES, s);
       HIP_TRY(launch_tile_order(state->ranges, (uint32_t)X, b.ctl->tile_class, b.class_list, s));
     }
-  }
-  {
-    StageScope sc(timer, GSR_STAGE_SORT, s);
-    if (shared)  // the pairs of every tile are in depth order already
-      HIP_TRY(launch_finalize_pairs(state->pair_vals, state->pair_vals + P, b.keys_a, b.keys_b, state->sort_sel,
-                                    b.rec_of, state->counters, P, state->pair_emit,
-                                    debug ? debug->keys_sorted : nullptr, s));
-    else
+    if (debug)
+      HIP_TRY(launch_order_debug(o, R, state->records, state->offsets, debug->tile_box, debug->keys_emit,
+                                 debug->vals_emit, debug->keys_sorted, s));
+  } else {
+    {
+      StageScope sc(timer, GSR_STAGE_DUPLICATE, s);
+      HIP_TRY(launch_duplicate(b.n_tiles, state->offsets, b.tile_box, R, state->counters, P, b.keys_a,
+                               state->pair_vals, b.rec_of, s));
+    }
+    if (debug) {
+      if (debug->keys_emit) HIP_TRY(hipMemcpyAsync(debug->keys_emit, b.keys_a, 8ull * P, hipMemcpyDeviceToDevice, s));
+      if (debug->vals_emit) HIP_TRY(hipMemcpyAsync(debug->vals_emit, b.rec_of, 4ull * P, hipMemcpyDeviceToDevice, s));
+    }
+    {
+      StageScope sc(timer, GSR_STAGE_SORT, s);
+      if (tile_sort12(X, P))
+        HIP_TRY(launch_tile_sort12(b.keys_a, b.keys_b, state->pair_vals, state->pair_vals + P, state->counters, P,
+                                   (uint32_t)X, b.ctl->hist12, b.status, state->ranges, b.ctl->tile_class,
+                                   b.class_list, state->sort_sel, state->counters + kCntError, s));
+      else
+        HIP_TRY(launch_sort(b.keys_a, b.keys_b, state->pair_vals, state->pair_vals + P, state->counters, P,
+                            kDepthPasses, tile_pass_end(X), b.ctl->hist, b.status, b.ctl->pass_ctr,
+                            state->sort_sel, state->counters + kCntError, s));
+    }
+    {
+      StageScope sc(timer, GSR_STAGE_RANGES, s);
+      if (!tile_sort12(X, P)) {  // (the one-pass grouping writes the ranges and classes itself)
+        HIP_TRY(launch_ranges(b.keys_a, b.keys_b, state->sort_sel, state->counters, P, (uint32_t)X, state->ranges, s));
+        HIP_TRY(launch_tile_order(state->ranges, (uint32_t)X, b.ctl->tile_class, b.class_list, s));
+      }
+    }
+    {
+      StageScope sc(timer, GSR_STAGE_SORT, s);
       HIP_TRY(launch_sort_segments(b.keys_a, b.keys_b, state->pair_vals, state->pair_vals + P, state->sort_sel,
                                    state->ranges, (uint32_t)X, b.rec_of, state->counters, P, state->pair_emit,
                                    debug ? debug->keys_sorted : nullptr, b.ctl->tile_class, b.class_list,
                                    &b.ctl->seg_ticket, state->counters + kCntError, s));
+    }
   }
   uint32_t* batch_tile = state->batch_map + X + 1;
   {
@@ -639,7 +723,8 @@ gsr_status forward_impl(const gsr_model* model, int32_t n_views, const gsr_camer
   }
   if (debug) {
     if (debug->n_tiles) HIP_TRY(hipMemcpyAsync(debug->n_tiles, b.n_tiles, 4ull * R, hipMemcpyDeviceToDevice, s));
-    if (debug->tile_box) HIP_TRY(hipMemcpyAsync(debug->tile_box, b.tile_box, 16ull * R, hipMemcpyDeviceToDevice, s));
+    if (debug->tile_box && !op.on)
+      HIP_TRY(hipMemcpyAsync(debug->tile_box, b.tile_box, 16ull * R, hipMemcpyDeviceToDevice, s));
     HIP_TRY(hipStreamSynchronize(s));
   }
   return GSR_OK;
@@ -698,10 +783,17 @@ gsr_status gsr_rasterize_forward_noalloc(const gsr_model* model, int32_t n_views
   if (!single_view_args_ok(model, n_views, cams, views) || !state || !rgb || !alpha || !state_ok(state))
     return GSR_EINVAL;
   const uint64_t X = (uint64_t)tiles_of(cams[0]) * (uint64_t)n_views;
-  Carver c(nullptr);
+  // the limit holds for the per-tile path's scratch (a shared order: 24 bytes
+  // a Gaussian and a record more), whichever path the call takes: the
+  // order-first one needs less, and a size is refused or not by one rule
+  const bool shared = views[0].sort_shared != 0;
+  const size_t n = (size_t)model->n, R = n * (size_t)n_views;
+  const uint32_t P = state->pair_capacity;
+  Carver per_tile(nullptr), own(nullptr);
   PipeBufs b;
-  const size_t need = carve(c, b, (size_t)n_views, (size_t)model->n * (size_t)n_views, state->pair_capacity, 0,
-                            false, X, 0, false, views[0].sort_shared ? (size_t)std::max(model->n, 1) : 0);
+  const size_t need =
+      std::max(carve(per_tile, b, (size_t)n_views, R, P, 0, false, X, 0, false, OrderPlan{}) + (shared ? 24 * (n + R) : 0),
+               carve(own, b, (size_t)n_views, R, P, 0, false, X, 0, false, single_plan(model->n, n_views, X, P, shared)));
   if (need > kNoallocScratchBytes) return GSR_ENOSPACE;
   void* ws = nullptr;
   const gsr_status st = scratch_of_current_device(&ws);
@@ -747,7 +839,8 @@ gsr_status gsr_rasterize_backward(const gsr_model* model, int32_t n_views, const
   const size_t plane = (size_t)W * H;
   Carver c(ws);
   PipeBufs b;
-  if (carve(c, b, n_views, R, P, 0, false, X, 0, true) > ws_bytes)
+  const OrderPlan op = single_plan(n, n_views, X, P, false);
+  if (carve(c, b, n_views, R, P, 0, false, X, 0, true, op) > ws_bytes)
     return GSR_ENOSPACE;
   std::vector<ViewD> hv(n_views);
   std::vector<int> ids(n_views);
@@ -786,8 +879,9 @@ gsr_status gsr_rasterize_backward(const gsr_model* model, int32_t n_views, const
     StageScope sc(timer, GSR_STAGE_BLEND_BWD, s);
     HIP_TRY(launch_blend_bwd(b.views, n_views, state->records, R, state->pair_vals, state->sort_sel, P,
                              state->ranges, reinterpret_cast<const float4*>(state->checkpoints), batch_tile,
-                             n_batches, b.order_cnt, b.order_list, dL_drgb, dL_dalpha, state->pair_emit, b.g_pair,
-                             reinterpret_cast<uint8_t*>(b.alive), max_contrib != nullptr, s));
+                             n_batches, b.order_cnt, b.order_list, dL_drgb, dL_dalpha, state->pair_emit,
+                             op.on ? reinterpret_cast<const uint2*>(state->pair_emit) : nullptr, state->offsets,
+                             b.g_pair, reinterpret_cast<uint8_t*>(b.alive), max_contrib != nullptr, s));
   }
   const ModelD md = make_model(*model);
   {
@@ -809,14 +903,13 @@ struct BatchPlan {
   std::vector<ViewD> views;
   std::vector<uint32_t> req_rec;
   uint64_t R = 0, X = 0, Q = 0;
-  // with any request sharing one depth order between its eyes, every view
-  // takes the order-first path: R_sort records in n_units sort units
-  bool ordered = false;
-  uint64_t R_sort = 0;
-  uint32_t n_units = 0;
+  // with any request sharing one depth order between its eyes, or where
+  // order_first says so, the records are ordered before they are paired
+  OrderPlan order;
 };
 
-bool plan_batch(const gsr_model* models, int32_t n_models, const gsr_request* reqs, int32_t n_req, BatchPlan& bp) {
+bool plan_batch(const gsr_model* models, int32_t n_models, const gsr_request* reqs, int32_t n_req,
+                uint32_t pair_capacity, BatchPlan& bp) {
   if (!models || n_models <= 0 || !reqs || n_req <= 0) return false;
   for (int m = 0; m < n_models; ++m)
     if (!model_ok(&models[m])) return false;
@@ -841,28 +934,37 @@ bool plan_batch(const gsr_model* models, int32_t n_models, const gsr_request* re
     }
   }
   bp.req_rec[n_req] = (uint32_t)bp.R;
-  for (int q = 0; q < n_req; ++q) bp.ordered = bp.ordered || reqs[q].vs.sort_shared != 0;
-  if (bp.ordered) {
+  if (bp.R >= (1ull << 31) || bp.X >= (1ull << 31)) return false;
+  bool shared = false;
+  for (int q = 0; q < n_req; ++q) shared = shared || reqs[q].vs.sort_shared != 0;
+  bp.order.on = shared || order_first(bp.X, pair_capacity, bp.R);
+  if (bp.order.on) {
+    bp.order.own_boxes = true;
+    bp.order.seq_tile = emit_tile(bp.R);
     // each view is a sort unit by its own depth, except the eyes of a
     // request that shares one order: the first eye sorts by the request's
     // sort camera, the second follows it
-    size_t v = 0;
+    std::vector<int> lead;
+    std::vector<const gsr_camera*> cam;
+    std::vector<uint32_t> n;
+    std::vector<uint32_t> views_of(n_models, 0u);
     for (int q = 0; q < n_req; ++q) {
       const gsr_request& r = reqs[q];
       const bool sh = r.vs.sort_shared != 0;
-      for (int e = 0; e < r.n_views; ++e, ++v) {
-        ViewD& d = bp.views[v];
-        if (sh && e > 0) {
-          set_sort_fields(d, r.vs, kSortFollow, 0, 0, (uint32_t)(v - e));
-        } else {
-          set_sort_fields(d, r.vs, sh ? kSortCamera : kSortOwn, bp.n_units++, (uint32_t)bp.R_sort, 0);
-          bp.R_sort += (uint64_t)models[r.model].n;
-        }
+      const int first = (int)lead.size();
+      for (int e = 0; e < r.n_views; ++e) {
+        lead.push_back(sh ? first : first + e);
+        cam.push_back(sh && e == 0 ? &r.vs.sort_cam : nullptr);
+        n.push_back((uint32_t)models[r.model].n);
       }
+      // (a model's views go through the projection kMaxJobViews at a time)
+      const uint32_t j0 = views_of[r.model], j1 = j0 + (uint32_t)r.n_views;
+      bp.views[first].sort_whole = j0 / kMaxJobViews == (j1 - 1) / kMaxJobViews;
+      views_of[r.model] = j1;
     }
-    if (bp.n_units > 65536) return false;  // two unit passes at most
+    plan_order(bp.order, bp.views, lead, cam, n);
   }
-  return bp.R < (1ull << 31) && bp.X < (1ull << 31);
+  return true;
 }
 
 }  // namespace
@@ -870,27 +972,25 @@ bool plan_batch(const gsr_model* models, int32_t n_models, const gsr_request* re
 size_t gsr_batch_workspace_size(const gsr_model* models, int32_t n_models, const gsr_request* reqs, int32_t n_req,
                                 uint32_t pair_capacity) {
   BatchPlan bp;
-  if (!plan_batch(models, n_models, reqs, n_req, bp) || pair_capacity >= (1u << 30)) return 0;
+  if (!plan_batch(models, n_models, reqs, n_req, pair_capacity, bp) || pair_capacity >= (1u << 30)) return 0;
   Carver c(nullptr);
   PipeBufs b;
-  return carve(c, b, bp.views.size(), bp.R, pair_capacity, n_req, true, bp.X, bp.Q, false,
-               bp.ordered ? std::max<uint64_t>(bp.R_sort, 1) : 0);
+  return carve(c, b, bp.views.size(), bp.R, pair_capacity, n_req, true, bp.X, bp.Q, false, bp.order);
 }
 
 gsr_status gsr_render_batch(const gsr_model* models, int32_t n_models, const gsr_request* reqs, int32_t n_req,
                             uint32_t pair_capacity, void* ws, size_t ws_bytes, int32_t* req_status, gsr_timer* timer,
                             void* stream) {
   BatchPlan bp;
-  if (!plan_batch(models, n_models, reqs, n_req, bp) || !ws || !req_status || pair_capacity >= (1u << 30))
+  if (!plan_batch(models, n_models, reqs, n_req, pair_capacity, bp) || !ws || !req_status || pair_capacity >= (1u << 30))
     return GSR_EINVAL;
   const hipStream_t s = static_cast<hipStream_t>(stream);
   const uint32_t P = pair_capacity;
   const uint32_t R = (uint32_t)bp.R;
   const int n_views = (int)bp.views.size();
-  const uint32_t n_sort = bp.ordered ? (uint32_t)std::max<uint64_t>(bp.R_sort, 1) : 0u;
   Carver c(ws);
   PipeBufs b;
-  if (carve(c, b, n_views, R, P, n_req, true, bp.X, bp.Q, false, n_sort) > ws_bytes) return GSR_ENOSPACE;
+  if (carve(c, b, n_views, R, P, n_req, true, bp.X, bp.Q, false, bp.order) > ws_bytes) return GSR_ENOSPACE;
   // per-view transmittance / last index scratch
   size_t q_off = 0;
   for (ViewD& d : bp.views) {
@@ -901,8 +1001,7 @@ gsr_status gsr_render_batch(const gsr_model* models, int32_t n_models, const gsr
   WordUpload up;
   HIP_TRY(upload_views(b.views, bp.views.data(), n_views, up, s));
   HIP_TRY(launch_upload(b.req_rec, bp.req_rec.data(), (size_t)n_req + 1, s));
-  HIP_TRY(clear_workspace(b, b.counters, false, b.ranges, bp.X, R, P, b.sel, s, &up, nullptr, 0, n_sort));
-  if (bp.ordered) HIP_TRY(launch_set_u32(&b.gwords[0], n_sort, s));
+  HIP_TRY(clear_workspace(b, b.counters, false, b.ranges, bp.X, R, P, b.sel, s, &up));
   {
     StageScope sc(timer, GSR_STAGE_PROJECT, s);
     for (int m = 0; m < n_models; ++m) {
@@ -912,55 +1011,57 @@ gsr_status gsr_render_batch(const gsr_model* models, int32_t n_models, const gsr
       if (ids.empty()) continue;
       const ModelD md = make_model(models[m]);
       for (const JobD& j : make_jobs(md, ids))
-        HIP_TRY(launch_project(j, b.views, b.records, b.n_tiles, b.tile_box, bp.ordered ? b.gk_a : nullptr,
-                               bp.ordered ? b.gv_a : nullptr, b.counters, s));
+        HIP_TRY(launch_project(j, b.views, b.records, b.n_tiles, b.tile_box, b.boxes, b.sort_keys, b.counters, s));
     }
   }
+  OrderBufs o;
+  if (bp.order.on) o = order_bufs(b, bp.order, n_views, bp.X, P, b.boxes, b.vals, b.counters, b.ranges, b.sel);
   {
     StageScope sc(timer, GSR_STAGE_SCAN, s);
-    if (bp.ordered)
-      HIP_TRY(order_before_pairs(b, b.views, n_views, R, n_sort, bp.n_units, b.offsets, b.counters, P, s));
+    if (bp.order.on)
+      HIP_TRY(launch_order_scan(o, b.n_tiles, b.offsets, b.scan_status, &b.ctl->scan_ticket, R, s));
     else
       HIP_TRY(launch_scan(b.n_tiles, b.offsets, b.scan_status, &b.ctl->scan_ticket, R, b.counters, P, s));
-    // (a request's records keep their positions in the emission sequence,
-    // so its pairs end at offsets[req_rec[q + 1]] in either order)
+    // (ordered records are emitted view by view, so a request's pairs end at
+    // offsets[req_rec[q + 1]] in either order)
     HIP_TRY(launch_batch_status(b.req_rec, n_req, b.offsets, P, b.counters, req_status, s));
   }
-  {
-    StageScope sc(timer, GSR_STAGE_DUPLICATE, s);
-    if (bp.ordered)
-      HIP_TRY(launch_duplicate(b.n_tiles_seq, b.offsets, b.tile_box_seq, R, b.counters, P, b.keys_a, b.vals,
-                               b.rec_of, s, b.seq_rec));
-    else
-      HIP_TRY(launch_duplicate(b.n_tiles, b.offsets, b.tile_box, R, b.counters, P, b.keys_a, b.vals, b.rec_of, s));
-  }
-  {
-    StageScope sc(timer, GSR_STAGE_SORT, s);
-    if (tile_sort12(bp.X, P))
-      HIP_TRY(launch_tile_sort12(b.keys_a, b.keys_b, b.vals, b.vals + P, b.counters, P, (uint32_t)bp.X,
-                                 b.ctl->hist12, b.status, b.ranges, b.ctl->tile_class, b.class_list, b.sel,
-                                 b.counters + kCntError, s));
-    else
-      HIP_TRY(launch_sort(b.keys_a, b.keys_b, b.vals, b.vals + P, b.counters, P, kDepthPasses,
-                          tile_pass_end(bp.X), b.ctl->hist, b.status, b.ctl->pass_ctr, b.sel,
-                          b.counters + kCntError, s));
-  }
-  {
-    StageScope sc(timer, GSR_STAGE_RANGES, s);
-    if (!tile_sort12(bp.X, P)) {  // (the one-pass grouping writes the ranges and classes itself)
-      HIP_TRY(launch_ranges(b.keys_a, b.keys_b, b.sel, b.counters, P, (uint32_t)bp.X, b.ranges, s));
-      HIP_TRY(launch_tile_order(b.ranges, (uint32_t)bp.X, b.ctl->tile_class, b.class_list, s));
+  if (bp.order.on) {
+    {
+      StageScope sc(timer, GSR_STAGE_SORT, s);
+      HIP_TRY(launch_order(o, s));
     }
-  }
-  {
-    StageScope sc(timer, GSR_STAGE_SORT, s);
-    if (bp.ordered)  // the pairs of every tile are in depth order already
-      HIP_TRY(launch_finalize_pairs(b.vals, b.vals + P, b.keys_a, b.keys_b, b.sel, b.rec_of, b.counters, P, nullptr,
-                                    nullptr, s));
-    else
-      HIP_TRY(launch_sort_segments(b.keys_a, b.keys_b, b.vals, b.vals + P, b.sel, b.ranges, (uint32_t)bp.X,
-                                   b.rec_of, b.counters, P, nullptr, nullptr, b.ctl->tile_class, b.class_list,
+    StageScope sc(timer, GSR_STAGE_RANGES, s);
+    HIP_TRY(launch_tile_order(b.ranges, (uint32_t)bp.X, b.ctl->tile_class, b.class_list, s));
+  } else {
+    {
+      StageScope sc(timer, GSR_STAGE_DUPLICATE, s);
+      HIP_TRY(launch_duplicate(b.n_tiles, b.offsets, b.tile_box, R, b.counters, P, b.keys_a, b.vals, b.rec_of, s));
+    }
+    {
+      StageScope sc(timer, GSR_STAGE_SORT, s);
+      if (tile_sort12(bp.X, P))
+        HIP_TRY(launch_tile_sort12(b.keys_a, b.keys_b, b.vals, b.vals + P, b.counters, P, (uint32_t)bp.X,
+                                   b.ctl->hist12, b.status, b.ranges, b.ctl->tile_class, b.class_list, b.sel,
+                                   b.counters + kCntError, s));
+      else
+        HIP_TRY(launch_sort(b.keys_a, b.keys_b, b.vals, b.vals + P, b.counters, P, kDepthPasses,
+                            tile_pass_end(bp.X), b.ctl->hist, b.status, b.ctl->pass_ctr, b.sel,
+                            b.counters + kCntError, s));
+    }
+    {
+      StageScope sc(timer, GSR_STAGE_RANGES, s);
+      if (!tile_sort12(bp.X, P)) {  // (the one-pass grouping writes the ranges and classes itself)
+        HIP_TRY(launch_ranges(b.keys_a, b.keys_b, b.sel, b.counters, P, (uint32_t)bp.X, b.ranges, s));
+        HIP_TRY(launch_tile_order(b.ranges, (uint32_t)bp.X, b.ctl->tile_class, b.class_list, s));
+      }
+    }
+    {
+      StageScope sc(timer, GSR_STAGE_SORT, s);
+      HIP_TRY(launch_sort_segments(b.keys_a, b.keys_b, b.vals, b.vals + P, b.sel, b.ranges, (uint32_t)bp.X, b.rec_of,
+                                   b.counters, P, nullptr, nullptr, b.ctl->tile_class, b.class_list,
                                    &b.ctl->seg_ticket, b.counters + kCntError, s));
+    }
   }
   {
     StageScope sc(timer, GSR_STAGE_BLEND, s);

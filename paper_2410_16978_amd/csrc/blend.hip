@@ -610,7 +610,8 @@ k_blend_bwd(const ViewD* __restrict__ views, int n_views, const float* __restric
             const uint32_t* __restrict__ batch_tile, uint32_t n_batches, const uint32_t* __restrict__ order_cnt,
             const uint32_t* __restrict__ order_list, const float* __restrict__ dL_drgb,
             const float* __restrict__ dL_dalpha, const uint32_t* __restrict__ pair_emit,
-            float* __restrict__ g_pair, uint8_t* __restrict__ alive, int want_max) {
+            const uint2* __restrict__ boxes, const uint32_t* __restrict__ offsets, float* __restrict__ g_pair,
+            uint8_t* __restrict__ alive, int want_max) {
   __shared__ BatchLds L;
   constexpr int kSub = 64;  // pairs whose wave partials are held in LDS at a time
   // one float of padding per row: the nine lanes that store a pair's sums
@@ -705,8 +706,21 @@ k_blend_bwd(const ViewD* __restrict__ views, int n_views, const float* __restric
     const uint16_t* blk = reinterpret_cast<const uint16_t*>(pair_vals + (*sel ? 0u : cap));
     s_blk[tid] = tid < n ? blk[start + tid] : (uint16_t)0;
   }
-  uint32_t my_emit = tid < n ? pair_emit[start + tid] : 0u;
-  if (my_emit >= cap) my_emit = 0;  // never write out of range (an inconsistent sort shows up as wrong gradients)
+  // emission index of the pair, where its partial goes: as the per-tile sort
+  // left it, or (order-first) the record's first one plus the tile's place in
+  // its box.  One at or beyond the capacity is not written.
+  uint32_t my_emit = cap;
+  if (tid < n) {
+    if (boxes) {
+      const uint32_t r = vals[start + tid];
+      if (r < n_rec) {
+        const uint2 bx = boxes[r];
+        my_emit = offsets[r] + ((uint32_t)ty - (bx.x >> 16)) * (bx.y & 0xFFFFu) + ((uint32_t)tx - (bx.x & 0xFFFFu));
+      }
+    } else {
+      my_emit = pair_emit[start + tid];
+    }
+  }
   for (int i = tid; i < 4 * kGradSlots * kSubPad; i += 256) (&part[0][0][0])[i] = 0.f;
   // the wave's 8 x 8 quadrant: 2 x 2 of the tile's 4 x 4 blocks
   const uint32_t qmask = 0x33u << (2 * (wave & 1) + 8 * (wave >> 1));
@@ -848,11 +862,13 @@ k_blend_bwd(const ViewD* __restrict__ views, int n_views, const float* __restric
         for (int q = 0; q < kGradSlots; ++q) part[w][q][js] = 0.f;
       o[10] = 0.f;
       o[11] = 0.f;
-      float4* dst = reinterpret_cast<float4*>(g_pair + (size_t)my_emit * 12);
-      dst[0] = make_float4(o[0], o[1], o[2], o[3]);
-      dst[1] = make_float4(o[4], o[5], o[6], o[7]);
-      dst[2] = make_float4(o[8], o[9], o[10], o[11]);
-      alive[my_emit] = 1;
+      if (my_emit < cap) {
+        float4* dst = reinterpret_cast<float4*>(g_pair + (size_t)my_emit * 12);
+        dst[0] = make_float4(o[0], o[1], o[2], o[3]);
+        dst[1] = make_float4(o[4], o[5], o[6], o[7]);
+        dst[2] = make_float4(o[8], o[9], o[10], o[11]);
+        alive[my_emit] = 1;
+      }
     }
     __syncthreads();
   }
@@ -862,12 +878,12 @@ hipError_t launch_blend_bwd(const ViewD* views_dev, int n_views, const float* re
                             const uint32_t* pair_vals, const uint32_t* sel, uint32_t cap, const uint32_t* ranges,
                             const float4* ckpt, const uint32_t* batch_tile, uint32_t n_batches,
                             const uint32_t* order_cnt, const uint32_t* order_list, const float* dL_drgb,
-                            const float* dL_dalpha, const uint32_t* pair_emit, float* g_pair, uint8_t* alive,
-                            bool want_max, hipStream_t s) {
+                            const float* dL_dalpha, const uint32_t* pair_emit, const uint2* boxes,
+                            const uint32_t* offsets, float* g_pair, uint8_t* alive, bool want_max, hipStream_t s) {
   if (n_batches == 0) return hipSuccess;
   hipLaunchKernelGGL(k_blend_bwd, dim3(n_batches), dim3(256), 0, s, views_dev, n_views, records, n_rec, pair_vals,
                      sel, cap, ranges, ckpt, batch_tile, n_batches, order_cnt, order_list, dL_drgb, dL_dalpha,
-                     pair_emit, g_pair, alive, want_max ? 1 : 0);
+                     pair_emit, boxes, offsets, g_pair, alive, want_max ? 1 : 0);
   return hipGetLastError();
 }
 

@@ -63,16 +63,19 @@ struct ViewD {
   float* alpha;        // [H][W]
   float* pix;          // [H][W][4]: final transmittance, colour before the background
   uint32_t* last;      // [H][W]
-  // Depth order of a call that sorts Gaussians before pairing them (one
-  // order shared by the eyes of a stereo frame, Sec. 3.3): kSortNone in the
-  // per-tile path; a sort unit's records take slots [sort_off, sort_off + n)
-  // of the Gaussian sort, keyed by (sort_unit, depth) with the depth its own
-  // (kSortOwn) or the sort camera's, sort_r . mean + sort_t (kSortCamera); a
+  // Depth order of a call that sorts records before pairing them (order.hip):
+  // kSortNone in the per-tile path; a sort unit's records take slots
+  // [sort_off, sort_off + sort_n) of the record sort, keyed by the view's own
+  // depth (kSortOwn) or the sort camera's, sort_r . mean + sort_t
+  // (kSortCamera, the eyes of a stereo frame sharing one order, Sec. 3.3); a
   // follower (kSortFollow) takes the order of view sort_lead.
   uint32_t sort_mode;
-  uint32_t sort_unit;
   uint32_t sort_off;
+  uint32_t sort_n;
   uint32_t sort_lead;
+  uint32_t sort_blk;    // first block of the unit in the record passes
+  uint32_t seq_blk;     // first block of the view in the emission
+  uint32_t sort_whole;  // kSortCamera: the unit's views are all in one projection job
   float sort_r[3];
   float sort_t;
   float layer_op[32];  // opacity factor per layer (1 when the view has no fading)
@@ -80,6 +83,18 @@ struct ViewD {
   float mip_var;
 };
 constexpr uint32_t kSortNone = 0, kSortOwn = 1, kSortCamera = 2, kSortFollow = 3;
+constexpr uint32_t kSortCulled = 0xFFFFFFFFu;  // sort key of a record no view of its unit keeps (never a depth)
+constexpr uint32_t kRecTile = 4096;   // records per block of a record pass
+constexpr uint32_t kRecSmall = 8192;  // units up to this size are sorted by one block each
+// Sequence positions per run of the emission: with 4096 the tickets of 32M
+// positions do not queue up, with 1024 two million positions fill the chip.
+constexpr uint32_t kEmitTile = 4096, kEmitTileSmall = 1024;
+inline uint32_t emit_tile(uint64_t records) { return records > (8u << 20) ? kEmitTile : kEmitTileSmall; }
+constexpr uint32_t kPairBlocks = 512;  // blocks of a tile-digit pass at most
+// pairs a block of a tile-digit pass handles at a time
+constexpr uint32_t kPairStep = 8192, kPairStepSmall = 2048;
+inline uint32_t pair_step(uint32_t cap) { return cap > kPairBlocks * kPairStepSmall ? kPairStep : kPairStepSmall; }
+constexpr int kMaxTilePasses = 4;     // tile digits of at most 8 bits
 
 constexpr int kFmtF32 = 0, kFmtHalfPacked = 1, kFmtHalfCodebook = 2;
 struct ModelD {
@@ -154,7 +169,7 @@ __device__ __forceinline__ uint32_t wave_or(uint32_t x) {
 // Launchers (host side, defined in the .hip files).  All enqueue on `s`.
 namespace gsr {
 
-constexpr int kClearRanges = 12;
+constexpr int kClearRanges = 16;
 struct ClearSet {
   uint32_t* p[kClearRanges];
   size_t n[kClearRanges];
@@ -173,27 +188,49 @@ hipError_t launch_upload(uint32_t* dst, const void* src, size_t n_words, hipStre
 hipError_t launch_activate(const ModelD& m, float* scale_out, float* opacity_out, hipStream_t s);
 hipError_t launch_clear_u32(uint32_t* p, size_t n, hipStream_t s);
 hipError_t launch_project(const JobD& job, const ViewD* views_dev, float* records, uint32_t* n_tiles,
-                          uint4* tile_box, uint64_t* sort_keys, uint32_t* sort_vals, uint32_t* counters,
-                          hipStream_t s);
+                          uint4* tile_box, uint2* boxes, uint32_t* sort_keys, uint32_t* counters, hipStream_t s);
 uint32_t scan_tiles(uint32_t n);
 hipError_t launch_scan(const uint32_t* in, uint32_t* out, uint64_t* status, uint32_t* ticket, uint32_t n,
                        uint32_t* counters, uint32_t pair_capacity, hipStream_t s);
 hipError_t launch_duplicate(const uint32_t* n_tiles, const uint32_t* offsets, const uint4* tile_box,
                             uint32_t n_rec, const uint32_t* counters, uint32_t pair_capacity,
-                            uint64_t* keys, uint32_t* vals, uint32_t* rec_of, hipStream_t s,
-                            const uint32_t* rec_map = nullptr);
-hipError_t launch_set_u32(uint32_t* p, uint32_t value, hipStream_t s);
-hipError_t launch_seq_build(const ViewD* views_dev, int n_views, uint32_t n_rec, const uint64_t* sk_a,
-                            const uint64_t* sk_b, const uint32_t* sv_a, const uint32_t* sv_b, const uint32_t* sel,
-                            uint32_t n_sort, const uint32_t* n_tiles, const uint4* tile_box, uint32_t* seq_rec,
-                            uint32_t* n_tiles_seq, uint4* tile_box_seq, uint32_t* counters, hipStream_t s);
-hipError_t launch_finalize_pairs(uint32_t* vals_a, uint32_t* vals_b, const uint64_t* keys_a, const uint64_t* keys_b,
-                                 const uint32_t* sel, const uint32_t* rec_of, const uint32_t* counters,
-                                 uint32_t pair_capacity, uint32_t* emit, uint64_t* keys_out, hipStream_t s);
+                            uint64_t* keys, uint32_t* vals, uint32_t* rec_of, hipStream_t s);
+// Buffers of the order-first path (order.hip).
+struct OrderBufs {
+  const ViewD* views;
+  int n_views;
+  uint32_t n_tiles;               // of all views
+  uint32_t rec_blocks, seq_blocks, seq_tile;
+  bool small;                     // every unit has at most kRecSmall records
+  uint32_t *keys_a, *keys_b;      // depth keys by sort slot (the projection writes keys_a), double-buffered
+  uint32_t *vals_a, *vals_b;      // records by sort slot
+  uint32_t* rec_hist;             // [n_views][4][256]
+  uint32_t* rec_status;           // [4][rec_blocks][256]
+  uint32_t* unit;                 // [n_views][2]
+  const uint2* boxes;             // [R] x0 | y0 << 16, w | h << 16 in tiles of the view
+  uint32_t* counters;
+  uint32_t cap;
+  uint32_t *tile_a, *tile_b;      // tiles by pair (2 or 4 bytes each), double-buffered
+  uint32_t *rec_a, *rec_b;        // records by pair, double-buffered
+  uint64_t* emit_status;          // [seq_blocks]
+  uint32_t* pair_counts;          // [pair_pass_blocks][256]
+  uint32_t* tile_total;           // [256]
+  uint32_t* tickets;              // [8]: record passes, emission
+  uint32_t* ranges;
+  uint32_t* sel;
+};
+void tile_passes(uint32_t n_tiles, int* bits, int* np);
+uint32_t pair_pass_blocks(uint32_t cap);
+hipError_t launch_order_scan(const OrderBufs& o, const uint32_t* n_tiles, uint32_t* offsets, uint64_t* scan_status,
+                             uint32_t* scan_ticket, uint32_t n_rec, hipStream_t s);
+hipError_t launch_order(const OrderBufs& o, hipStream_t s);
+hipError_t launch_order_debug(const OrderBufs& o, uint32_t n_rec, const float* records, const uint32_t* offsets,
+                              uint32_t* tile_box, uint64_t* keys_emit, uint32_t* vals_emit, uint64_t* keys_sorted,
+                              hipStream_t s);
 hipError_t launch_sort(uint64_t* keys_a, uint64_t* keys_b, uint32_t* vals_a, uint32_t* vals_b,
                        const uint32_t* counters, uint32_t pair_capacity, int pass_begin, int pass_end,
                        uint32_t* hist, uint32_t* status, uint32_t* pass_ctr, uint32_t* sel_out,
-                       uint32_t* error_flag, hipStream_t s, const uint32_t* sel_in = nullptr);
+                       uint32_t* error_flag, hipStream_t s);
 size_t sort_status_stride(uint32_t pair_capacity);
 constexpr uint32_t kXcds = 8;  // accelerator dies per MI355X, each with its own L2
 constexpr uint32_t kT12MaxPairs = 1u << 24;  // the one-pass tile grouping keeps per-block tile counts: 4 B per pair slot
@@ -247,8 +284,9 @@ hipError_t launch_blend_bwd(const ViewD* views_dev, int n_views, const float* re
                             const uint32_t* pair_vals, const uint32_t* sel, uint32_t cap, const uint32_t* ranges,
                             const float4* ckpt, const uint32_t* batch_tile, uint32_t n_batches,
                             const uint32_t* order_cnt, const uint32_t* order_list,
-                            const float* dL_drgb, const float* dL_dalpha, const uint32_t* pair_emit, float* g_pair,
-                            uint8_t* alive, bool want_max, hipStream_t s);
+                            const float* dL_drgb, const float* dL_dalpha, const uint32_t* pair_emit,
+                            const uint2* boxes, const uint32_t* offsets, float* g_pair, uint8_t* alive,
+                            bool want_max, hipStream_t s);
 hipError_t launch_project_bwd(const JobD& job, const ViewD* views_dev, const float* records,
                               const uint32_t* offsets, const float* g_pair, const uint8_t* alive,
                               uint32_t pair_capacity,

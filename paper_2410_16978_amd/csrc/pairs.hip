@@ -3,146 +3,15 @@
 // pairs in emission order, and per-tile [start, end) ranges of the sorted
 // pairs.
 #include "common.hpp"
+#include "scan.hpp"
 
 namespace gsr {
 
 // ---------------------------------------------------------------- scan
-__device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t x) { return wave_scan_add(x); }
-
-// Block-wide exclusive scan of one value per thread (256 threads = 4 waves).
-__device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t x, uint32_t* lds_waves, uint32_t* total) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const uint32_t inc = wave_inclusive_scan(x);
-  if (lane == 63) lds_waves[wave] = inc;
-  __syncthreads();
-  uint32_t wave_off = 0, tot = 0;
-#pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    const uint32_t c = lds_waves[w];
-    if (w < wave) wave_off += c;
-    tot += c;
-  }
-  __syncthreads();
-  *total = tot;
-  return wave_off + inc - x;
-}
-
-// Single pass with decoupled look-back: blocks take their tile index from a
-// ticket (so a block only waits for blocks already running), publish the
-// tile's total, and the first wave looks back over 64 predecessors at a time
-// for the nearest inclusive prefix.  Status words: flag in the top 2 bits,
-// 62-bit value.  The last tile writes the total K and the capacity check to
-// counters.
-constexpr uint64_t kScanAgg = 1ull << 62;
-constexpr uint64_t kScanIncl = 2ull << 62;
-constexpr uint64_t kScanValue = (1ull << 62) - 1;
-constexpr uint32_t kScanSpinLimit = 1u << 22;
-
 __global__ void __launch_bounds__(kScanThreads)
 k_scan(const uint32_t* __restrict__ in, uint32_t n, uint32_t* __restrict__ out, uint64_t* __restrict__ status,
        uint32_t* __restrict__ ticket, uint32_t* __restrict__ counters, uint32_t pair_capacity) {
-  __shared__ uint32_t lds[4];
-  __shared__ uint32_t s_bid;
-  __shared__ uint64_t s_excl;
-  if (threadIdx.x == 0) s_bid = atomicAdd(ticket, 1u);
-  __syncthreads();
-  const uint32_t bid = s_bid;
-  const uint32_t nb = gridDim.x;
-  // thread t owns kScanItems consecutive items
-  const uint32_t base = bid * (uint32_t)kScanTile + threadIdx.x * kScanItems;
-  uint32_t v[kScanItems];
-  if (base + kScanItems <= n) {
-    const uint4* in4 = reinterpret_cast<const uint4*>(in + base);  // 64-byte aligned run
-#pragma unroll
-    for (int k = 0; k < kScanItems / 4; ++k) {
-      const uint4 q = in4[k];
-      v[4 * k] = q.x;
-      v[4 * k + 1] = q.y;
-      v[4 * k + 2] = q.z;
-      v[4 * k + 3] = q.w;
-    }
-  } else {
-#pragma unroll
-    for (int k = 0; k < kScanItems; ++k) v[k] = (base + k < n) ? in[base + k] : 0u;
-  }
-  uint32_t sum = 0;
-#pragma unroll
-  for (int k = 0; k < kScanItems; ++k) sum += v[k];
-  uint32_t total;
-  const uint32_t local = block_exclusive_scan(sum, lds, &total);
-  if (threadIdx.x < 64) {
-    const int lane = threadIdx.x;
-    if (lane == 0)
-      __hip_atomic_store(&status[bid], (bid == 0 ? kScanIncl : kScanAgg) | total, __ATOMIC_RELAXED,
-                         __HIP_MEMORY_SCOPE_AGENT);
-    uint64_t excl = 0;
-    if (bid > 0) {
-      int j = (int)bid - 1;  // window [j - 63, j]
-      uint32_t spins = 0;
-      for (;;) {
-        const int idx = j - lane;
-        const uint64_t sv =
-            idx >= 0 ? __hip_atomic_load(&status[idx], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : kScanIncl;
-        const uint64_t flag = sv & ~kScanValue;
-        const uint64_t ready = __ballot(flag != 0);
-        const uint64_t incl = __ballot(flag == kScanIncl);
-        // lanes up to the first inclusive one, all ready: sum them
-        const int first_incl = incl ? __builtin_ctzll(incl) : 64;
-        const uint64_t need = first_incl < 63 ? ((2ull << first_incl) - 1) : ~0ull;
-        if ((ready & need) != need) {
-          if (++spins > kScanSpinLimit) {
-            if (lane == 0) atomicOr(&counters[kCntError], 16u);
-            break;
-          }
-          __builtin_amdgcn_s_sleep(1);
-          continue;
-        }
-        uint64_t x = (lane <= first_incl && idx >= 0) ? (sv & kScanValue) : 0ull;
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
-        excl += x;
-        if (first_incl < 64) break;
-        j -= 64;
-      }
-      if (lane == 0)
-        __hip_atomic_store(&status[bid], kScanIncl | ((excl + total) & kScanValue), __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
-    }
-    if (lane == 0) {
-      s_excl = excl;
-      if (bid == nb - 1) {
-        const uint64_t K = excl + total;
-        counters[kCntPairs] = K > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)K;
-        if (K > pair_capacity) atomicOr(&counters[kCntOverflow], 1u);  // sticky until the caller checks
-      }
-    }
-  }
-  __syncthreads();
-  uint32_t run = (uint32_t)s_excl + local;
-  if (base + kScanItems <= n && (reinterpret_cast<uintptr_t>(out) & 15) == 0) {
-    uint4* out4 = reinterpret_cast<uint4*>(out + base);
-#pragma unroll
-    for (int k = 0; k < kScanItems / 4; ++k) {
-      uint4 q;
-      q.x = run;
-      run += v[4 * k];
-      q.y = run;
-      run += v[4 * k + 1];
-      q.z = run;
-      run += v[4 * k + 2];
-      q.w = run;
-      run += v[4 * k + 3];
-      out4[k] = q;
-    }
-  } else {
-#pragma unroll
-    for (int k = 0; k < kScanItems; ++k) {
-      if (base + k < n) out[base + k] = run;
-      run += v[k];
-    }
-  }
-  // out[n] = total, written by the thread that owns the end
-  if (base <= n && n < base + kScanItems) out[n] = run;
+  scan_block<kScanThreads>(in, n, out, status, ticket, counters, pair_capacity, gridDim.x);
 }
 
 uint32_t scan_tiles(uint32_t n) { return div_up(n + 1, (uint32_t)kScanTile); }
@@ -165,13 +34,12 @@ hipError_t launch_scan(const uint32_t* in, uint32_t* out, uint64_t* status, uint
 // lane.  Pairs at or beyond min(capacity, counters[pairs]) are dropped (the
 // overflow flag or the batch status already records it).  The sort carries
 // each pair's emission index as its value; rec_of[e] keeps the record of
-// emission index e (rec_map[j] when the records were given in another
-// order, the j-th of the arrays being record rec_map[j]).
+// emission index e.
 __global__ void __launch_bounds__(256)
 k_duplicate(const uint32_t* __restrict__ n_tiles, const uint32_t* __restrict__ offsets,
             const uint4* __restrict__ tile_box, uint32_t n_rec, const uint32_t* __restrict__ counters,
             uint32_t pair_capacity, uint64_t* __restrict__ keys, uint32_t* __restrict__ vals,
-            uint32_t* __restrict__ rec_of, const uint32_t* __restrict__ rec_map) {
+            uint32_t* __restrict__ rec_of) {
   const uint32_t r = blockIdx.x * blockDim.x + threadIdx.x;
   const int lane = threadIdx.x & 63;
   const uint32_t lim = min(pair_capacity, counters[kCntPairs]);
@@ -214,135 +82,17 @@ k_duplicate(const uint32_t* __restrict__ n_tiles, const uint32_t* __restrict__ o
       const uint32_t tile = bx + dy * bw + (j - dy * w);
       keys[e] = ((uint64_t)tile << 32) | bz;
       vals[e] = e;
-      rec_of[e] = rec_map ? rec_map[r0 + (uint32_t)lo] : r0 + (uint32_t)lo;
+      rec_of[e] = r0 + (uint32_t)lo;
     }
   }
 }
 
 hipError_t launch_duplicate(const uint32_t* n_tiles, const uint32_t* offsets, const uint4* tile_box,
                             uint32_t n_rec, const uint32_t* counters, uint32_t pair_capacity,
-                            uint64_t* keys, uint32_t* vals, uint32_t* rec_of, hipStream_t s,
-                            const uint32_t* rec_map) {
+                            uint64_t* keys, uint32_t* vals, uint32_t* rec_of, hipStream_t s) {
   if (n_rec == 0) return hipSuccess;
   hipLaunchKernelGGL(k_duplicate, dim3(div_up(n_rec, 256u)), dim3(256), 0, s, n_tiles, offsets, tile_box,
-                     n_rec, counters, pair_capacity, keys, vals, rec_of, rec_map);
-  return hipGetLastError();
-}
-
-// ---------------------------------------------------------------- depth order first
-// Calls whose Gaussians are depth-sorted before they are paired (one order
-// for the eyes of a stereo frame, Sec. 3.3) emit each view's records in the
-// sorted order; a stable grouping of the pairs by tile then leaves every
-// tile's pairs in depth order, with no per-tile sort.
-
-__global__ void k_set_u32(uint32_t* p, uint32_t value) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) *p = value;
-}
-
-hipError_t launch_set_u32(uint32_t* p, uint32_t value, hipStream_t s) {
-  hipLaunchKernelGGL(k_set_u32, dim3(1), dim3(64), 0, s, p, value);
-  return hipGetLastError();
-}
-
-// View whose records include record r (views are in record order).
-__device__ __forceinline__ int view_of_record(const ViewD* __restrict__ views, int n_views, uint32_t r) {
-  int lo = 0, hi = n_views - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (views[mid].rec_off <= r) lo = mid; else hi = mid - 1;
-  }
-  return lo;
-}
-
-// Position s of the emission sequence (view by view, each view's records in
-// its unit's depth order, a follower in its lead's): the record, its tile
-// count, and its tile box whose depth word is the sort key (the pair keys'
-// low word).  A culled record (no tiles) keeps a zero box.
-__global__ void __launch_bounds__(256)
-k_seq_build(const ViewD* __restrict__ views, int n_views, uint32_t n_rec, const uint64_t* __restrict__ sk_a,
-            const uint64_t* __restrict__ sk_b, const uint32_t* __restrict__ sv_a, const uint32_t* __restrict__ sv_b,
-            const uint32_t* __restrict__ sel, uint32_t n_sort, const uint32_t* __restrict__ n_tiles,
-            const uint4* __restrict__ tile_box, uint32_t* __restrict__ seq_rec, uint32_t* __restrict__ n_tiles_seq,
-            uint4* __restrict__ tile_box_seq, uint32_t* __restrict__ counters) {
-  const bool side = *sel != 0;
-  const uint64_t* keys = side ? sk_b : sk_a;
-  const uint32_t* vals = side ? sv_b : sv_a;
-  for (uint32_t s = blockIdx.x * blockDim.x + threadIdx.x; s < n_rec; s += gridDim.x * blockDim.x) {
-    const int v = view_of_record(views, n_views, s);
-    const ViewD& V = views[v];
-    const uint32_t lead = V.sort_mode == kSortFollow ? V.sort_lead : (uint32_t)v;
-    const uint32_t v_end = v + 1 < n_views ? views[v + 1].rec_off : n_rec;
-    uint32_t rec = s, nt = 0, key = 0;
-    bool ok = lead < (uint32_t)n_views;
-    if (ok) {
-      const ViewD& L = views[lead];
-      const uint32_t slot = L.sort_off + (s - V.rec_off);
-      ok = slot < n_sort;
-      if (ok) {
-        const uint32_t lead_rec = vals[slot];
-        const uint32_t gi = lead_rec - L.rec_off;  // the Gaussian (wraps when out of range)
-        key = (uint32_t)keys[slot];
-        ok = lead_rec >= L.rec_off && V.rec_off + gi < v_end;
-        if (ok) rec = V.rec_off + gi;
-      }
-    }
-    if (!ok) atomicOr(&counters[kCntError], 64u);  // an inconsistent order: the pairs of s are dropped
-    if (ok) nt = n_tiles[rec];
-    uint4 tb = make_uint4(0u, 0u, 0u, 0u);
-    if (nt) {
-      tb = tile_box[rec];
-      tb.z = key;
-    }
-    seq_rec[s] = rec;
-    n_tiles_seq[s] = nt;
-    tile_box_seq[s] = tb;
-  }
-}
-
-hipError_t launch_seq_build(const ViewD* views_dev, int n_views, uint32_t n_rec, const uint64_t* sk_a,
-                            const uint64_t* sk_b, const uint32_t* sv_a, const uint32_t* sv_b, const uint32_t* sel,
-                            uint32_t n_sort, const uint32_t* n_tiles, const uint4* tile_box, uint32_t* seq_rec,
-                            uint32_t* n_tiles_seq, uint4* tile_box_seq, uint32_t* counters, hipStream_t s) {
-  if (n_rec == 0) return hipSuccess;
-  uint32_t grid = div_up(n_rec, 256u);
-  if (grid > 16384) grid = 16384;
-  hipLaunchKernelGGL(k_seq_build, dim3(grid), dim3(256), 0, s, views_dev, n_views, n_rec, sk_a, sk_b, sv_a, sv_b,
-                     sel, n_sort, n_tiles, tile_box, seq_rec, n_tiles_seq, tile_box_seq, counters);
-  return hipGetLastError();
-}
-
-// After the tile grouping of depth-ordered pairs: each sorted pair's value
-// (its emission index) becomes its record id; the emission index goes to
-// emit and the key to keys_out (both nullable).
-__global__ void __launch_bounds__(256)
-k_finalize_pairs(uint32_t* __restrict__ vals_a, uint32_t* __restrict__ vals_b, const uint64_t* __restrict__ keys_a,
-                 const uint64_t* __restrict__ keys_b, const uint32_t* __restrict__ sel,
-                 const uint32_t* __restrict__ rec_of, uint32_t* __restrict__ counters, uint32_t pair_capacity,
-                 uint32_t* __restrict__ emit, uint64_t* __restrict__ keys_out) {
-  const uint32_t K = min(counters[kCntPairs], pair_capacity);
-  const bool side = *sel != 0;
-  uint32_t* vals = side ? vals_b : vals_a;
-  const uint64_t* keys = side ? keys_b : keys_a;
-  for (uint32_t k = blockIdx.x * blockDim.x + threadIdx.x; k < K; k += gridDim.x * blockDim.x) {
-    uint32_t e = vals[k];
-    if (e >= K) {
-      atomicOr(&counters[kCntError], 64u);
-      e = 0;
-    }
-    vals[k] = rec_of[e];
-    if (emit) emit[k] = e;
-    if (keys_out) keys_out[k] = keys[k];
-  }
-}
-
-hipError_t launch_finalize_pairs(uint32_t* vals_a, uint32_t* vals_b, const uint64_t* keys_a, const uint64_t* keys_b,
-                                 const uint32_t* sel, const uint32_t* rec_of, const uint32_t* counters,
-                                 uint32_t pair_capacity, uint32_t* emit, uint64_t* keys_out, hipStream_t s) {
-  if (pair_capacity == 0) return hipSuccess;
-  uint32_t grid = div_up(pair_capacity, 256u);
-  if (grid > 16384) grid = 16384;
-  hipLaunchKernelGGL(k_finalize_pairs, dim3(grid), dim3(256), 0, s, vals_a, vals_b, keys_a, keys_b, sel, rec_of,
-                     const_cast<uint32_t*>(counters), pair_capacity, emit, keys_out);
+                     n_rec, counters, pair_capacity, keys, vals, rec_of);
   return hipGetLastError();
 }
 

@@ -208,8 +208,8 @@ __device__ __forceinline__ bool view_may_keep(const ViewD& V, uint32_t layer, fl
 template <int D, int F>
 __global__ void __launch_bounds__(256)
 k_project(JobD job, const ViewD* __restrict__ views, float* __restrict__ records,
-          uint32_t* __restrict__ n_tiles_out, uint4* __restrict__ tile_box, uint64_t* __restrict__ sort_keys,
-          uint32_t* __restrict__ sort_vals, uint32_t* __restrict__ counters) {
+          uint32_t* __restrict__ n_tiles_out, uint4* __restrict__ tile_box, uint2* __restrict__ boxes,
+          uint32_t* __restrict__ sort_keys, uint32_t* __restrict__ counters) {
   constexpr int NC = (D + 1) * (D + 1);
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   const ModelD& m = job.m;
@@ -239,12 +239,14 @@ k_project(JobD job, const ViewD* __restrict__ views, float* __restrict__ records
   }
   float Rq[9];
   float qn = -1.f;  // < 0: rotation not computed yet
+  uint32_t kept = 0u;  // bit per view of the job
 
   for (int jv = 0; jv < job.n_views; ++jv) {
     const ViewD& V = views[job.view[jv]];
     const uint32_t r = V.rec_off + (uint32_t)i;
     uint32_t nt = 0;
-    uint32_t own_key = 0xFFFFFFFFu;  // depth bits of a kept record (culled ones sort last)
+    uint32_t own_key = kSortCulled;  // depth bits of a kept record
+    uint2 box = make_uint2(0u, 0u);
     do {
       // layer activation mask
       if (layer >= 32u || !((V.layer_mask >> layer) & 1u)) break;
@@ -376,20 +378,17 @@ k_project(JobD job, const ViewD* __restrict__ views, float* __restrict__ records
       rec[0] = make_float4(u, v, ca, cb);
       rec[1] = make_float4(cc, opf, rgb[0], rgb[1]);
       rec[2] = make_float4(rgb[2], tz, __uint_as_float(clamp_bits), __uint_as_float(nt));
-      const uint32_t base_tile = V.tile_off + (uint32_t)y0 * (uint32_t)V.tiles_x + (uint32_t)x0;
-      tile_box[r] = make_uint4(base_tile, (uint32_t)(x1 - x0) | ((uint32_t)(y1 - y0) << 16),
-                               __float_as_uint(tz), (uint32_t)V.tiles_x);
+      box = make_uint2((uint32_t)x0 | ((uint32_t)y0 << 16), (uint32_t)(x1 - x0) | ((uint32_t)(y1 - y0) << 16));
+      if (!boxes) {
+        const uint32_t base_tile = V.tile_off + (uint32_t)y0 * (uint32_t)V.tiles_x + (uint32_t)x0;
+        tile_box[r] = make_uint4(base_tile, box.y, __float_as_uint(tz), (uint32_t)V.tiles_x);
+      }
       own_key = __float_as_uint(tz);
+      kept |= 1u << jv;
     } while (false);
-    if (sort_keys && (V.sort_mode == kSortOwn || V.sort_mode == kSortCamera)) {
-      // the Gaussian's key in its sort unit: its own depth, or (every
-      // Gaussian, kept in this view or not: a follower view may keep it) its
-      // depth in the sort camera, in the order of the view's own depth
-      const uint32_t key = V.sort_mode == kSortOwn
-                               ? own_key
-                               : __float_as_uint(((V.sort_r[0] * mx + V.sort_r[1] * my) + V.sort_r[2] * mz) + V.sort_t);
-      sort_keys[V.sort_off + (uint32_t)i] = ((uint64_t)V.sort_unit << 32) | key;
-      sort_vals[V.sort_off + (uint32_t)i] = r;
+    if (boxes) {
+      boxes[r] = box;
+      if (V.sort_mode == kSortOwn) sort_keys[V.sort_off + (uint32_t)i] = own_key;
     }
     n_tiles_out[r] = nt;
     if (nt == 0) {
@@ -397,41 +396,54 @@ k_project(JobD job, const ViewD* __restrict__ views, float* __restrict__ records
       records[(size_t)r * kRecordFloats + 11] = __uint_as_float(0u);
     }
   }
+  if (!boxes) return;
+  // Units that share one order: the Gaussian's depth in the sort camera, if
+  // any view of the unit keeps it (a unit whose views another job also
+  // projects keeps every Gaussian).
+  for (int jv = 0; jv < job.n_views; ++jv) {
+    const ViewD& V = views[job.view[jv]];
+    if (V.sort_mode != kSortCamera) continue;
+    bool any = V.sort_whole == 0u || ((kept >> jv) & 1u);
+    for (int j2 = 0; j2 < job.n_views; ++j2) {
+      const ViewD& E = views[job.view[j2]];
+      any = any || (E.sort_mode == kSortFollow && (int)E.sort_lead == job.view[jv] && ((kept >> j2) & 1u));
+    }
+    const uint32_t key = __float_as_uint(((V.sort_r[0] * mx + V.sort_r[1] * my) + V.sort_r[2] * mz) + V.sort_t);
+    sort_keys[V.sort_off + (uint32_t)i] = any ? key : kSortCulled;
+  }
 }
 
 namespace {
 template <int F>
 void launch_project_fmt(const JobD& job, const ViewD* views_dev, float* records, uint32_t* n_tiles,
-                        uint4* tile_box, uint64_t* sort_keys, uint32_t* sort_vals, uint32_t* counters,
-                        hipStream_t s) {
+                        uint4* tile_box, uint2* boxes, uint32_t* sort_keys, uint32_t* counters, hipStream_t s) {
   const dim3 grid(div_up((uint32_t)job.m.n, 256u)), block(256);
   switch (job.m.D) {
     case 0: hipLaunchKernelGGL((k_project<0, F>), grid, block, 0, s, job, views_dev, records, n_tiles, tile_box,
-                               sort_keys, sort_vals, counters); break;
+                               boxes, sort_keys, counters); break;
     case 1: hipLaunchKernelGGL((k_project<1, F>), grid, block, 0, s, job, views_dev, records, n_tiles, tile_box,
-                               sort_keys, sort_vals, counters); break;
+                               boxes, sort_keys, counters); break;
     case 2: hipLaunchKernelGGL((k_project<2, F>), grid, block, 0, s, job, views_dev, records, n_tiles, tile_box,
-                               sort_keys, sort_vals, counters); break;
+                               boxes, sort_keys, counters); break;
     default: hipLaunchKernelGGL((k_project<3, F>), grid, block, 0, s, job, views_dev, records, n_tiles, tile_box,
-                                sort_keys, sort_vals, counters); break;
+                                boxes, sort_keys, counters); break;
   }
 }
 }  // namespace
 
 hipError_t launch_project(const JobD& job, const ViewD* views_dev, float* records, uint32_t* n_tiles,
-                          uint4* tile_box, uint64_t* sort_keys, uint32_t* sort_vals, uint32_t* counters,
-                          hipStream_t s) {
+                          uint4* tile_box, uint2* boxes, uint32_t* sort_keys, uint32_t* counters, hipStream_t s) {
   if (job.m.n <= 0 || job.n_views <= 0) return hipSuccess;
   switch (job.m.fmt) {
     case kFmtHalfPacked:
-      launch_project_fmt<kFmtHalfPacked>(job, views_dev, records, n_tiles, tile_box, sort_keys, sort_vals, counters, s);
+      launch_project_fmt<kFmtHalfPacked>(job, views_dev, records, n_tiles, tile_box, boxes, sort_keys, counters, s);
       break;
     case kFmtHalfCodebook:
-      launch_project_fmt<kFmtHalfCodebook>(job, views_dev, records, n_tiles, tile_box, sort_keys, sort_vals, counters,
+      launch_project_fmt<kFmtHalfCodebook>(job, views_dev, records, n_tiles, tile_box, boxes, sort_keys, counters,
                                            s);
       break;
     default:
-      launch_project_fmt<kFmtF32>(job, views_dev, records, n_tiles, tile_box, sort_keys, sort_vals, counters, s);
+      launch_project_fmt<kFmtF32>(job, views_dev, records, n_tiles, tile_box, boxes, sort_keys, counters, s);
       break;
   }
   return hipGetLastError();
