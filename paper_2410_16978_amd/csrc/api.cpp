@@ -68,6 +68,7 @@ struct PipeBufs {
   uint32_t* class_list = nullptr;  // [kTileClasses][X] tiles by size class
   float* g_pair = nullptr;
   float* g_col = nullptr;    // [R][3] colour gradient of each record (backward)
+  uint32_t* g_max = nullptr;       // [n] bits of each Gaussian's largest alpha T (backward)
   uint32_t* alive = nullptr;       // [P] bytes (as words): 1 where a pair's partials were written (backward)
   uint32_t* order_cnt = nullptr;   // [kBatchClasses] batches per work class (backward)
   uint32_t* order_list = nullptr;  // [kBatchClasses][batch capacity] batch indices by class (backward)
@@ -149,6 +150,7 @@ size_t carve(Carver& c, PipeBufs& b, size_t n_views, size_t R, size_t P, size_t 
   if (backward) {
     b.g_pair = c.take<float>(12 * (std::max<size_t>(P, 1) + 1));  // + one zero entry, index P
     b.g_col = c.take<float>(3 * std::max<size_t>(R, 1));
+    b.g_max = c.take<uint32_t>(std::max<size_t>(R / std::max<size_t>(n_views, 1), 1));
     b.alive = c.take<uint32_t>(std::max<size_t>(P, 1) / 4 + 1);
     b.order_cnt = c.take<uint32_t>(kBatchClasses);
     b.order_list = c.take<uint32_t>(kBatchClasses * (P / kBatch + X + 1));
@@ -867,7 +869,9 @@ gsr_status gsr_rasterize_backward(const gsr_model* model, int32_t n_views, const
     cs.n[1] = (size_t)P / 4 + 1;
     cs.p[2] = reinterpret_cast<uint32_t*>(b.g_pair + 12 * (size_t)P);  // the zero entry
     cs.n[2] = 12;
-    cs.n_ranges = 3;
+    cs.p[3] = b.g_max;
+    cs.n[3] = max_contrib ? n : 0;
+    cs.n_ranges = 4;
     HIP_TRY(launch_clear_multi(cs, s, up.n ? &up : nullptr));
   }
   const uint32_t* batch_tile = state->batch_map + X + 1;
@@ -881,7 +885,7 @@ gsr_status gsr_rasterize_backward(const gsr_model* model, int32_t n_views, const
                              state->ranges, reinterpret_cast<const float4*>(state->checkpoints), batch_tile,
                              n_batches, b.order_cnt, b.order_list, dL_drgb, dL_dalpha, state->pair_emit,
                              op.on ? reinterpret_cast<const uint2*>(state->pair_emit) : nullptr, state->offsets,
-                             b.g_pair, reinterpret_cast<uint8_t*>(b.alive), max_contrib != nullptr, s));
+                             b.g_pair, reinterpret_cast<uint8_t*>(b.alive), max_contrib ? b.g_max : nullptr, s));
   }
   const ModelD md = make_model(*model);
   {
@@ -890,7 +894,7 @@ gsr_status gsr_rasterize_backward(const gsr_model* model, int32_t n_views, const
       HIP_TRY(launch_project_bwd(j, b.views, state->records, state->offsets, b.g_pair,
                                  reinterpret_cast<const uint8_t*>(b.alive), P,
                                  state->counters, trainable_layers, grads->g_mean, grads->g_scale, grads->g_quat,
-                                 grads->g_opacity, grads->g_sh, b.g_col, max_contrib, activity,
+                                 grads->g_opacity, grads->g_sh, b.g_col, b.g_max, max_contrib, activity,
                                  grads->densify_grad, grads->densify_count, s));
   }
   return GSR_OK;

@@ -83,11 +83,6 @@ __device__ __forceinline__ Staged fetch_record(const float* __restrict__ records
   return st;
 }
 
-__device__ __forceinline__ Staged fetch(const float* __restrict__ records, uint32_t n_rec,
-                                        const uint32_t* __restrict__ vals, uint32_t k, bool ok) {
-  return fetch_record(records, n_rec, ok ? vals[k] : 0u, ok);
-}
-
 // Cut-off of the pair's reach: o exp(-q/2) >= 1/255 needs q <= 2 ln(255 o).
 // A relative margin of 1e-2 plus 0.05 on q covers the rounding of q, exp
 // and this computation, so skipping a pair for pixel centres where its q
@@ -560,9 +555,10 @@ constexpr int kGradSlots = 10;
 
 // g_pair: [P][12] per pair, at its emission index (pair_emit of its sorted
 // position), so that a Gaussian's partials are contiguous: u, v, conic a,
-// b, c, opacity, r, g, b, max alpha*T, 2 unused; alive[e] = 1 marks the
-// entries written (pairs of batches the forward never evaluated at a live
-// pixel are zero and skipped).
+// b, c, opacity, r, g, b, 3 unused; alive[e] = 1 marks the entries written
+// (pairs of batches the forward never evaluated at a live pixel are zero and
+// skipped).  g_max (nullable, zero on entry): the bits of each Gaussian's
+// largest alpha T.
 // The backward's block order: batches by work class, heaviest first, so that
 // the longest blocks start early instead of ending the launch.  Each block
 // buckets 4096 batch words; per class one atomic reserves its range of the
@@ -611,7 +607,7 @@ k_blend_bwd(const ViewD* __restrict__ views, int n_views, const float* __restric
             const uint32_t* __restrict__ order_list, const float* __restrict__ dL_drgb,
             const float* __restrict__ dL_dalpha, const uint32_t* __restrict__ pair_emit,
             const uint2* __restrict__ boxes, const uint32_t* __restrict__ offsets, float* __restrict__ g_pair,
-            uint8_t* __restrict__ alive, int want_max) {
+            uint8_t* __restrict__ alive, uint32_t* __restrict__ g_max) {
   __shared__ BatchLds L;
   constexpr int kSub = 64;  // pairs whose wave partials are held in LDS at a time
   // one float of padding per row: the nine lanes that store a pair's sums
@@ -700,7 +696,8 @@ k_blend_bwd(const ViewD* __restrict__ views, int n_views, const float* __restric
   // thread t stages pair t and later combines its sums (sub-batch t / kSub
   // runs on wave t / kSub), so the pair's exact conic, opacity and emission
   // index stay in its registers
-  const Staged mine = fetch(records, n_rec, vals, start + tid, tid < n);
+  const uint32_t my_rec = tid < n ? vals[start + tid] : n_rec;
+  const Staged mine = fetch_record(records, n_rec, my_rec, tid < n);
   put(L, mine, tid < n, tid);
   {
     const uint16_t* blk = reinterpret_cast<const uint16_t*>(pair_vals + (*sel ? 0u : cap));
@@ -711,14 +708,11 @@ k_blend_bwd(const ViewD* __restrict__ views, int n_views, const float* __restric
   // its box.  One at or beyond the capacity is not written.
   uint32_t my_emit = cap;
   if (tid < n) {
-    if (boxes) {
-      const uint32_t r = vals[start + tid];
-      if (r < n_rec) {
-        const uint2 bx = boxes[r];
-        my_emit = offsets[r] + ((uint32_t)ty - (bx.x >> 16)) * (bx.y & 0xFFFFu) + ((uint32_t)tx - (bx.x & 0xFFFFu));
-      }
-    } else {
+    if (!boxes) {
       my_emit = pair_emit[start + tid];
+    } else if (my_rec < n_rec) {
+      const uint2 bx = boxes[my_rec];
+      my_emit = offsets[my_rec] + ((uint32_t)ty - (bx.x >> 16)) * (bx.y & 0xFFFFu) + ((uint32_t)tx - (bx.x & 0xFFFFu));
     }
   }
   for (int i = tid; i < 4 * kGradSlots * kSubPad; i += 256) (&part[0][0][0])[i] = 0.f;
@@ -827,7 +821,7 @@ k_blend_bwd(const ViewD* __restrict__ views, int n_views, const float* __restric
         float R = (b1 ? W1 : W0) + dpp<0x4E, 0xF>(b1 ? W0 : W1);  // quad_perm [2,3,0,1]
         R += qperm<0xB1>(R);                                        // quad_perm [1,0,3,2]
         if (writer && (!front || hb)) part_lane[front ? jb : ja] = R;
-        if (want_max) {
+        if (g_max) {
           const float mxa = wave_max63(wa);
           const float mxb = wave_max63(wb);
           if (lane == 63) {
@@ -855,13 +849,18 @@ k_blend_bwd(const ViewD* __restrict__ views, int n_views, const float* __restric
       o[6] = m9[6];
       o[7] = m9[7];
       o[8] = m9[8];
-      o[9] = fmaxf(fmaxf(part[0][9][js], part[1][9][js]), fmaxf(part[2][9][js], part[3][9][js]));
+      // the largest alpha T of the Gaussian over its pairs and views: weights
+      // are not negative, so the integer order of the bits is theirs, and a
+      // maximum does not depend on the order it is taken in
+      if (g_max && my_rec < n_rec) {
+        const float w = fmaxf(fmaxf(part[0][9][js], part[1][9][js]), fmaxf(part[2][9][js], part[3][9][js]));
+        if (w > 0.f) atomicMax(&g_max[my_rec - V.rec_off], __float_as_uint(w));
+      }
 #pragma unroll
       for (int w = 0; w < 4; ++w)
 #pragma unroll
         for (int q = 0; q < kGradSlots; ++q) part[w][q][js] = 0.f;
-      o[10] = 0.f;
-      o[11] = 0.f;
+      o[9] = o[10] = o[11] = 0.f;
       if (my_emit < cap) {
         float4* dst = reinterpret_cast<float4*>(g_pair + (size_t)my_emit * 12);
         dst[0] = make_float4(o[0], o[1], o[2], o[3]);
@@ -879,11 +878,12 @@ hipError_t launch_blend_bwd(const ViewD* views_dev, int n_views, const float* re
                             const float4* ckpt, const uint32_t* batch_tile, uint32_t n_batches,
                             const uint32_t* order_cnt, const uint32_t* order_list, const float* dL_drgb,
                             const float* dL_dalpha, const uint32_t* pair_emit, const uint2* boxes,
-                            const uint32_t* offsets, float* g_pair, uint8_t* alive, bool want_max, hipStream_t s) {
+                            const uint32_t* offsets, float* g_pair, uint8_t* alive, uint32_t* g_max,
+                            hipStream_t s) {
   if (n_batches == 0) return hipSuccess;
   hipLaunchKernelGGL(k_blend_bwd, dim3(n_batches), dim3(256), 0, s, views_dev, n_views, records, n_rec, pair_vals,
                      sel, cap, ranges, ckpt, batch_tile, n_batches, order_cnt, order_list, dL_drgb, dL_dalpha,
-                     pair_emit, boxes, offsets, g_pair, alive, want_max ? 1 : 0);
+                     pair_emit, boxes, offsets, g_pair, alive, g_max);
   return hipGetLastError();
 }
 

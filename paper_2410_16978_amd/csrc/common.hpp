@@ -286,12 +286,13 @@ hipError_t launch_blend_bwd(const ViewD* views_dev, int n_views, const float* re
                             const uint32_t* order_cnt, const uint32_t* order_list,
                             const float* dL_drgb, const float* dL_dalpha, const uint32_t* pair_emit,
                             const uint2* boxes, const uint32_t* offsets, float* g_pair, uint8_t* alive,
-                            bool want_max, hipStream_t s);
+                            uint32_t* g_max, hipStream_t s);
 hipError_t launch_project_bwd(const JobD& job, const ViewD* views_dev, const float* records,
                               const uint32_t* offsets, const float* g_pair, const uint8_t* alive,
                               uint32_t pair_capacity,
                               const uint32_t* counters, uint32_t trainable, float* g_mean, float* g_scale,
-                              float* g_quat, float* g_opacity, float* g_sh, float* g_col, float* max_contrib,
+                              float* g_quat, float* g_opacity, float* g_sh, float* g_col, const uint32_t* g_max,
+                              float* max_contrib,
                               float* activity, float* dens_grad, float* dens_cnt, hipStream_t s);
 hipError_t launch_batch_error(const uint32_t* counters, int n_req, int32_t* req_status, hipStream_t s);
 hipError_t launch_batch_status(const uint32_t* req_rec, int n_req, const uint32_t* offsets,

@@ -15,14 +15,13 @@ namespace gsr {
 
 // Screen-space gradient of record r: the sum of its pairs' partials (stored
 // at their emission indices, so contiguous per record) in emission order,
-// accumulated in double, and the largest alpha * T it reached.  Only pairs
+// accumulated in double.  Only pairs
 // with alive[e] set have partials (the others are exactly zero and were never
 // written); their loads are redirected to the zero entry at index `zero`, so
 // the loads stay branch-free and adding its +0 leaves every sum bit for bit
 // unchanged (a sum that starts at +0 never holds -0).
 __device__ __forceinline__ void record_grad(uint32_t e0, uint32_t e1, const float* __restrict__ g_pair,
-                                            const uint8_t* __restrict__ alive, uint32_t zero, double* g,
-                                            float& wmax) {
+                                            const uint8_t* __restrict__ alive, uint32_t zero, double* g) {
   for (int c = 0; c < 9; ++c) g[c] = 0.0;
   if (e0 >= e1) return;
   // four pairs per step: their loads in flight at once, and with them the
@@ -37,13 +36,14 @@ __device__ __forceinline__ void record_grad(uint32_t e0, uint32_t e1, const floa
       const uint32_t q = e + (uint32_t)u;
       idx[u] = q < e1 && live[u] ? q : zero;
     }
-    float4 x[12];
+    float4 x[8];
+    float x8[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const float4* src = reinterpret_cast<const float4*>(g_pair + (size_t)idx[u] * 12);
-      x[3 * u] = src[0];
-      x[3 * u + 1] = src[1];
-      x[3 * u + 2] = src[2];
+      const float* src = g_pair + (size_t)idx[u] * 12;
+      x[2 * u] = reinterpret_cast<const float4*>(src)[0];
+      x[2 * u + 1] = reinterpret_cast<const float4*>(src)[1];
+      x8[u] = src[8];
     }
     uint8_t nf[4];
 #pragma unroll
@@ -55,11 +55,10 @@ __device__ __forceinline__ void record_grad(uint32_t e0, uint32_t e1, const floa
     for (int u = 0; u < 4; ++u) live[u] = nf[u] != 0;
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const float4 x0 = x[3 * u], x1 = x[3 * u + 1], x2 = x[3 * u + 2];
+      const float4 x0 = x[2 * u], x1 = x[2 * u + 1];
       g[0] += x0.x; g[1] += x0.y; g[2] += x0.z; g[3] += x0.w;
       g[4] += x1.x; g[5] += x1.y; g[6] += x1.z; g[7] += x1.w;
-      g[8] += x2.x;
-      wmax = fmaxf(wmax, x2.y);
+      g[8] += x8[u];
     }
   }
 }
@@ -78,7 +77,8 @@ k_project_bwd_geom(JobD job, const ViewD* __restrict__ views, const float* __res
                    const uint8_t* __restrict__ alive, uint32_t cap, const uint32_t* __restrict__ counters,
                    uint32_t trainable, float* __restrict__ g_mean, float* __restrict__ g_scale,
                    float* __restrict__ g_quat, float* __restrict__ g_opacity, float* __restrict__ g_col,
-                   float* __restrict__ max_contrib, float* __restrict__ dens_grad, float* __restrict__ dens_cnt) {
+                   const uint32_t* __restrict__ g_max, float* __restrict__ max_contrib,
+                   float* __restrict__ dens_grad, float* __restrict__ dens_cnt) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   const ModelD& m = job.m;
   if (i >= m.n) return;
@@ -86,20 +86,8 @@ k_project_bwd_geom(JobD job, const ViewD* __restrict__ views, const float* __res
   const uint32_t layer = m.layer[i];
   const bool train = layer < 32u && ((trainable >> layer) & 1u);
   const uint32_t K = min(counters[kCntPairs], cap);
-  float wmax = 0.f;
   double gm[3] = {0.0, 0.0, 0.0}, gs[3] = {0.0, 0.0, 0.0}, gq[4] = {0.0, 0.0, 0.0, 0.0}, go = 0.0;
   double dgs = 0.0, dgc = 0.0;
-  if (!train && max_contrib) {
-    double g[9];
-    for (int jv = 0; jv < job.n_views; ++jv) {
-      const uint32_t r = views[job.view[jv]].rec_off + (uint32_t)i;
-      const uint32_t kept = __float_as_uint(records[(size_t)r * kRecordFloats + 11]);
-      uint32_t e0 = offsets[r], e1 = offsets[r + 1];
-      asm volatile("" : "+v"(e0), "+v"(e1));  // both loads issued before the test, not sunk below it
-      e1 = min(e1, K);
-      if (kept != 0u) record_grad(e0, e1, g_pair, alive, cap, g, wmax);
-    }
-  }
   if (train) {
     const double mx = m.mean[i], my = m.mean[n + i], mz = m.mean[2 * n + i];
     const double s[3] = {act_scale(m.scale[i], m.raw), act_scale(m.scale[n + i], m.raw),
@@ -140,7 +128,7 @@ k_project_bwd_geom(JobD job, const ViewD* __restrict__ views, const float* __res
       e1 = min(e1, K);
       if (kept == 0u) continue;  // culled in this view
       double g[9];
-      record_grad(e0, e1, g_pair, alive, cap, g, wmax);
+      record_grad(e0, e1, g_pair, alive, cap, g);
       go += g[5] * (double)V.layer_op[layer];  // the record holds o times the view's factor
       {
         // density-control statistic: gradient of the projected centre in
@@ -295,7 +283,7 @@ k_project_bwd_geom(JobD job, const ViewD* __restrict__ views, const float* __res
 #pragma unroll
   for (int k = 0; k < 4; ++k) g_quat[(size_t)k * n + i] = (float)gq[k];
   g_opacity[i] = (float)go;
-  if (max_contrib) max_contrib[i] = fmaxf(max_contrib[i], wmax);
+  if (max_contrib) max_contrib[i] = fmaxf(max_contrib[i], __uint_as_float(g_max[i]));
   if (train && dens_grad) {
     dens_grad[i] += (float)dgs;
     dens_cnt[i] += (float)dgc;
@@ -396,12 +384,13 @@ hipError_t launch_project_bwd(const JobD& job, const ViewD* views_dev, const flo
                               const uint32_t* offsets, const float* g_pair, const uint8_t* alive,
                               uint32_t pair_capacity,
                               const uint32_t* counters, uint32_t trainable, float* g_mean, float* g_scale,
-                              float* g_quat, float* g_opacity, float* g_sh, float* g_col, float* max_contrib,
+                              float* g_quat, float* g_opacity, float* g_sh, float* g_col, const uint32_t* g_max,
+                              float* max_contrib,
                               float* activity, float* dens_grad, float* dens_cnt, hipStream_t s) {
   if (job.m.n <= 0) return hipSuccess;
   const dim3 grid(div_up((uint32_t)job.m.n, 256u)), block(256);
   hipLaunchKernelGGL(k_project_bwd_geom, grid, block, 0, s, job, views_dev, records, offsets, g_pair, alive,
-                     pair_capacity, counters, trainable, g_mean, g_scale, g_quat, g_opacity, g_col, max_contrib,
+                     pair_capacity, counters, trainable, g_mean, g_scale, g_quat, g_opacity, g_col, g_max, max_contrib,
                      dens_grad, dens_cnt);
   switch (job.m.D) {
     case 0: hipLaunchKernelGGL(k_project_bwd_sh<0>, grid, block, 0, s, job, views_dev, records, trainable, g_col,
