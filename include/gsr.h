@@ -195,11 +195,12 @@ typedef struct {
  *                             offsets[R] = pair count
  *   pair_vals   uint32[2][P]  sorted record ids; which half holds the result
  *                             is recorded on the device in *sort_sel.  A
- *                             forward with checkpoints leaves in the other
- *                             half, as uint16[P], each sorted pair's mask of
- *                             the 4 x 4-pixel blocks of its tile that its
- *                             ellipse reaches (bit 4 row + column), for the
- *                             backward
+ *                             forward leaves in the other half, as
+ *                             uint8[4][P], each sorted pair's mask of the
+ *                             4 x 4-pixel blocks of its tile that its ellipse
+ *                             reaches (plane: block row, bit: column), for
+ *                             the backward; a row of blocks has none behind
+ *                             the batch in which its last pixel stopped
  *   sort_sel    uint32[1]
  *   pair_emit   uint32[P]     emission index of each sorted pair; or, in
  *                             calls that order their records before pairing
@@ -219,12 +220,13 @@ typedef struct {
  *                             colour (r, g, b) behind the batch (the later
  *                             batches' colours plus the background times
  *                             the final transmittance); written for the
- *                             batches up to the one in which the tile's
- *                             last pixel stops (later ones are never read)
+ *                             batches up to the one in which the last pixel
+ *                             of its four image rows stops (later ones are
+ *                             never read); not written by a shared order
  *   batch_map   uint32[X + 1 + B]  X + 1 unused words, then for each
  *                             checkpoint batch index a word whose low 24
  *                             bits hold 1 + its tile (0: none) and whose top
- *                             byte holds the batch's work class (the
+ *                             byte holds the batch's weight (the
  *                             backward runs the heavier batches first);
  *                             tile t's batches have the indices
  *                             floor(ranges[t][0] / 256) + t + c

@@ -76,8 +76,6 @@ struct PipeBufs {
   float* records = nullptr;
   uint32_t* vals = nullptr;
   uint32_t* ranges = nullptr;
-  float* pix = nullptr;
-  uint32_t* last = nullptr;
   uint32_t* counters = nullptr;
   uint32_t* sel = nullptr;
   // order-first (order.hip): the record sort, the pairs, and the control
@@ -124,7 +122,7 @@ size_t order_ctl_words(const OrderPlan& op, size_t n_views) {
 }
 
 size_t carve(Carver& c, PipeBufs& b, size_t n_views, size_t R, size_t P, size_t n_req, bool batch,
-             size_t X, size_t Q, bool backward, const OrderPlan& op) {
+             size_t X, bool backward, const OrderPlan& op) {
   b.views = c.take<ViewD>(std::max<size_t>(n_views, 1));
   b.req_rec = c.take<uint32_t>(n_req + 1);
   b.n_tiles = c.take<uint32_t>(std::max<size_t>(R, 1));
@@ -160,8 +158,6 @@ size_t carve(Carver& c, PipeBufs& b, size_t n_views, size_t R, size_t P, size_t 
     b.records = c.take<float>(kRecordFloats * std::max<size_t>(R, 1));
     b.vals = c.take<uint32_t>(2 * std::max<size_t>(P, 1));
     b.ranges = c.take<uint32_t>(2 * std::max<size_t>(X, 1));
-    b.pix = c.take<float>(4 * std::max<size_t>(Q, 1));
-    b.last = c.take<uint32_t>(std::max<size_t>(Q, 1));
     b.counters = c.take<uint32_t>(4);
     b.sel = c.take<uint32_t>(1);
   }
@@ -529,11 +525,11 @@ size_t gsr_workspace_size(int32_t n, int32_t n_views, int32_t width, int32_t hei
   Carver c(nullptr);
   PipeBufs b;
   const size_t X = (size_t)n_views * (size_t)((width + kTile - 1) / kTile) * (size_t)((height + kTile - 1) / kTile);
-  const size_t own = carve(c, b, (size_t)n_views, (size_t)n * n_views, pair_capacity, 0, false, X, 0, true,
+  const size_t own = carve(c, b, (size_t)n_views, (size_t)n * n_views, pair_capacity, 0, false, X, true,
                            single_plan(n, n_views, X, pair_capacity, false));
   if (!shared_order) return own;
   Carver cs(nullptr);
-  return std::max(own, carve(cs, b, (size_t)n_views, (size_t)n * n_views, pair_capacity, 0, false, X, 0, true,
+  return std::max(own, carve(cs, b, (size_t)n_views, (size_t)n * n_views, pair_capacity, 0, false, X, true,
                              single_plan(n, n_views, X, pair_capacity, true)));
 }
 
@@ -604,7 +600,7 @@ gsr_status forward_impl(const gsr_model* model, int32_t n_views, const gsr_camer
   OrderPlan op = single_plan(n, n_views, X, P, shared);
   Carver c(ws);
   PipeBufs b;
-  if (carve(c, b, n_views, R, P, 0, false, X, 0, backward_layout, op) > ws_bytes) return GSR_ENOSPACE;
+  if (carve(c, b, n_views, R, P, 0, false, X, backward_layout, op) > ws_bytes) return GSR_ENOSPACE;
 
   std::vector<ViewD> hv(n_views);
   std::vector<int> ids(n_views);
@@ -718,9 +714,9 @@ gsr_status forward_impl(const gsr_model* model, int32_t n_views, const gsr_camer
   uint32_t* batch_tile = state->batch_map + X + 1;
   {
     StageScope sc(timer, GSR_STAGE_BLEND, s);
-    HIP_TRY(launch_blend_fwd_tile(b.views, n_views, (uint32_t)X, state->records, R, state->pair_vals,
+    HIP_TRY(launch_blend_fwd(b.views, n_views, (uint32_t)X, state->records, R, state->pair_vals,
                                   state->sort_sel, P, state->ranges, batch_tile, state->batch_capacity,
-                                  nullptr, reinterpret_cast<float4*>(state->checkpoints), b.ctl->tile_class,
+                                  nullptr, shared ? nullptr : reinterpret_cast<float4*>(state->checkpoints), b.ctl->tile_class,
                                   b.class_list, s));
   }
   if (debug) {
@@ -794,8 +790,8 @@ gsr_status gsr_rasterize_forward_noalloc(const gsr_model* model, int32_t n_views
   Carver per_tile(nullptr), own(nullptr);
   PipeBufs b;
   const size_t need =
-      std::max(carve(per_tile, b, (size_t)n_views, R, P, 0, false, X, 0, false, OrderPlan{}) + (shared ? 24 * (n + R) : 0),
-               carve(own, b, (size_t)n_views, R, P, 0, false, X, 0, false, single_plan(model->n, n_views, X, P, shared)));
+      std::max(carve(per_tile, b, (size_t)n_views, R, P, 0, false, X, false, OrderPlan{}) + (shared ? 24 * (n + R) : 0),
+               carve(own, b, (size_t)n_views, R, P, 0, false, X, false, single_plan(model->n, n_views, X, P, shared)));
   if (need > kNoallocScratchBytes) return GSR_ENOSPACE;
   void* ws = nullptr;
   const gsr_status st = scratch_of_current_device(&ws);
@@ -842,7 +838,7 @@ gsr_status gsr_rasterize_backward(const gsr_model* model, int32_t n_views, const
   Carver c(ws);
   PipeBufs b;
   const OrderPlan op = single_plan(n, n_views, X, P, false);
-  if (carve(c, b, n_views, R, P, 0, false, X, 0, true, op) > ws_bytes)
+  if (carve(c, b, n_views, R, P, 0, false, X, true, op) > ws_bytes)
     return GSR_ENOSPACE;
   std::vector<ViewD> hv(n_views);
   std::vector<int> ids(n_views);
@@ -906,7 +902,7 @@ namespace {
 struct BatchPlan {
   std::vector<ViewD> views;
   std::vector<uint32_t> req_rec;
-  uint64_t R = 0, X = 0, Q = 0;
+  uint64_t R = 0, X = 0;
   // with any request sharing one depth order between its eyes, or where
   // order_first says so, the records are ordered before they are paired
   OrderPlan order;
@@ -934,7 +930,6 @@ bool plan_batch(const gsr_model* models, int32_t n_models, const gsr_request* re
       bp.views.push_back(d);
       bp.R += (uint64_t)models[r.model].n;
       bp.X += tiles_of(r.cam[e]);
-      bp.Q += (uint64_t)r.cam[e].width * r.cam[e].height;
     }
   }
   bp.req_rec[n_req] = (uint32_t)bp.R;
@@ -979,7 +974,7 @@ size_t gsr_batch_workspace_size(const gsr_model* models, int32_t n_models, const
   if (!plan_batch(models, n_models, reqs, n_req, pair_capacity, bp) || pair_capacity >= (1u << 30)) return 0;
   Carver c(nullptr);
   PipeBufs b;
-  return carve(c, b, bp.views.size(), bp.R, pair_capacity, n_req, true, bp.X, bp.Q, false, bp.order);
+  return carve(c, b, bp.views.size(), bp.R, pair_capacity, n_req, true, bp.X, false, bp.order);
 }
 
 gsr_status gsr_render_batch(const gsr_model* models, int32_t n_models, const gsr_request* reqs, int32_t n_req,
@@ -994,14 +989,7 @@ gsr_status gsr_render_batch(const gsr_model* models, int32_t n_models, const gsr
   const int n_views = (int)bp.views.size();
   Carver c(ws);
   PipeBufs b;
-  if (carve(c, b, n_views, R, P, n_req, true, bp.X, bp.Q, false, bp.order) > ws_bytes) return GSR_ENOSPACE;
-  // per-view transmittance / last index scratch
-  size_t q_off = 0;
-  for (ViewD& d : bp.views) {
-    d.pix = b.pix + 4 * q_off;
-    d.last = b.last + q_off;
-    q_off += (size_t)d.W * d.H;
-  }
+  if (carve(c, b, n_views, R, P, n_req, true, bp.X, false, bp.order) > ws_bytes) return GSR_ENOSPACE;
   WordUpload up;
   HIP_TRY(upload_views(b.views, bp.views.data(), n_views, up, s));
   HIP_TRY(launch_upload(b.req_rec, bp.req_rec.data(), (size_t)n_req + 1, s));
@@ -1069,7 +1057,7 @@ gsr_status gsr_render_batch(const gsr_model* models, int32_t n_models, const gsr
   }
   {
     StageScope sc(timer, GSR_STAGE_BLEND, s);
-    HIP_TRY(launch_blend_fwd_tile(b.views, n_views, (uint32_t)bp.X, b.records, R, b.vals, b.sel, P, b.ranges,
+    HIP_TRY(launch_blend_fwd(b.views, n_views, (uint32_t)bp.X, b.records, R, b.vals, b.sel, P, b.ranges,
                                   nullptr, 0, req_status, nullptr, b.ctl->tile_class, b.class_list, s));
   }
   HIP_TRY(launch_batch_error(b.counters, n_req, req_status, s));

@@ -26,13 +26,15 @@
 // values a lane carries), the ninth and the max with DPP - the four wave sums
 // in a fixed order through LDS, and written as the pair's partial gradient:
 // no atomics, bitwise reproducible.
+#include <algorithm>
+
 #include "common.hpp"
 #include "cull.hpp"
 
 namespace gsr {
 
 // G = exp(-q / 2) = 2^(kPowScale q): the kernels evaluate q from the record's
-// conic (b staged doubled, which is exact) and scale it once.  Staging the
+// conic and scale it once.  Staging the
 // conic pre-multiplied by kPowScale would save that multiply but round each
 // coefficient once per splat: the same relative error at every pixel of the
 // splat, which the gradient sums over its pixels would then add up
@@ -41,7 +43,7 @@ namespace gsr {
 constexpr float kPowScale = -0.72134752044448170368f;
 
 struct BatchLds {
-  float4 a[kBatch];    // u, v, conic a, 2 b
+  float4 a[kBatch];    // u, v, conic a, b
   float4 b[kBatch];    // conic c, opacity, r, g
   float c[kBatch];     // b
 };
@@ -94,7 +96,7 @@ __device__ __forceinline__ float reach_cutoff(float opacity) {
 
 __device__ __forceinline__ void put(BatchLds& L, const Staged& st, bool ok, int tid) {
   if (ok) {
-    L.a[tid] = make_float4(st.a.x, st.a.y, st.a.z, 2.f * st.a.w);
+    L.a[tid] = st.a;
     L.b[tid] = st.b;
     L.c[tid] = st.c;
   }
@@ -163,36 +165,18 @@ __device__ __forceinline__ uint64_t lanes_below() {
   return lane == 0 ? 0ull : (~0ull >> (64 - lane));
 }
 
-// Block memberships of a batch: thread t of a 1024-thread block takes pair
-// t mod 256 and the tile's block row t / 256 and writes the 4 bits of the
-// row's 4 x 4 blocks the pair's ellipse reaches (band_blocks) to
-// nib[row][pair].  A tile is 4 x 4 such blocks; bit 4 row + column of a
-// pair's 16-bit block mask is block (column, row).
-static_assert(kBatch * 4 == 1024, "one block row per thread");
-
-__device__ __forceinline__ void block_nibbles(const BatchRaw& L, uint8_t (*nib)[kBatch], int n, float tx0,
-                                              float ty0) {
-  const int j = threadIdx.x & (kBatch - 1), r = threadIdx.x >> 8;
-  uint32_t bits = 0u;
-  if (j < n) {
-    const float4 A = L.a[j], B = L.b[j];
-    bits = band_blocks(A.x, A.y, A.z, A.w, B.x, reach_cutoff(B.y), tx0, ty0 + 4.f * (float)r);
-  }
-  nib[r][j] = (uint8_t)bits;
-}
-
 // The wave's list of the batch's pairs (ascending, j < n) whose ellipse
-// reaches its block (bit `col` of the block row's nibbles); each lane tests
+// reaches its block (bit `col` of the band's nibbles); each lane tests
 // one pair per round, a ballot compacts the hits.  Returns the
 // (wave-uniform) count.  Pairs not in the list cannot reach alpha >= 1/255 on
 // any of the wave's pixels, so skipping them changes nothing.
-__device__ __forceinline__ int wave_list(const uint8_t* nib_row, int col, uint8_t* list, int n) {
+__device__ __forceinline__ int wave_list(const uint8_t* nib, int col, uint8_t* list, int n) {
   const int lane = threadIdx.x & 63;
   int cnt = 0;
 #pragma unroll
   for (int r = 0; r < kBatch / 64; ++r) {
     const int j = r * 64 + lane;
-    const bool hit = j < n && ((nib_row[j] >> col) & 1u);
+    const bool hit = j < n && ((nib[j] >> col) & 1u);
     const uint64_t m = __ballot(hit);
     if (hit) list[cnt + __popcll(m & lanes_below())] = (uint8_t)j;
     cnt += __popcll(m);
@@ -202,9 +186,10 @@ __device__ __forceinline__ int wave_list(const uint8_t* nib_row, int col, uint8_
 }
 
 // Base-2 exponent kPowScale q of one pair at a pixel offset (dx, dy) =
-// centre - pixel, q = a dx^2 + 2 b dx dy + c dy^2 from the staged conic;
+// centre - pixel, q = a dx^2 + 2 b dx dy + c dy^2 from the record's conic;
 // G = 2^power.  q is rounded exactly as its plain left-to-right evaluation
-// is - (a dx) dx + (c dy) dy first, then + (2b dx) dy, no fused operations -
+// is - (a dx) dx + (c dy) dy first, then + (2b dx) dy - (doubling is exact, so
+// it may come last and share the addition's rounding),
 // which is also the reference's order: for a thin splat q is a small
 // difference of terms thousands of times larger, and any other order rounds
 // it differently by enough to move alpha across the 1/255 cut-off.  This file
@@ -213,7 +198,7 @@ __device__ __forceinline__ int wave_list(const uint8_t* nib_row, int col, uint8_
 // the same skip decisions.  power <= 0 is q >= 0.
 __device__ __forceinline__ float pair_power(const float4 A, const float4 B, float dx, float dy) {
   const float qa = (A.z * dx) * dx, qc = (B.x * dy) * dy, qb = (A.w * dx) * dy;
-  return kPowScale * ((qa + qc) + qb);
+  return kPowScale * fmaf(2.f, qb, qa + qc);
 }
 
 __device__ __forceinline__ float pair_gauss(float power) { return __builtin_amdgcn_exp2f(power); }
@@ -226,24 +211,30 @@ __device__ __forceinline__ float pair_alpha(const float4 B, float power) {
 __device__ __forceinline__ uint64_t ballot(bool x) { return __builtin_amdgcn_ballot_w64(x); }
 
 // ---------------------------------------------------------------- forward
-// One 1024-thread block per tile walks the tile's batches in order.  Each of
-// its 16 waves owns a 4 x 4 pixel sub-tile and gives every pixel a quad of
+// One 256-thread block per band of a tile (four rows of 4 x 4-pixel blocks
+// make the tile) walks the tile's batches in order.  Each of its four waves
+// owns one 4 x 4 block and gives every pixel a quad of
 // four lanes: a step takes the next four pairs of the wave's list, one per
 // lane of each quad, and advances the pixel's transmittance by the quad's
 // prefix product of (1 - alpha) - four pairs per step of the serial chain
 // instead of one.  The first pair (in list order) that would bring T below
 // 1e-4 ends the pixel and is not blended, as are the pairs after it.  Per
 // batch the records are staged once, a wave with a live pixel builds its list
-// (pairs whose ellipse meets the sub-tile), and the block leaves when every
-// pixel has stopped.  Per batch it stores the checkpoint (T entering the
-// batch, then colour behind the batch) the backward starts from, at the
-// pixel's index in the backward's 8 x 8-quadrant layout (ckpt may be null: render
-// only, then batch_tile is not written).  Tile t's batches have the indices
-// first_batch(t) + c, c = 0, 1, ...: distinct over the tiles and below
-// P / 256 + X + 1 for any pair count P.  Each batch's word in batch_tile holds
-// 1 + tile and, in the top byte, a work class for the backward's order: from
-// the longest list any wave stepped through in the batch (16 classes of 16
-// entries, heaviest first), the last class for batches never reached.
+// (pairs whose ellipse meets the block), and the block leaves when every
+// pixel of the band has stopped.  Per batch it stores the checkpoint (T
+// entering the batch, then colour behind the batch) the backward starts from,
+// at the pixel's index in the backward's 8 x 8-quadrant layout (ckpt may be
+// null: render only, then batch_tile is not written).  Tile t's batches have
+// the indices first_batch(t) + c, c = 0, 1, ...: distinct over the tiles and
+// below P / 256 + X + 1 for any pair count P.
+//
+// The kernel is bound by VALU issue (65 - 75 % of the cycles in flight).
+// Four blocks a tile instead of one of 1024 threads: a barrier waits for 4
+// waves instead of 16, a band leaves as soon as its own 64 pixels have
+// stopped, and on a view with few deep tiles four compute units share one;
+// the records are staged four times, from L2.  The inner step keeps its lane
+// masks in scalar registers and takes the products for a stopping pixel only
+// in steps where one stops.  Tiles without pairs only write the background.
 constexpr int kQuadPix = 4;  // sub-tile edge
 
 // Checkpoint batch index of a tile's first batch: floor(start / 256) + t.
@@ -253,9 +244,12 @@ __device__ __forceinline__ uint32_t first_batch(uint32_t tile, uint32_t tile_sta
   return tile_start / (uint32_t)kBatch + tile;
 }
 
+// A batch's word: 1 + tile and, in the top byte, its weight in the backward's
+// order from the longest list a wave stepped through (1 .. 16 in steps of 16
+// entries, 0: never evaluated).  The bands of a tile take the largest.
 __device__ __forceinline__ uint32_t batch_word(uint32_t tile, uint32_t est) {
-  const uint32_t cls = est == 0 ? kBatchClasses - 1 : (kBatch - min(est, (uint32_t)kBatch)) >> 4;
-  return (tile + 1u) | (cls << 24);
+  const uint32_t weight = est == 0 ? 0u : 16u - ((kBatch - min(est, (uint32_t)kBatch)) >> 4);
+  return (tile + 1u) | (weight << 24);
 }
 
 // Full-mask lane permutation: every lane has a source, so no old value.
@@ -264,225 +258,297 @@ __device__ __forceinline__ float qperm(float v) {
   return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, true));
 }
 
-__device__ __forceinline__ float quad_shift1(float x, int slot) {  // x of slot - 1, 1 for slot 0
-  const float y = qperm<0x90>(x);                                // quad_perm [0,0,1,2]
-  return slot >= 1 ? y : 1.f;
-}
-
-__device__ __forceinline__ float quad_shift2(float x, int slot) {  // x of slot - 2, 1 for slots 0, 1
-  const float y = qperm<0x40>(x);                                // quad_perm [0,0,0,1]
-  return slot >= 2 ? y : 1.f;
-}
-
 __device__ __forceinline__ float quad_sum(float v) {
   v += dpp<0xB1, 0xF>(v);  // quad_perm [1,0,3,2]
   v += dpp<0x4E, 0xF>(v);  // quad_perm [2,3,0,1]
   return v;
 }
 
-__device__ __forceinline__ uint32_t quad_max_u32(uint32_t v) {
-  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, false));
-  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, false));
+__device__ __forceinline__ int quad_max(int v) {
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, false));
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, false));
   return v;
 }
 
-// At most 80 SGPRs: two 1024-thread blocks per compute unit need it (with
-// 81 the kernel measured 35 % slower, one block per compute unit at a time).
-__global__ void __launch_bounds__(1024) __attribute__((amdgpu_num_sgpr(80)))
-k_blend_tile(const ViewD* __restrict__ views, int n_views, uint32_t total_tiles, const float* __restrict__ records,
-             uint32_t n_rec, const uint32_t* __restrict__ pair_vals, const uint32_t* __restrict__ sel, uint32_t cap,
-             const uint32_t* __restrict__ ranges, uint32_t* __restrict__ batch_tile, uint32_t batch_cap,
-             const int32_t* __restrict__ req_status, float4* __restrict__ ckpt,
-             const uint32_t* __restrict__ class_count, const uint32_t* __restrict__ class_list) {
-  __shared__ BatchRaw R[2];  // batch c's records in R[c & 1]
-  __shared__ uint8_t lists[16][kBatch];
-  __shared__ uint8_t nib[4][kBatch];
-  // block b takes the b-th tile of the largest-first order (if given): the
-  // class counts are read at once, the first wave finds b's class by a scan
-  __shared__ uint32_t s_tile;
-  uint32_t tile = blockIdx.x;
-  if (class_count) {
-    if (threadIdx.x < 64) {
-      const uint32_t k = threadIdx.x;
-      const uint32_t cnt = k < kTileClasses ? min(class_count[k], total_tiles) : 0u;
-      const uint32_t inc = wave_scan_add(cnt);
-      const uint32_t b = blockIdx.x;
-      const bool here = k < kTileClasses && b >= inc - cnt && b < inc;
-      if (here) s_tile = class_list[(size_t)k * total_tiles + (b - (inc - cnt))];
-      if (__ballot(here) == 0ull && threadIdx.x == 0) s_tile = 0xFFFFFFFFu;
-    }
-    __syncthreads();
-    tile = s_tile;
-  }
-  if (tile >= total_tiles) return;
-  const int vi = find_view(views, n_views, tile);
-  const ViewD& V = views[vi];
-  if (req_status && req_status[V.request] != 0) return;  // a request that did not fit is not written
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int slot = lane & 3, p = lane >> 2;
-  const uint32_t upto_slot = (2u << slot) - 1u;  // stop bits of the slots up to this one
-  const uint32_t local = tile - V.tile_off;
-  const int tx = (int)(local % (uint32_t)V.tiles_x), ty = (int)(local / (uint32_t)V.tiles_x);
-  const int lx = (wave & 3) * kQuadPix + (p & 3), ly = (wave >> 2) * kQuadPix + (p >> 2);  // in the tile
-  const int px = tx * kTile + lx, py = ty * kTile + ly;
-  const int bidx = ((ly >> 3) * 2 + (lx >> 3)) * 64 + (ly & 7) * 8 + (lx & 7);  // backward's thread of this pixel
-  const bool inside = px < V.W && py < V.H;
-  const float fx = (float)px + 0.5f, fy = (float)py + 0.5f;
-  const uint32_t* vals = pair_vals + (*sel ? cap : 0u);
-  // a training forward leaves each sorted pair's block mask for the backward
-  // in the other half of pair_vals (free once the sort is done)
-  uint16_t* blk_out = ckpt ? reinterpret_cast<uint16_t*>(const_cast<uint32_t*>(pair_vals) + (*sel ? 0u : cap))
-                           : nullptr;
-  const uint32_t t_end = min(ranges[2 * tile + 1], cap);
-  const uint32_t t_start = min(ranges[2 * tile], t_end);
-  const uint32_t b0 = first_batch(tile, t_start);
-  __shared__ uint32_t s_est;  // longest list stepped through in the current batch
-  if (tid == 0) s_est = 0;
-  uint8_t* list = lists[wave];
-  float T = 1.f, C0 = 0.f, C1 = 0.f, C2 = 0.f;
-  uint32_t last = 0;
-  bool done = !inside;
-  uint32_t n_ck = 0;  // batches processed (checkpoints written)
-  // per batch parity, byte w: whether wave w still has a live pixel
-  __shared__ __align__(16) uint32_t s_live[2][4];
-  // Staging: waves 0-3 load the records of batch c + 1 straight into LDS
-  // while batch c is blended, and the record ids of batch c + 2 into
-  // registers; batch 0's loads start here.
-  const bool stager = tid < kBatch;
-  uint32_t rid = stager && t_start + (uint32_t)tid < t_end ? vals[t_start + tid] : 0u;
-  if (stager && t_start < t_end) stage_async(R[0], records, n_rec, rid, t_start + (uint32_t)tid < t_end);
-  {
-    const uint32_t k = t_start + kBatch + (uint32_t)tid;
-    rid = stager && k < t_end ? vals[k] : 0u;
-  }
-  for (uint32_t start = t_start, c = 0; start < t_end; start += kBatch, ++c) {
-    // this batch's records have landed (each wave waits for its own loads);
-    // the block leaves once every pixel has stopped: each wave posts its
-    // flag, one barrier (which also shows the records to every wave and
-    // orders the previous batch's reads of the other buffer before its
-    // refill), every wave reads the sixteen posts (the other parity's posts
-    // are rewritten only after the next batch's barriers)
-    __builtin_amdgcn_s_waitcnt(kWaitVm0);
-    {
-      const bool any_live = __ballot(!done) != 0ull;
-      if (lane == 0) reinterpret_cast<uint8_t*>(s_live[c & 1])[wave] = any_live ? 1 : 0;
-      __syncthreads();
-      const uint4 posts = *reinterpret_cast<const uint4*>(s_live[c & 1]);
-      if ((posts.x | posts.y | posts.z | posts.w) == 0u) break;
-    }
-    if (ckpt && tid == 0 && c > 0) {
-      if (b0 + c - 1 < batch_cap) batch_tile[b0 + c - 1] = batch_word(tile, s_est);
-      s_est = 0;
-    }
-    const int n = (int)min((uint32_t)kBatch, t_end - start);
-    const BatchRaw& L = R[c & 1];
-    {
-      const uint32_t nstart = start + kBatch;
-      if (stager && nstart < t_end) stage_async(R[(c + 1) & 1], records, n_rec, rid, nstart + (uint32_t)tid < t_end);
-      const uint32_t k = nstart + kBatch + (uint32_t)tid;
-      rid = stager && k < t_end ? vals[k] : 0u;
-    }
-    block_nibbles(L, nib, n, (float)(tx * kTile) + 0.5f, (float)(ty * kTile) + 0.5f);
-    lds_barrier();
-    if (blk_out && tid < n)
-      blk_out[start + tid] = (uint16_t)(nib[0][tid] | (nib[1][tid] << 4) | (nib[2][tid] << 8) | (nib[3][tid] << 12));
-    const float T0 = T;
-    float D0 = 0.f, D1 = 0.f, D2 = 0.f;
-    uint32_t lst = 0;
-    const int cnt = __ballot(!done) ? wave_list(nib[wave >> 2], wave & 3, list, n) : 0;
-    int stepped = cnt;
-    for (int t0 = 0; t0 < cnt; t0 += 4) {
-      const int te = t0 + slot;
-      const bool has = te < cnt;
-      const int j = has ? (int)list[te] : 0;
-      const float4 R4 = L.a[j], B = L.b[j];
-      const float cb = L.c[j];
-      const float4 A = make_float4(R4.x, R4.y, R4.z, 2.f * R4.w);  // b doubled (exact)
-      const float power = pair_power(A, B, A.x - fx, A.y - fy);
-      const float alpha = pair_alpha(B, power);
-      const bool cand = has && !done && power <= 0.f && alpha >= kAlphaMin;
-      const float f = cand ? 1.f - alpha : 1.f;
-      float P = f * quad_shift1(f, slot);
-      P = P * quad_shift2(P, slot);        // prod of f over slots <= slot
-      const float E = quad_shift1(P, slot);  // over slots < slot
-      const float Tn = T * P;
-      const bool stop = cand && Tn < kTStop;
-      // the quad's stop bits: a slot blends if no slot up to it stops
-      const uint32_t sbits = (uint32_t)(ballot(stop) >> (lane & 60));
-      const bool blend = cand && (sbits & upto_slot) == 0u;
-      const float w = blend ? alpha * (T * E) : 0.f;
-      D0 = fmaf(B.z, w, D0);
-      D1 = fmaf(B.w, w, D1);
-      D2 = fmaf(cb, w, D2);
-      lst = blend ? start + (uint32_t)j + 1 : lst;
-      // T after the quad's last blended slot: T times the quad's product of
-      // (1 - alpha) over its blended slots (1 elsewhere; a quad that blends
-      // nothing multiplies T by exactly 1)
-      float g = blend ? f : 1.f;
-      g *= dpp<0xB1, 0xF>(g);  // quad_perm [1,0,3,2]
-      g *= dpp<0x4E, 0xF>(g);  // quad_perm [2,3,0,1]
-      T *= g;
-      done = done || (sbits & 0xFu) != 0u;
-      if (ballot(!done) == 0ull) {
-        stepped = min(cnt, t0 + 4);
-        break;
-      }
-    }
-    if (ckpt && lane == 0 && stepped > 0) atomicMax(&s_est, (uint32_t)stepped);
-    D0 = quad_sum(D0);
-    D1 = quad_sum(D1);
-    D2 = quad_sum(D2);
-    lst = quad_max_u32(lst);
-    C0 += D0;
-    C1 += D1;
-    C2 += D2;
-    last = lst ? lst : last;
-    if (ckpt && slot == 0 && b0 + c < batch_cap) ckpt[(size_t)(b0 + c) * kBatch + bidx] = make_float4(T0, D0, D1, D2);
-    n_ck = c + 1;
-  }
-  if (ckpt) {
-    // the last batch reached, then the ones never reached
-    __syncthreads();
-    if (tid == 0 && n_ck > 0 && b0 + n_ck - 1 < batch_cap) batch_tile[b0 + n_ck - 1] = batch_word(tile, s_est);
-    const uint32_t nb = (t_end - t_start + (uint32_t)kBatch - 1) / (uint32_t)kBatch;
-    for (uint32_t c = n_ck + tid; c < nb; c += 1024)
-      if (b0 + c < batch_cap) batch_tile[b0 + c] = batch_word(tile, 0);
-  }
-  if (ckpt && slot == 0) {
-    // replace each batch's colour by the colour behind the batch: the
-    // background under the final transmittance plus the later batches,
-    // summed from the back (a batch after the pixel stopped adds 0)
-    float a0 = T * V.bg[0], a1 = T * V.bg[1], a2 = T * V.bg[2];
-    for (int cc = (int)n_ck - 1; cc >= 0; --cc) {
-      if (b0 + (uint32_t)cc >= batch_cap) continue;
-      float4* q = ckpt + (size_t)(b0 + (uint32_t)cc) * kBatch + bidx;
-      const float4 d = *q;
-      *q = make_float4(d.x, a0, a1, a2);
-      a0 += d.y;
-      a1 += d.z;
-      a2 += d.w;
-    }
-  }
-  if (!inside || slot != 0) return;
-  const size_t pix = (size_t)py * V.W + px;
-  const size_t plane = (size_t)V.W * V.H;
-  V.rgb[pix] = fmaf(T, V.bg[0], C0);
-  V.rgb[plane + pix] = fmaf(T, V.bg[1], C1);
-  V.rgb[2 * plane + pix] = fmaf(T, V.bg[2], C2);
-  V.alpha[pix] = 1.f - T;
-  reinterpret_cast<float4*>(V.pix)[pix] = make_float4(T, C0, C1, C2);
-  V.last[pix] = last;
+// The tiles in order of size: class k's tiles are ranks
+// [inc - cnt, inc) of lane k, class_list[k] lists them.
+__device__ __forceinline__ uint32_t tile_of_rank(uint32_t rank, uint32_t cnt, uint32_t inc, uint32_t total_tiles,
+                                                 const uint32_t* __restrict__ class_list) {
+  const uint64_t m = __ballot(rank >= inc - cnt && rank < inc);
+  if (m == 0ull) return total_tiles;
+  const int k = __builtin_ctzll(m);
+  const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)(inc - cnt), k);
+  return class_list[(size_t)k * total_tiles + (rank - first)];
 }
 
-hipError_t launch_blend_fwd_tile(const ViewD* views_dev, int n_views, uint32_t total_tiles, const float* records,
-                                 uint32_t n_rec, const uint32_t* pair_vals, const uint32_t* sel, uint32_t cap,
-                                 const uint32_t* ranges, uint32_t* batch_tile, uint32_t batch_cap,
-                                 const int32_t* req_status, float4* ckpt, const uint32_t* class_count,
-                                 const uint32_t* class_list, hipStream_t s) {
+// One pixel's results; slot s of the pixel's quad stores plane s of the image.
+__device__ __forceinline__ void store_pixel(const ViewD& V, int px, int py, int slot, float T, float C0, float C1,
+                                            float C2, uint32_t last) {
+  const size_t pix = (size_t)py * V.W + px, plane = (size_t)V.W * V.H;
+  const float bg = slot == 0 ? V.bg[0] : slot == 1 ? V.bg[1] : V.bg[2];
+  const float C = slot == 0 ? C0 : slot == 1 ? C1 : C2;
+  if (slot < 3) V.rgb[(size_t)slot * plane + pix] = fmaf(T, bg, C);
+  else V.alpha[pix] = 1.f - T;
+  if (V.pix && slot == 0) {
+    reinterpret_cast<float4*>(V.pix)[pix] = make_float4(T, C0, C1, C2);
+    V.last[pix] = last;
+  }
+}
+
+// The arguments an item needs once are read from the argument segment there
+// (fwd_args() hides that it gives the same pointer each time): held in scalar
+// registers across the walk they crowd out the walk's own, which then spill.
+struct FwdArgs {
+  const ViewD* views;
+  const float* records;
+  const uint32_t* pair_vals;
+  const uint32_t* sel;
+  const uint32_t* ranges;
+  uint32_t* batch_tile;
+  const int32_t* req_status;
+  float4* ckpt;
+  const uint32_t* class_count;
+  const uint32_t* class_list;
+  int32_t n_views;
+  uint32_t total_tiles, n_rec, cap, batch_cap;
+};
+typedef const FwdArgs __attribute__((address_space(4))) FwdArgsC;
+
+__device__ __forceinline__ FwdArgsC* fwd_args() {
+  FwdArgsC* a = (FwdArgsC*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(a));
+  return a;
+}
+
+__global__ void __launch_bounds__(256, 8) k_blend_fwd(FwdArgs args) {
+  __shared__ BatchRaw R[2];  // batch c's records in R[c & 1]
+  __shared__ uint8_t lists[4][kBatch];
+  __shared__ uint8_t nib[kBatch];
+  __shared__ uint32_t s_live[2];  // per batch parity, byte w: whether wave w still has a live pixel
+  __shared__ uint32_t s_est;      // longest list stepped through in the current batch
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int slot = lane & 3, p = lane >> 2;
+  const uint32_t cnt_k = (uint32_t)lane < kTileClasses ? min(fwd_args()->class_count[lane], fwd_args()->total_tiles) : 0u;
+  const uint32_t inc_k = wave_scan_add(cnt_k);
+  const uint32_t n_all = (uint32_t)__builtin_amdgcn_readlane((int)inc_k, (int)kTileClasses - 1);
+  const uint32_t n_full = (uint32_t)__builtin_amdgcn_readlane((int)inc_k, (int)kTileClasses - 2);  // tiles with pairs
+  const uint32_t full_items = div_up(n_full, kXcds) * kXcds * 4u, items = full_items + div_up(n_all - n_full, 4u);
+  const uint32_t total_tiles = args.total_tiles;
+  const uint32_t off_v = lane < args.n_views ? args.views[lane].tile_off : 0xFFFFFFFFu;
+  auto view_of = [&](uint32_t tile) -> int {
+    const int n_views = fwd_args()->n_views;
+    return n_views <= 64 ? (int)__builtin_popcountll(__ballot(off_v <= tile)) - 1
+                         : find_view(fwd_args()->views, n_views, tile);
+  };
+  // the four bands of a tile are 8 items apart: on one XCD, whose L2 then
+  // holds the tile's records for all of them
+  auto rank_of = [](uint32_t item) -> uint32_t { return item / (4u * kXcds) * kXcds + item % kXcds; };
+  // a tile's index is loaded an item ahead
+  uint32_t next = blockIdx.x < full_items
+                      ? tile_of_rank(rank_of(blockIdx.x), cnt_k, inc_k, total_tiles, fwd_args()->class_list)
+                      : 0u;
+
+  for (uint32_t item = blockIdx.x; item < items; item += gridDim.x) {
+    FwdArgsC* A0 = fwd_args();
+    if (item >= full_items) {
+      // four tiles without pairs, one per wave: the background
+      const uint32_t rank = n_full + (item - full_items) * 4u + (uint32_t)wave;
+      const uint32_t tile = rank < n_all ? tile_of_rank(rank, cnt_k, inc_k, total_tiles, A0->class_list) : total_tiles;
+      if (tile >= total_tiles) continue;
+      const ViewD& V = A0->views[view_of(tile)];
+      if (A0->req_status && A0->req_status[V.request] != 0) continue;
+      const uint32_t local = tile - V.tile_off;
+      const int px = (int)(local % (uint32_t)V.tiles_x) * kTile + (lane & 15);
+      const int py = (int)(local / (uint32_t)V.tiles_x) * kTile + (lane >> 4);
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (px < V.W && py + 4 * q < V.H)
+#pragma unroll
+          for (int s = 3; s >= 0; --s) store_pixel(V, px, py + 4 * q, s, 1.f, 0.f, 0.f, 0.f, 0u);
+      continue;
+    }
+    const int band = (int)(item / kXcds) & 3;
+    const uint32_t tile = next;
+    const uint32_t rank = rank_of(item), item1 = item + gridDim.x;
+    if (item1 < full_items) next = tile_of_rank(rank_of(item1), cnt_k, inc_k, total_tiles, A0->class_list);
+    if (rank >= n_full || tile >= total_tiles) continue;
+    const ViewD& V = A0->views[view_of(tile)];
+    if (A0->req_status && A0->req_status[V.request] != 0) continue;  // a request that did not fit is not written
+    const uint32_t local = tile - V.tile_off;
+    const int tx = (int)(local % (uint32_t)V.tiles_x), ty = (int)(local / (uint32_t)V.tiles_x);
+    const int lx = wave * kQuadPix + (p & 3), ly = band * kQuadPix + (p >> 2);  // in the tile
+    const int px = tx * kTile + lx, py = ty * kTile + ly;
+    const int bidx = ((ly >> 3) * 2 + (lx >> 3)) * 64 + (ly & 7) * 8 + (lx & 7);  // backward's thread of this pixel
+    const bool inside = px < V.W && py < V.H;
+    const float fx = (float)px + 0.5f, fy = (float)py + 0.5f;
+    const uint32_t t_end = min(A0->ranges[2 * tile + 1], A0->cap);
+    const uint32_t t_start = min(A0->ranges[2 * tile], t_end);
+    const uint32_t b0 = first_batch(tile, t_start);
+    uint8_t* list = lists[wave];
+    float T = 1.f, C0 = 0.f, C1 = 0.f, C2 = 0.f;
+    uint32_t last = 0;
+    uint64_t live = ballot(inside);  // lanes of pixels that have not stopped (whole quads)
+    uint32_t n_ck = 0;               // batches processed (checkpoints written)
+    // Staging: every wave loads 64 records of batch c + 1 straight into LDS
+    // while batch c is blended, and the record ids of batch c + 2 into
+    // registers; batch 0's loads start here.
+    __syncthreads();  // the previous item's LDS is read
+    if (tid == 0) s_est = 0;
+    // in a training forward, where the band leaves each sorted pair's block
+    // masks for the backward: in the other half of pair_vals (free once the
+    // sort is done), one byte plane per band
+    const bool second = *A0->sel != 0;
+    const uint32_t* vals = A0->pair_vals + (second ? A0->cap : 0u);
+    float4* ckpt = A0->ckpt;
+    uint8_t* blk_out = reinterpret_cast<uint8_t*>(const_cast<uint32_t*>(A0->pair_vals) + (second ? 0u : A0->cap)) +
+                       (size_t)band * A0->cap;
+    const float* records = args.records;
+    const uint32_t n_rec = args.n_rec;
+    uint32_t rid = t_start + (uint32_t)tid < t_end ? vals[t_start + tid] : 0u;
+    stage_async(R[0], records, n_rec, rid, t_start + (uint32_t)tid < t_end);
+    {
+      const uint32_t k = t_start + kBatch + (uint32_t)tid;
+      rid = k < t_end ? vals[k] : 0u;
+    }
+    for (uint32_t start = t_start, c = 0; start < t_end; start += kBatch, ++c) {
+      // this batch's records have landed (each wave waits for its own loads);
+      // the block leaves once every pixel of the band has stopped: each wave
+      // posts its flag, one barrier (which also shows the records to every
+      // wave and orders the previous batch's reads of the other buffer before
+      // its refill), every wave reads the four posts (the other parity's
+      // posts are rewritten only after the next batch's barriers)
+      __builtin_amdgcn_s_waitcnt(kWaitVm0);
+      if (lane == 0) reinterpret_cast<uint8_t*>(&s_live[c & 1])[wave] = live != 0ull ? 1 : 0;
+      __syncthreads();
+      if (s_live[c & 1] == 0u) break;
+      if (ckpt && tid == 0 && c > 0) {
+        if (b0 + c - 1 < args.batch_cap) atomicMax(&args.batch_tile[b0 + c - 1], batch_word(tile, s_est));
+        s_est = 0;
+      }
+      const int n = (int)min((uint32_t)kBatch, t_end - start);
+      const BatchRaw& L = R[c & 1];
+      {
+        const uint32_t nstart = start + kBatch;
+        if (nstart < t_end) stage_async(R[(c + 1) & 1], records, n_rec, rid, nstart + (uint32_t)tid < t_end);
+        const uint32_t k = nstart + kBatch + (uint32_t)tid;
+        rid = k < t_end ? vals[k] : 0u;
+      }
+      {
+        // thread t: the band's 4 x 4 blocks that pair t's ellipse reaches
+        uint32_t bits = 0u;
+        if (tid < n) {
+          const float4 A = L.a[tid], B = L.b[tid];
+          bits = band_blocks(A.x, A.y, A.z, A.w, B.x, reach_cutoff(B.y), (float)(tx * kTile) + 0.5f,
+                             (float)(ty * kTile + band * kQuadPix) + 0.5f);
+        }
+        nib[tid] = (uint8_t)bits;
+        if (ckpt && tid < n) blk_out[start + tid] = (uint8_t)bits;
+      }
+      lds_barrier();
+      const float T0 = T;
+      float D0 = 0.f, D1 = 0.f, D2 = 0.f;
+      int lst = -1;  // batch index of the pixel's last blended pair
+      const int cnt = live ? wave_list(nib, wave, list, n) : 0;
+      int t0 = 0;
+      for (; t0 < cnt && live != 0ull; t0 += 4) {
+        // past the list's end an old entry is read and masked out
+        const int j = (int)list[t0 + slot];
+        const float4 A = L.a[j], B = L.b[j];
+        const float cb = L.c[j];
+        const float power = pair_power(A, B, A.x - fx, A.y - fy);
+        const float alpha = fminf(kAlphaMax, B.y * pair_gauss(power));
+        // the masks are scalar: lanes whose pair blends unless the pixel stops
+        const uint64_t has = cnt - t0 >= 4 ? ~0ull : 0x1111111111111111ull * ((1ull << (cnt - t0)) - 1ull);
+        uint64_t blend = ballot(power <= 0.f) & ballot(alpha >= kAlphaMin) & live & has;
+        float al = __builtin_amdgcn_inverse_ballot_w64(blend) ? alpha : 0.f;
+        const float f = 1.f - al;
+        // P: product of f over the slots up to this one; TE: transmittance in front
+        const float f1 = f * qperm<0x90>(f);    // quad_perm [0,0,1,2]
+        const float P1 = slot >= 1 ? f1 : f;
+        const float f2 = P1 * qperm<0x40>(P1);  // quad_perm [0,0,0,1]
+        float P = slot >= 2 ? f2 : P1;
+        const float te = T * qperm<0x90>(P);
+        const float TE = slot >= 1 ? te : T;
+        const uint64_t stop = ballot(T * P < kTStop) & blend;
+        if (stop != 0ull) {  // (wave-uniform, rare) some pixel stops in this step
+          // a slot blends if no slot of its quad up to it stops
+          uint64_t m = stop | ((stop & 0x7777777777777777ull) << 1);
+          m |= (m & 0x3333333333333333ull) << 2;
+          blend &= ~m;
+          al = __builtin_amdgcn_inverse_ballot_w64(blend) ? al : 0.f;
+          // the product over the slots that blend, in every slot
+          P = 1.f - al;
+          P *= dpp<0xB1, 0xF>(P);  // quad_perm [1,0,3,2]
+          P *= dpp<0x4E, 0xF>(P);  // quad_perm [2,3,0,1]
+          live &= ~(((m >> 3) & 0x1111111111111111ull) * 15ull);  // (a stop reaches slot 3)
+        }
+        const float w = al * TE;
+        D0 = fmaf(B.z, w, D0);
+        D1 = fmaf(B.w, w, D1);
+        D2 = fmaf(cb, w, D2);
+        lst = __builtin_amdgcn_inverse_ballot_w64(blend) ? j : lst;
+        T *= qperm<0xFF>(P);  // quad_perm [3,3,3,3]: the whole quad's product
+      }
+      const int stepped = min(cnt, t0);
+      if (ckpt && lane == 0 && stepped > 0) atomicMax(&s_est, (uint32_t)stepped);
+      D0 = quad_sum(D0);
+      D1 = quad_sum(D1);
+      D2 = quad_sum(D2);
+      lst = quad_max(lst);
+      C0 += D0;
+      C1 += D1;
+      C2 += D2;
+      last = lst >= 0 ? start + (uint32_t)lst + 1u : last;
+      if (ckpt && slot == 0 && b0 + c < args.batch_cap) ckpt[(size_t)(b0 + c) * kBatch + bidx] = make_float4(T0, D0, D1, D2);
+      n_ck = c + 1;
+    }
+    if (ckpt) {
+      uint32_t* batch_tile = args.batch_tile;
+      const uint32_t batch_cap = args.batch_cap;
+      // the last batch reached, then (one band writes them) all of the tile's
+      __syncthreads();
+      if (tid == 0 && n_ck > 0 && b0 + n_ck - 1 < batch_cap)
+        atomicMax(&batch_tile[b0 + n_ck - 1], batch_word(tile, s_est));
+      const uint32_t nb = (t_end - t_start + (uint32_t)kBatch - 1) / (uint32_t)kBatch;
+      if (band == 0)
+        for (uint32_t c = n_ck + tid; c < nb; c += 256)
+          if (b0 + c < batch_cap) atomicMax(&batch_tile[b0 + c], batch_word(tile, 0));
+      if (slot == 0) {
+        // replace each batch's colour by the colour behind the batch: the
+        // background under the final transmittance plus the later batches,
+        // summed from the back (a batch after the pixel stopped adds 0)
+        float a0 = T * V.bg[0], a1 = T * V.bg[1], a2 = T * V.bg[2];
+        for (int cc = (int)n_ck - 1; cc >= 0; --cc) {
+          if (b0 + (uint32_t)cc >= batch_cap) continue;
+          float4* q = ckpt + (size_t)(b0 + (uint32_t)cc) * kBatch + bidx;
+          const float4 d = *q;
+          *q = make_float4(d.x, a0, a1, a2);
+          a0 += d.y;
+          a1 += d.z;
+          a2 += d.w;
+        }
+      }
+    }
+    if (inside) store_pixel(V, px, py, slot, T, C0, C1, C2, last);
+  }
+}
+
+hipError_t launch_blend_fwd(const ViewD* views_dev, int n_views, uint32_t total_tiles, const float* records,
+                            uint32_t n_rec, const uint32_t* pair_vals, const uint32_t* sel, uint32_t cap,
+                            const uint32_t* ranges, uint32_t* batch_tile, uint32_t batch_cap,
+                            const int32_t* req_status, float4* ckpt, const uint32_t* class_count,
+                            const uint32_t* class_list, hipStream_t s) {
   if (total_tiles == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_blend_tile, dim3(total_tiles), dim3(1024), 0, s, views_dev, n_views, total_tiles, records,
-                     n_rec, pair_vals, sel, cap, ranges, batch_tile, batch_cap, req_status, ckpt, class_count,
-                     class_list);
+  // a block per band of every tile, so that the dispatcher balances them;
+  // beyond kFwdBlocks a block takes further items (on a stereo frame of 27600
+  // tiles, half of them empty, 2^12 / 2^14 / 2^16 / 2^17 blocks: 242 / 219 /
+  // 213 / 225 us).  A multiple of 32: the
+  // bands of a tile stay on one XCD.
+  constexpr uint32_t kFwdBlocks = 1u << 16;
+  const uint32_t grid = std::min(div_up(total_tiles, kXcds) * kXcds * 4u, kFwdBlocks);
+  const FwdArgs a{views_dev, records, pair_vals, sel, ranges, batch_tile, req_status, ckpt, class_count, class_list,
+                  n_views, total_tiles, n_rec, cap, batch_cap};
+  hipLaunchKernelGGL(k_blend_fwd, dim3(grid), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
@@ -579,7 +645,7 @@ k_batch_order(const uint32_t* __restrict__ batch_tile, uint32_t n, uint32_t* __r
   for (uint32_t r = 0; r < kOrderItems; ++r) {
     const uint32_t i = i0 + r * 1024u;
     const uint32_t word = i < n ? batch_tile[i] : 0u;
-    cls[r] = (word & kBatchTileMask) ? min(word >> 24, kBatchClasses - 1) : kBatchClasses;
+    cls[r] = (word & kBatchTileMask) ? kBatchClasses - 1 - min(word >> 24, kBatchClasses - 1) : kBatchClasses;
     if (cls[r] < kBatchClasses) rank[r] = atomicAdd(&s_cnt[cls[r]], 1u);
   }
   __syncthreads();
@@ -615,6 +681,7 @@ k_blend_bwd(const ViewD* __restrict__ views, int n_views, const float* __restric
   constexpr int kSubPad = kSub + 1;
   __shared__ float part[4][kGradSlots][kSubPad];
   __shared__ uint16_t s_blk[kBatch];  // block masks the forward left
+  __shared__ uint32_t s_emit[kBatch], s_gauss[kBatch];  // where pair j's partial goes, its Gaussian
   // block b takes the b-th batch of the heaviest-first order: the first wave
   // scans the class counts and finds b's class
   __shared__ uint32_t s_bi;
@@ -643,7 +710,7 @@ k_blend_bwd(const ViewD* __restrict__ views, int n_views, const float* __restric
   // The forward evaluated none of this batch's pairs at a live pixel (its
   // pixels had stopped, or no pair's ellipse reaches one): every partial is
   // zero, and none is written (their alive flags stay 0).
-  if ((word >> 24) == kBatchClasses - 1) return;
+  if ((word >> 24) == 0u) return;
   const int vi = find_view(views, n_views, tile);
   const ViewD& V = views[vi];
   const uint32_t* vals = pair_vals + (*sel ? cap : 0u);
@@ -694,35 +761,41 @@ k_blend_bwd(const ViewD* __restrict__ views, int n_views, const float* __restric
     }
   }
   // thread t stages pair t and later combines its sums (sub-batch t / kSub
-  // runs on wave t / kSub), so the pair's exact conic, opacity and emission
-  // index stay in its registers
+  // runs on wave t / kSub)
   const uint32_t my_rec = tid < n ? vals[start + tid] : n_rec;
-  const Staged mine = fetch_record(records, n_rec, my_rec, tid < n);
-  put(L, mine, tid < n, tid);
+  put(L, fetch_record(records, n_rec, my_rec, tid < n), tid < n, tid);
   {
-    const uint16_t* blk = reinterpret_cast<const uint16_t*>(pair_vals + (*sel ? 0u : cap));
-    s_blk[tid] = tid < n ? blk[start + tid] : (uint16_t)0;
+    const uint8_t* blk = reinterpret_cast<const uint8_t*>(pair_vals + (*sel ? 0u : cap)) + start + tid;
+    s_blk[tid] = tid < n ? (uint16_t)(blk[0] | (blk[cap] << 4) | (blk[2 * (size_t)cap] << 8) | (blk[3 * (size_t)cap] << 12))
+                         : (uint16_t)0;
   }
   // emission index of the pair, where its partial goes: as the per-tile sort
   // left it, or (order-first) the record's first one plus the tile's place in
   // its box.  One at or beyond the capacity is not written.
-  uint32_t my_emit = cap;
-  if (tid < n) {
-    if (!boxes) {
-      my_emit = pair_emit[start + tid];
-    } else if (my_rec < n_rec) {
-      const uint2 bx = boxes[my_rec];
-      my_emit = offsets[my_rec] + ((uint32_t)ty - (bx.x >> 16)) * (bx.y & 0xFFFFu) + ((uint32_t)tx - (bx.x & 0xFFFFu));
+  {
+    uint32_t emit = cap;
+    if (tid < n) {
+      if (!boxes) {
+        emit = pair_emit[start + tid];
+      } else if (my_rec < n_rec) {
+        const uint2 bx = boxes[my_rec];
+        emit = offsets[my_rec] + ((uint32_t)ty - (bx.x >> 16)) * (bx.y & 0xFFFFu) + ((uint32_t)tx - (bx.x & 0xFFFFu));
+      }
     }
+    s_emit[tid] = emit;
+    s_gauss[tid] = my_rec < n_rec ? my_rec - V.rec_off : 0xFFFFFFFFu;
   }
   for (int i = tid; i < 4 * kGradSlots * kSubPad; i += 256) (&part[0][0][0])[i] = 0.f;
-  // the wave's 8 x 8 quadrant: 2 x 2 of the tile's 4 x 4 blocks
-  const uint32_t qmask = 0x33u << (2 * (wave & 1) + 8 * (wave >> 1));
-  // the wave's reach: no pair at or behind its pixels' last blended pair counts
-  int n_wave = lim;
+  // the wave's 8 x 8 quadrant: 2 x 2 of the tile's 4 x 4 blocks, its upper
+  // half (lanes 0-31) in one band of the forward, its lower in the next
+  const uint32_t qmask = 3u << (2 * (wave & 1) + 8 * (wave >> 1));
+  // the halves' reach: no pair at or behind their pixels' last blended pair
+  // counts (nor was a band's mask written once all its pixels had stopped)
+  int n_up = lim;
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) n_wave = max(n_wave, __shfl_xor(n_wave, off, 64));
-  n_wave = __builtin_amdgcn_readfirstlane(n_wave);
+  for (int off = 16; off > 0; off >>= 1) n_up = max(n_up, __shfl_xor(n_up, off, 64));
+  const int n_low = __builtin_amdgcn_readlane(n_up, 32);
+  n_up = __builtin_amdgcn_readfirstlane(n_up);
   __syncthreads();
 
   // back to front in sub-batches of kSub pairs; after each, the four wave
@@ -793,7 +866,8 @@ k_blend_bwd(const ViewD* __restrict__ views, int n_views, const float* __restric
     // gives the set of those that can reach alpha >= 1/255 at a pixel centre
     // of its quadrant in front of its pixels' last blended pair
     const int jl = j0 + lane;
-    uint64_t m = ballot(jl < n_wave && (s_blk[jl] & qmask) != 0u);
+    const uint32_t reach = s_blk[jl];
+    uint64_t m = ballot((jl < n_up && (reach & qmask) != 0u) || (jl < n_low && (reach & (qmask << 4)) != 0u));
     // two pairs per step (the second, in front, may be absent)
     while (m != 0ull) {
       const int ja = pop(m);
@@ -839,7 +913,7 @@ k_blend_bwd(const ViewD* __restrict__ views, int n_views, const float* __restric
       float m9[9], o[12];
 #pragma unroll
       for (int q = 0; q < 9; ++q) m9[q] = ((part[0][q][js] + part[1][q][js]) + part[2][q][js]) + part[3][q][js];
-      const float4 A = mine.a, B = mine.b;  // the conic unscaled
+      const float4 A = L.a[tid], B = L.b[tid];
       o[0] = -fmaf(A.z, m9[0], A.w * m9[1]);
       o[1] = -fmaf(A.w, m9[0], B.x * m9[1]);
       o[2] = -0.5f * m9[2];
@@ -852,21 +926,22 @@ k_blend_bwd(const ViewD* __restrict__ views, int n_views, const float* __restric
       // the largest alpha T of the Gaussian over its pairs and views: weights
       // are not negative, so the integer order of the bits is theirs, and a
       // maximum does not depend on the order it is taken in
-      if (g_max && my_rec < n_rec) {
+      if (g_max && s_gauss[tid] != 0xFFFFFFFFu) {
         const float w = fmaxf(fmaxf(part[0][9][js], part[1][9][js]), fmaxf(part[2][9][js], part[3][9][js]));
-        if (w > 0.f) atomicMax(&g_max[my_rec - V.rec_off], __float_as_uint(w));
+        if (w > 0.f) atomicMax(&g_max[s_gauss[tid]], __float_as_uint(w));
       }
 #pragma unroll
       for (int w = 0; w < 4; ++w)
 #pragma unroll
         for (int q = 0; q < kGradSlots; ++q) part[w][q][js] = 0.f;
       o[9] = o[10] = o[11] = 0.f;
-      if (my_emit < cap) {
-        float4* dst = reinterpret_cast<float4*>(g_pair + (size_t)my_emit * 12);
+      const uint32_t emit = s_emit[tid];
+      if (emit < cap) {
+        float4* dst = reinterpret_cast<float4*>(g_pair + (size_t)emit * 12);
         dst[0] = make_float4(o[0], o[1], o[2], o[3]);
         dst[1] = make_float4(o[4], o[5], o[6], o[7]);
         dst[2] = make_float4(o[8], o[9], o[10], o[11]);
-        alive[my_emit] = 1;
+        alive[emit] = 1;
       }
     }
     __syncthreads();

@@ -18,8 +18,8 @@ constexpr int kSortTile = kSortThreads * kSortItems;
 constexpr int kBatch = 256;          // pairs per blend batch (one per thread of a tile block)
 constexpr uint32_t kTileClasses = 34;  // tile size classes of the forward's largest-first order
 // Work classes of the backward's batches (heaviest first; the last class holds
-// the batches the forward never reached), kept in the top byte of the
-// batch-to-tile words; the low 24 bits hold 1 + tile.
+// the batches the forward never reached); the top byte of a batch-to-tile word
+// holds the weight kBatchClasses - 1 - class, the low 24 bits 1 + tile.
 constexpr uint32_t kBatchClasses = 17;
 constexpr uint32_t kBatchTileMask = 0xFFFFFFu;
 constexpr uint32_t kSegWaveMax = 512;  // tiles with more pairs are depth-sorted by a whole block
@@ -61,8 +61,8 @@ struct ViewD {
   float bg[3];
   float* rgb;          // [3][H][W]
   float* alpha;        // [H][W]
-  float* pix;          // [H][W][4]: final transmittance, colour before the background
-  uint32_t* last;      // [H][W]
+  float* pix;          // [H][W][4]: final transmittance, colour before the background; null in a batch
+  uint32_t* last;      // [H][W] (null with pix)
   // Depth order of a call that sorts records before pairing them (order.hip):
   // kSortNone in the per-tile path; a sort unit's records take slots
   // [sort_off, sort_off + sort_n) of the record sort, keyed by the view's own
@@ -251,11 +251,11 @@ hipError_t launch_tile_order(const uint32_t* ranges, uint32_t n_tiles, uint32_t*
 hipError_t launch_ranges(const uint64_t* keys_a, const uint64_t* keys_b, const uint32_t* sel,
                          uint32_t* counters, uint32_t pair_capacity, uint32_t total_tiles, uint32_t* ranges,
                          hipStream_t s);
-hipError_t launch_blend_fwd_tile(const ViewD* views_dev, int n_views, uint32_t total_tiles, const float* records,
-                                 uint32_t n_rec, const uint32_t* pair_vals, const uint32_t* sel, uint32_t cap,
-                                 const uint32_t* ranges, uint32_t* batch_tile, uint32_t batch_cap,
-                                 const int32_t* req_status, float4* ckpt, const uint32_t* class_count,
-                                 const uint32_t* class_list, hipStream_t s);
+hipError_t launch_blend_fwd(const ViewD* views_dev, int n_views, uint32_t total_tiles, const float* records,
+                            uint32_t n_rec, const uint32_t* pair_vals, const uint32_t* sel, uint32_t cap,
+                            const uint32_t* ranges, uint32_t* batch_tile, uint32_t batch_cap,
+                            const int32_t* req_status, float4* ckpt, const uint32_t* class_count,
+                            const uint32_t* class_list, hipStream_t s);
 uint32_t l1_loss_blocks(int n_views, int hw);
 hipError_t launch_l1_loss(int n_views, int hw, const float* rgb, const float* alpha, const float* t_rgb,
                           const float* t_alpha, const float* bg_host, float* partials, float* loss,
