@@ -96,7 +96,7 @@ struct OrderPlan {
   bool own_boxes = false;  // tile boxes in the workspace, not in the state's pair_emit
   size_t S = 0;            // sort slots: records of all sort units
   size_t rec_blocks = 0, seq_blocks = 0;
-  uint32_t seq_tile = 0;   // emit_tile of the call's records
+  uint32_t rec_tile = 0, seq_tile = 0;  // rec_tile, emit_tile of the call's records
   bool small = true;       // every unit has at most kRecSmall records
 };
 
@@ -257,7 +257,7 @@ void plan_order(OrderPlan& op, std::vector<ViewD>& views, const std::vector<int>
     }
     op.S += n[v];
     op.small = op.small && n[v] <= kRecSmall;
-    op.rec_blocks += div_up(n[v], kRecTile);
+    op.rec_blocks += div_up(n[v], op.rec_tile);
   }
 }
 
@@ -271,6 +271,7 @@ OrderBufs order_bufs(const PipeBufs& b, const OrderPlan& op, int n_views, size_t
   o.rec_blocks = (uint32_t)op.rec_blocks;
   o.seq_blocks = (uint32_t)op.seq_blocks;
   o.seq_tile = op.seq_tile;
+  o.rec_tile = op.rec_tile;
   o.small = op.small;
   o.keys_a = b.sort_keys;
   o.keys_b = b.sort_keys + std::max<size_t>(op.S, 1);
@@ -337,7 +338,8 @@ OrderPlan single_plan(int64_t n, int n_views, uint64_t X, uint32_t P, bool share
   op.own_boxes = shared;  // a forward that shares an order has no backward
   const int units = shared ? 1 : n_views;
   op.S = (size_t)units * n;
-  op.rec_blocks = (size_t)units * div_up((uint32_t)n, kRecTile);
+  op.rec_tile = rec_tile((uint64_t)n * units);
+  op.rec_blocks = (size_t)units * div_up((uint32_t)n, op.rec_tile);
   op.small = (uint64_t)n <= kRecSmall;
   op.seq_tile = emit_tile((uint64_t)n * n_views);
   op.seq_blocks = (size_t)n_views * div_up((uint32_t)n, op.seq_tile);
@@ -940,6 +942,7 @@ bool plan_batch(const gsr_model* models, int32_t n_models, const gsr_request* re
   if (bp.order.on) {
     bp.order.own_boxes = true;
     bp.order.seq_tile = emit_tile(bp.R);
+    bp.order.rec_tile = rec_tile(bp.R);
     // each view is a sort unit by its own depth, except the eyes of a
     // request that shares one order: the first eye sorts by the request's
     // sort camera, the second follows it

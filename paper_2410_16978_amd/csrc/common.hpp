@@ -84,7 +84,10 @@ struct ViewD {
 };
 constexpr uint32_t kSortNone = 0, kSortOwn = 1, kSortCamera = 2, kSortFollow = 3;
 constexpr uint32_t kSortCulled = 0xFFFFFFFFu;  // sort key of a record no view of its unit keeps (never a depth)
-constexpr uint32_t kRecTile = 4096;   // records per block of a record pass
+// Records per block of a record pass: the blocks' look-back chain bounds a
+// pass over many records, the number of blocks one over few.
+constexpr uint32_t kRecTile = 8192, kRecTileSmall = 4096;
+inline uint32_t rec_tile(uint64_t records) { return records > (8u << 20) ? kRecTile : kRecTileSmall; }
 constexpr uint32_t kRecSmall = 8192;  // units up to this size are sorted by one block each
 // Sequence positions per run of the emission: with 4096 the tickets of 32M
 // positions do not queue up, with 1024 two million positions fill the chip.
@@ -200,7 +203,7 @@ struct OrderBufs {
   const ViewD* views;
   int n_views;
   uint32_t n_tiles;               // of all views
-  uint32_t rec_blocks, seq_blocks, seq_tile;
+  uint32_t rec_blocks, seq_blocks, rec_tile, seq_tile;
   bool small;                     // every unit has at most kRecSmall records
   uint32_t *keys_a, *keys_b;      // depth keys by sort slot (the projection writes keys_a), double-buffered
   uint32_t *vals_a, *vals_b;      // records by sort slot
@@ -215,7 +218,7 @@ struct OrderBufs {
   uint64_t* emit_status;          // [seq_blocks]
   uint32_t* pair_counts;          // [pair_pass_blocks][256]
   uint32_t* tile_total;           // [256]
-  uint32_t* tickets;              // [8]: record passes, emission
+  uint32_t* tickets;              // [8]: record passes, emission, byte passes some unit needs
   uint32_t* ranges;
   uint32_t* sel;
 };

@@ -120,8 +120,8 @@ __device__ __forceinline__ uint32_t look_back(const uint32_t* __restrict__ st, i
 // ---------------------------------------------------------------- record sort
 constexpr int kRecThreads = 512;
 constexpr int kRecWaves = kRecThreads / 64;
-constexpr int kRecItems = 8;
-static_assert(kRecThreads * kRecItems == kRecTile, "records per pass block");
+constexpr int kRecHistItems = 8;
+static_assert(kRecThreads * kRecHistItems == (int)kRecTileSmall && kRecThreads * 16 == (int)kRecTile, "records per pass block");
 
 // Digit counts [view][pass][256] of the kept records' keys.  A block takes a
 // run of pass blocks and adds its counts once per unit it meets.  The top
@@ -129,7 +129,8 @@ static_assert(kRecThreads * kRecItems == kRecTile, "records per pass block");
 // once.
 __device__ __forceinline__ void rec_hist(const ViewD* __restrict__ views, int n_views,
                                          const uint32_t* __restrict__ keys, uint32_t n_blk,
-                                         uint32_t* __restrict__ hist, uint32_t blk, uint32_t n_blocks) {
+                                         uint32_t* __restrict__ hist, uint32_t blk, uint32_t n_blocks,
+                                         uint32_t tile) {
   __shared__ uint32_t lh[kRecPasses * 256];
   const int t = threadIdx.x;
   for (int i = t; i < kRecPasses * 256; i += kRecThreads) lh[i] = 0;
@@ -153,25 +154,27 @@ __device__ __forceinline__ void rec_hist(const ViewD* __restrict__ views, int n_
       cur = v;
     }
     const ViewD& V = views[v];
-    const uint32_t base = (b - V.sort_blk) * (uint32_t)kRecTile;
-    uint32_t k[kRecItems];
+    for (uint32_t sub = 0; sub < tile; sub += kRecTileSmall) {
+      const uint32_t base = (b - V.sort_blk) * tile + sub;
+      uint32_t k[kRecHistItems];
 #pragma unroll
-    for (int r = 0; r < kRecItems; ++r) {
-      const uint32_t i = base + (uint32_t)(r * kRecThreads) + t;
-      k[r] = i < V.sort_n ? keys[V.sort_off + i] : kSortCulled;
-    }
+      for (int r = 0; r < kRecHistItems; ++r) {
+        const uint32_t i = base + (uint32_t)(r * kRecThreads) + t;
+        k[r] = i < V.sort_n ? keys[V.sort_off + i] : kSortCulled;
+      }
 #pragma unroll
-    for (int r = 0; r < kRecItems; ++r) {
-      const bool ok = k[r] != kSortCulled;
-      const uint64_t m = __ballot(ok);
-      if (ok) {
+      for (int r = 0; r < kRecHistItems; ++r) {
+        const bool ok = k[r] != kSortCulled;
+        const uint64_t m = __ballot(ok);
+        if (ok) {
 #pragma unroll
-        for (int q = 0; q < kRecPasses - 1; ++q) atomicAdd(&lh[q * 256 + ((k[r] >> (8 * q)) & 255u)], 1u);
-        const uint32_t d = k[r] >> 24, d0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)d);
-        if (__ballot(d == d0) == m) {
-          if ((m & ord_lanes_below()) == 0ull) atomicAdd(&lh[3 * 256 + d0], (uint32_t)__popcll(m));
-        } else {
-          atomicAdd(&lh[3 * 256 + d], 1u);
+          for (int q = 0; q < kRecPasses - 1; ++q) atomicAdd(&lh[q * 256 + ((k[r] >> (8 * q)) & 255u)], 1u);
+          const uint32_t d = k[r] >> 24, d0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)d);
+          if (__ballot(d == d0) == m) {
+            if ((m & ord_lanes_below()) == 0ull) atomicAdd(&lh[3 * 256 + d0], (uint32_t)__popcll(m));
+          } else {
+            atomicAdd(&lh[3 * 256 + d], 1u);
+          }
         }
       }
     }
@@ -182,15 +185,16 @@ __device__ __forceinline__ void rec_hist(const ViewD* __restrict__ views, int n_
 // The scan of the tile counts in record order (the pair count, and where the
 // backward keeps each record's partials) and the digit counts in one launch:
 // neither needs the other.
+template <int ITEMS>
 __global__ void __launch_bounds__(kRecThreads)
 k_scan_hist(const ViewD* __restrict__ views, int n_views, const uint32_t* __restrict__ keys, uint32_t n_blk,
             uint32_t* __restrict__ hist, uint32_t n_scan, const uint32_t* __restrict__ n_tiles, uint32_t n_rec,
             uint32_t* __restrict__ offsets, uint64_t* __restrict__ status, uint32_t* __restrict__ ticket,
-            uint32_t* __restrict__ counters, uint32_t cap) {
+            uint32_t* __restrict__ counters, uint32_t cap, uint32_t rec_tile) {
   if (blockIdx.x < n_scan)
-    scan_block<kRecThreads>(n_tiles, n_rec, offsets, status, ticket, counters, cap, n_scan);
+    scan_block<kRecThreads, ITEMS>(n_tiles, n_rec, offsets, status, ticket, counters, cap, n_scan);
   else
-    rec_hist(views, n_views, keys, n_blk, hist, blockIdx.x - n_scan, gridDim.x - n_scan);
+    rec_hist(views, n_views, keys, n_blk, hist, blockIdx.x - n_scan, gridDim.x - n_scan, rec_tile);
 }
 
 // Units of at most kRecSmall records each: a block sorts one in LDS, in place
@@ -321,20 +325,23 @@ k_rec_small(const ViewD* __restrict__ views, const uint32_t* __restrict__ keys, 
 
 // One stable pass.  The first reads every slot of the unit in record order,
 // drops the culled ones and always moves; a later pass whose digit is the
-// same for the whole unit is skipped.  unit[2 v], unit[2 v + 1]: the unit's
-// kept records and the buffer that holds them after the last pass.
-template <bool FIRST>
-__global__ void __launch_bounds__(kRecThreads)
+// same for the whole unit is skipped (one that is the same for every unit
+// before it takes a ticket; *needed: the others).  unit[2 v], unit[2 v + 1]:
+// the unit's kept records and the buffer that holds them after the last pass.
+template <bool FIRST, int kRecItems>
+__global__ void __launch_bounds__(kRecThreads, 4)
 k_rec_pass(const ViewD* __restrict__ views, int n_views, uint32_t* __restrict__ keys0, uint32_t* __restrict__ keys1,
            uint32_t* __restrict__ vals0, uint32_t* __restrict__ vals1, const uint32_t* __restrict__ hist,
            uint32_t* __restrict__ status, uint32_t* __restrict__ ticket, uint32_t* __restrict__ unit,
-           uint32_t* __restrict__ err, int pass) {
+           uint32_t* __restrict__ needed, uint32_t* __restrict__ err, int pass) {
+  constexpr uint32_t kTileRec = kRecThreads * kRecItems;
   __shared__ uint32_t s_bid, s_triv;
   __shared__ uint16_t wave_cnt[kRecWaves][256];
   __shared__ uint32_t s_start[256], s_global[256];
   __shared__ uint32_t s_w[4], s_hw[4];
-  __shared__ uint32_t s_keys[kRecTile], s_vals[kRecTile];
+  __shared__ uint32_t s_keys[kTileRec], s_vals[kTileRec];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  if (!FIRST && ((*needed >> pass) & 1u) == 0u) return;  // every unit agrees on this byte
   if (t == 0) {
     s_bid = atomicAdd(ticket, 1u);
     s_triv = 0;
@@ -356,24 +363,22 @@ k_rec_pass(const ViewD* __restrict__ views, int n_views, uint32_t* __restrict__ 
   }
   __syncthreads();
   const uint32_t K = s_hw[0] + s_hw[1] + s_hw[2] + s_hw[3];
-  if (!FIRST) {
-    if (t < 256) {
+  if (t < 256) {
 #pragma unroll
-      for (int q = 1; q < kRecPasses; ++q)
-        if (hv[q] == K) atomicOr(&s_triv, 1u << q);
-    }
-    __syncthreads();
+    for (int q = 1; q < kRecPasses; ++q)
+      if (hv[q] == K) atomicOr(&s_triv, 1u << q);
   }
-  const uint32_t triv = FIRST ? 0u : s_triv;
-  const uint32_t before = (1u << pass) - 1u;
-  const uint32_t moved = (uint32_t)__popc(before & ~triv);
-  if (pass == kRecPasses - 1 && lb == 0 && t == 0) {
+  __syncthreads();
+  const uint32_t triv = s_triv, moves = ((1u << kRecPasses) - 1u) & ~triv;
+  if (FIRST && lb == 0 && t == 0) {
     unit[2 * v] = K;
-    unit[2 * v + 1] = (uint32_t)__popc(((1u << kRecPasses) - 1u) & ~triv) & 1u;
+    unit[2 * v + 1] = (uint32_t)__popc(moves) & 1u;
+    atomicOr(needed, moves);
   }
-  if ((triv >> pass) & 1u) return;
+  if (!FIRST && ((triv >> pass) & 1u)) return;
+  const uint32_t moved = (uint32_t)__popc(moves & ((1u << pass) - 1u));
   const uint32_t n_in = FIRST ? views[v].sort_n : K;
-  const uint32_t base = lb * (uint32_t)kRecTile;
+  const uint32_t base = lb * kTileRec;
   if (base >= n_in) return;
   const bool src = !FIRST && (moved & 1u);
   const uint32_t* kin = (src ? keys1 : keys0) + off;
@@ -655,33 +660,36 @@ template <typename TT>
 __global__ void __launch_bounds__(kPairThreads)
 k_pair_count(const TT* __restrict__ tiles, const uint32_t* __restrict__ counters, uint32_t cap, uint32_t step,
              int shift, uint32_t mask, uint32_t* __restrict__ counts) {
-  __shared__ uint32_t lh[256];
-  constexpr uint32_t kItems = 16 / sizeof(TT);  // one 16-byte load
+  // eight counters per digit, by lane: the second pass meets runs of few
+  // digits (one view's tile rows), whose additions would queue on one word
+  constexpr uint32_t kRep = 8;
+  __shared__ uint32_t lh[256 * kRep];
   const int t = threadIdx.x;
-  if (t < 256) lh[t] = 0;
+  for (int i = t; i < (int)(256 * kRep); i += kPairThreads) lh[i] = 0;
   __syncthreads();
+  const uint32_t rep = (uint32_t)t % kRep;
   const uint32_t K = min(counters[kCntPairs], cap);
   uint32_t begin, end;
   pair_share(K, blockIdx.x, gridDim.x, step, begin, end);
-  for (uint32_t k = begin + (uint32_t)t * kItems; k < end; k += kPairThreads * kItems) {
-    if (k + kItems <= end) {
-      const uint4 q = *reinterpret_cast<const uint4*>(tiles + k);
-      const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+  // lanes take consecutive pairs: in emission order their tiles are
+  // consecutive too, and the additions fall in different banks
+  constexpr uint32_t kAhead = 8;  // loads in flight per thread
+  uint32_t k = begin + (uint32_t)t;
+  for (; (uint64_t)k + (kAhead - 1) * kPairThreads < end; k += kAhead * kPairThreads) {
+    TT q[kAhead];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        if constexpr (sizeof(TT) == 2) {
-          atomicAdd(&lh[((w[j] & 0xFFFFu) >> shift) & mask], 1u);
-          atomicAdd(&lh[((w[j] >> 16) >> shift) & mask], 1u);
-        } else {
-          atomicAdd(&lh[(w[j] >> shift) & mask], 1u);
-        }
-      }
-    } else {
-      for (uint32_t i = k; i < end; ++i) atomicAdd(&lh[((uint32_t)tiles[i] >> shift) & mask], 1u);
-    }
+    for (uint32_t u = 0; u < kAhead; ++u) q[u] = tiles[k + u * kPairThreads];
+#pragma unroll
+    for (uint32_t u = 0; u < kAhead; ++u) atomicAdd(&lh[(((uint32_t)q[u] >> shift) & mask) * kRep + rep], 1u);
   }
+  for (; k < end; k += kPairThreads) atomicAdd(&lh[(((uint32_t)tiles[k] >> shift) & mask) * kRep + rep], 1u);
   __syncthreads();
-  if (t < 256) counts[(size_t)blockIdx.x * 256 + t] = lh[t];
+  if (t < 256) {
+    uint32_t c = 0;
+#pragma unroll
+    for (uint32_t r = 0; r < kRep; ++r) c += lh[t * kRep + r];
+    counts[(size_t)blockIdx.x * 256 + t] = c;
+  }
 }
 
 // counts[b][d] becomes the count of digit d in the blocks before b, total[d]
@@ -941,11 +949,14 @@ uint32_t pair_pass_blocks(uint32_t cap) {
 // sort's digit counts.  Small units need no counts.
 hipError_t launch_order_scan(const OrderBufs& o, const uint32_t* n_tiles, uint32_t* offsets, uint64_t* scan_status,
                              uint32_t* scan_ticket, uint32_t n_rec, hipStream_t s) {
-  const uint32_t n_scan = div_up(n_rec + 1, (uint32_t)kRecThreads * kScanItems);
+  // (the scan's blocks look back along a chain: few long ones above 4M
+  // records, 166 -> 135 us at 32M with the digit counts beside it)
+  const bool big = n_rec > (1u << 22);
+  const uint32_t n_scan = div_up(n_rec + 1, (uint32_t)kRecThreads * (big ? 64u : (uint32_t)kScanItems));
   const uint32_t n_hist = o.small ? 0u : std::min(o.rec_blocks, 2u * (uint32_t)device_cus());
-  hipLaunchKernelGGL(k_scan_hist, dim3(n_scan + n_hist), dim3(kRecThreads), 0, s, o.views, o.n_views, o.keys_a,
-                     o.rec_blocks, o.rec_hist, n_scan, n_tiles, n_rec, offsets, scan_status, scan_ticket, o.counters,
-                     o.cap);
+  hipLaunchKernelGGL(big ? k_scan_hist<64> : k_scan_hist<kScanItems>, dim3(n_scan + n_hist), dim3(kRecThreads), 0, s,
+                     o.views, o.n_views, o.keys_a, o.rec_blocks, o.rec_hist, n_scan, n_tiles, n_rec, offsets,
+                     scan_status, scan_ticket, o.counters, o.cap, o.rec_tile);
   return hipGetLastError();
 }
 
@@ -959,9 +970,12 @@ hipError_t launch_order(const OrderBufs& o, hipStream_t s) {
     uint32_t* err = o.counters + kCntError;
     for (int p = 0; p < kRecPasses; ++p) {
       uint32_t* st = o.rec_status + (size_t)p * o.rec_blocks * 256;
-      const auto pass = p == 0 ? k_rec_pass<true> : k_rec_pass<false>;
+      const bool big = o.rec_tile == kRecTile;
+      const auto pass = p == 0 ? (big ? k_rec_pass<true, 16> : k_rec_pass<true, 8>)
+                               : (big ? k_rec_pass<false, 16> : k_rec_pass<false, 8>);
       hipLaunchKernelGGL(pass, dim3(o.rec_blocks), dim3(kRecThreads), 0, s, o.views, o.n_views, o.keys_a, o.keys_b,
-                         o.vals_a, o.vals_b, o.rec_hist, st, &o.tickets[p], o.unit, err, p);
+                         o.vals_a, o.vals_b, o.rec_hist, st, &o.tickets[p], o.unit, &o.tickets[5], err,
+                         p);
     }
   }
   if (o.seq_blocks == 0) return hipGetLastError();

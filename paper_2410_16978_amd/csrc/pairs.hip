@@ -11,7 +11,7 @@ namespace gsr {
 __global__ void __launch_bounds__(kScanThreads)
 k_scan(const uint32_t* __restrict__ in, uint32_t n, uint32_t* __restrict__ out, uint64_t* __restrict__ status,
        uint32_t* __restrict__ ticket, uint32_t* __restrict__ counters, uint32_t pair_capacity) {
-  scan_block<kScanThreads>(in, n, out, status, ticket, counters, pair_capacity, gridDim.x);
+  scan_block<kScanThreads, kScanItems>(in, n, out, status, ticket, counters, pair_capacity, gridDim.x);
 }
 
 uint32_t scan_tiles(uint32_t n) { return div_up(n + 1, (uint32_t)kScanTile); }

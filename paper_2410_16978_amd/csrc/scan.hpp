@@ -36,8 +36,8 @@ constexpr uint64_t kScanIncl = 2ull << 62;
 constexpr uint64_t kScanValue = (1ull << 62) - 1;
 constexpr uint32_t kScanSpinLimit = 1u << 22;
 
-// nb: the blocks of the launch that scan, THREADS kScanItems records each.
-template <int THREADS>
+// nb: the blocks of the launch that scan, THREADS ITEMS records each.
+template <int THREADS, int ITEMS>
 __device__ __forceinline__ void scan_block(const uint32_t* __restrict__ in, uint32_t n, uint32_t* __restrict__ out,
                                            uint64_t* __restrict__ status, uint32_t* __restrict__ ticket,
                                            uint32_t* __restrict__ counters, uint32_t pair_capacity, uint32_t nb) {
@@ -47,13 +47,13 @@ __device__ __forceinline__ void scan_block(const uint32_t* __restrict__ in, uint
   if (threadIdx.x == 0) s_bid = atomicAdd(ticket, 1u);
   __syncthreads();
   const uint32_t bid = s_bid;
-  // thread t owns kScanItems consecutive items
-  const uint32_t base = bid * (uint32_t)(THREADS * kScanItems) + threadIdx.x * kScanItems;
-  uint32_t v[kScanItems];
-  if (base + kScanItems <= n) {
+  // thread t owns ITEMS consecutive items
+  const uint32_t base = bid * (uint32_t)(THREADS * ITEMS) + threadIdx.x * ITEMS;
+  uint32_t v[ITEMS];
+  if (base + ITEMS <= n) {
     const uint4* in4 = reinterpret_cast<const uint4*>(in + base);  // 64-byte aligned run
 #pragma unroll
-    for (int k = 0; k < kScanItems / 4; ++k) {
+    for (int k = 0; k < ITEMS / 4; ++k) {
       const uint4 q = in4[k];
       v[4 * k] = q.x;
       v[4 * k + 1] = q.y;
@@ -62,11 +62,11 @@ __device__ __forceinline__ void scan_block(const uint32_t* __restrict__ in, uint
     }
   } else {
 #pragma unroll
-    for (int k = 0; k < kScanItems; ++k) v[k] = (base + k < n) ? in[base + k] : 0u;
+    for (int k = 0; k < ITEMS; ++k) v[k] = (base + k < n) ? in[base + k] : 0u;
   }
   uint32_t sum = 0;
 #pragma unroll
-  for (int k = 0; k < kScanItems; ++k) sum += v[k];
+  for (int k = 0; k < ITEMS; ++k) sum += v[k];
   uint32_t total;
   const uint32_t local = block_exclusive_scan<THREADS>(sum, lds, &total);
   if (threadIdx.x < 64) {
@@ -118,10 +118,10 @@ __device__ __forceinline__ void scan_block(const uint32_t* __restrict__ in, uint
   }
   __syncthreads();
   uint32_t run = (uint32_t)s_excl + local;
-  if (base + kScanItems <= n && (reinterpret_cast<uintptr_t>(out) & 15) == 0) {
+  if (base + ITEMS <= n && (reinterpret_cast<uintptr_t>(out) & 15) == 0) {
     uint4* out4 = reinterpret_cast<uint4*>(out + base);
 #pragma unroll
-    for (int k = 0; k < kScanItems / 4; ++k) {
+    for (int k = 0; k < ITEMS / 4; ++k) {
       uint4 q;
       q.x = run;
       run += v[4 * k];
@@ -135,13 +135,13 @@ __device__ __forceinline__ void scan_block(const uint32_t* __restrict__ in, uint
     }
   } else {
 #pragma unroll
-    for (int k = 0; k < kScanItems; ++k) {
+    for (int k = 0; k < ITEMS; ++k) {
       if (base + k < n) out[base + k] = run;
       run += v[k];
     }
   }
   // out[n] = total, written by the thread that owns the end
-  if (base <= n && n < base + kScanItems) out[n] = run;
+  if (base <= n && n < base + ITEMS) out[n] = run;
 }
 
 }  // namespace gsr
