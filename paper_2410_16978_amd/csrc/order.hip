@@ -337,7 +337,7 @@ k_rec_pass(const ViewD* __restrict__ views, int n_views, uint32_t* __restrict__ 
   constexpr uint32_t kTileRec = kRecThreads * kRecItems;
   __shared__ uint32_t s_bid, s_triv;
   __shared__ uint16_t wave_cnt[kRecWaves][256];
-  __shared__ uint32_t s_start[256], s_global[256];
+  __shared__ uint32_t s_global[256];
   __shared__ uint32_t s_w[4], s_hw[4];
   __shared__ uint32_t s_keys[kTileRec], s_vals[kTileRec];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
@@ -416,18 +416,14 @@ k_rec_pass(const ViewD* __restrict__ views, int n_views, uint32_t* __restrict__ 
     rank[r] = pre + (uint32_t)__popcll(front);
   }
   __syncthreads();
-  // thread t < 256 owns digit t: per-wave offsets, the block count, look-back
+  // thread t < 256 owns digit t: the block count, look-back, wave offsets
   uint32_t* st = status + (size_t)views[v].sort_blk * 256;
-  uint32_t cnt = 0, inc = 0;
+  uint32_t cnt = 0, inc = 0, cw[kRecWaves];
   if (t < 256) {
-    uint32_t cw[kRecWaves];
 #pragma unroll
     for (int w = 0; w < kRecWaves; ++w) cw[w] = wave_cnt[w][t];
 #pragma unroll
-    for (int w = 0; w < kRecWaves; ++w) {
-      wave_cnt[w][t] = (uint16_t)cnt;
-      cnt += cw[w];
-    }
+    for (int w = 0; w < kRecWaves; ++w) cnt += cw[w];
     inc = wave_scan_add(cnt);
     if (lane == 63) s_w[wave] = inc;
     __hip_atomic_store(&st[(size_t)lb * 256 + t], (lb == 0 ? kOrdFlagIncl : kOrdFlagAgg) | cnt, __ATOMIC_RELAXED,
@@ -435,19 +431,23 @@ k_rec_pass(const ViewD* __restrict__ views, int n_views, uint32_t* __restrict__ 
   }
   __syncthreads();
   if (t < 256) {
-    uint32_t o = 0, doff = hinc - hc;
+    uint32_t o = inc - cnt, doff = hinc - hc;
     for (int w = 0; w < wave; ++w) {
       o += s_w[w];
       doff += s_hw[w];
     }
-    s_start[t] = o + inc - cnt;
     uint32_t excl = 0;
     if (lb > 0) {
       excl = look_back(st, (int)lb, (uint32_t)t, err);
       __hip_atomic_store(&st[(size_t)lb * 256 + t], kOrdFlagIncl | ((excl + cnt) & kOrdValueMask), __ATOMIC_RELAXED,
                          __HIP_MEMORY_SCOPE_AGENT);
     }
-    s_global[t] = doff + excl;
+    s_global[t] = doff + excl - o;  // of an item at LDS position p: p + s_global
+#pragma unroll
+    for (int w = 0; w < kRecWaves; ++w) {
+      wave_cnt[w][t] = (uint16_t)o;
+      o += cw[w];
+    }
   }
   __syncthreads();
   const uint32_t n_items = s_w[0] + s_w[1] + s_w[2] + s_w[3];
@@ -455,15 +455,14 @@ k_rec_pass(const ViewD* __restrict__ views, int n_views, uint32_t* __restrict__ 
 #pragma unroll
   for (int r = 0; r < kRecItems; ++r)
     if (ok[r]) {
-      const uint32_t d = (key[r] >> shift) & 255u;
-      const uint32_t pos = s_start[d] + wave_cnt[wave][d] + rank[r];
+      const uint32_t pos = wave_cnt[wave][(key[r] >> shift) & 255u] + rank[r];
       s_keys[pos] = key[r];
       s_vals[pos] = val[r];
     }
   __syncthreads();
   for (uint32_t i = t; i < n_items; i += kRecThreads) {
-    const uint32_t k = s_keys[i], d = (k >> shift) & 255u;
-    const uint32_t dst = s_global[d] + (i - s_start[d]);
+    const uint32_t k = s_keys[i];
+    const uint32_t dst = s_global[(k >> shift) & 255u] + i;
     if (dst < K) {
       kout[dst] = k;
       vout[dst] = s_vals[i];
@@ -735,7 +734,7 @@ k_pair_pass(const TT* __restrict__ tin, TT* __restrict__ tout, const uint32_t* _
             uint32_t* __restrict__ sel_out, uint32_t sel, uint32_t* __restrict__ err) {
   constexpr uint32_t D = 1u << BITS, kStep = kPairThreads * kPairItems;
   __shared__ uint16_t wave_cnt[kPairWaves][D];
-  __shared__ uint32_t s_start[D], s_global[D];
+  __shared__ uint32_t s_global[D];
   __shared__ uint32_t s_w[4];
   __shared__ TT s_tile[kStep];
   __shared__ uint32_t s_rec[kStep];
@@ -774,22 +773,19 @@ k_pair_pass(const TT* __restrict__ tin, TT* __restrict__ tout, const uint32_t* _
       for (int w = 0; w < wave; ++w) next += s_w[w];
     }
   }
-  uint32_t til[kPairItems], rec[kPairItems];
+  // a pair's tile, and above it (2-byte tiles) or beside it its rank
+  uint32_t til[kPairItems], rec[kPairItems], rnk[sizeof(TT) == 2 ? 1 : kPairItems];
   const uint32_t wbase = (uint32_t)wave * (kPairItems * 64) + (uint32_t)lane;
-  auto load = [&](uint32_t base) {
+  for (uint32_t base = begin; base < end; base += kStep) {
 #pragma unroll
     for (int r = 0; r < kPairItems; ++r) {
       const uint32_t i = min(base + wbase + r * 64, end - 1u);  // (branch-free)
       til[r] = (uint32_t)tin[i];
       rec[r] = rin[i];
     }
-  };
-  load(begin);
-  for (uint32_t base = begin; base < end; base += kStep) {
     for (int i = t; i < (int)(kPairWaves * D / 2); i += kPairThreads)
       reinterpret_cast<uint32_t*>(&wave_cnt[0][0])[i] = 0;
     __syncthreads();  // (and the previous step's LDS is read)
-    uint32_t rank[kPairItems];
 #pragma unroll
     for (int r = 0; r < kPairItems; ++r) {
       const bool ok = base + wbase + r * 64 < end;
@@ -801,20 +797,19 @@ k_pair_pass(const TT* __restrict__ tin, TT* __restrict__ tout, const uint32_t* _
       __builtin_amdgcn_wave_barrier();
       if (ok && front == 0) wave_cnt[wave][d] = (uint16_t)(pre + (uint32_t)__popcll(peers));
       __builtin_amdgcn_wave_barrier();
-      rank[r] = pre + (uint32_t)__popcll(front);
+      const uint32_t rank = pre + (uint32_t)__popcll(front);
+      if constexpr (sizeof(TT) == 2) til[r] |= rank << 16;
+      else rnk[r] = rank;
     }
     __syncthreads();
-    uint32_t cnt = 0, inc = 0;
+    // thread t < D: digit t's place in the block, wave by wave
+    uint32_t cw[kPairWaves], cnt = 0, inc = 0;
     if (t < 256) {
       if (t < (int)D) {
-        uint32_t cw[kPairWaves];
 #pragma unroll
         for (int w = 0; w < kPairWaves; ++w) cw[w] = wave_cnt[w][t];
 #pragma unroll
-        for (int w = 0; w < kPairWaves; ++w) {
-          wave_cnt[w][t] = (uint16_t)cnt;
-          cnt += cw[w];
-        }
+        for (int w = 0; w < kPairWaves; ++w) cnt += cw[w];
       }
       inc = wave_scan_add(cnt);
       if (lane == 63) s_w[wave] = inc;
@@ -823,20 +818,24 @@ k_pair_pass(const TT* __restrict__ tin, TT* __restrict__ tout, const uint32_t* _
     if (t < (int)D) {
       uint32_t o = inc - cnt;
       for (int w = 0; w < wave; ++w) o += s_w[w];
-      s_start[t] = o;
       s_global[t] = next - o;  // of an item at LDS position p: p + s_global
       next += cnt;
+#pragma unroll
+      for (int w = 0; w < kPairWaves; ++w) {
+        wave_cnt[w][t] = (uint16_t)o;
+        o += cw[w];
+      }
     }
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < kPairItems; ++r)
       if (base + wbase + r * 64 < end) {
-        const uint32_t d = (til[r] >> shift) & mask;
-        const uint32_t pos = s_start[d] + wave_cnt[wave][d] + rank[r];
-        s_tile[pos] = (TT)til[r];
+        const uint32_t tile = sizeof(TT) == 2 ? til[r] & 0xFFFFu : til[r];
+        const uint32_t rank = sizeof(TT) == 2 ? til[r] >> 16 : rnk[sizeof(TT) == 2 ? 0 : r];
+        const uint32_t pos = wave_cnt[wave][(tile >> shift) & mask] + rank;
+        s_tile[pos] = (TT)tile;
         s_rec[pos] = rec[r];
       }
-    if (base + kStep < end) load(base + kStep);  // in flight during the write-out
     __syncthreads();
     const uint32_t n_items = min(end - base, kStep);
     for (uint32_t i = t; i < n_items; i += kPairThreads) {
@@ -852,42 +851,58 @@ k_pair_pass(const TT* __restrict__ tin, TT* __restrict__ tout, const uint32_t* _
   }
 }
 
-// The tiles' runs in the grouped pairs (ranges zero on entry): a thread
-// takes eight pairs and writes the run ends it sees.
+// The tiles' runs in the grouped pairs (ranges zero on entry).  A block takes
+// a contiguous share; a thread takes 16 bytes of tiles at a time, four such
+// loads in flight, and writes the run ends it sees - none where the last
+// pair's tile is that of the pair before the first, the tiles ascending.
 template <typename TT>
 __global__ void __launch_bounds__(256)
 k_tile_runs(const TT* __restrict__ tiles, uint32_t* __restrict__ counters, uint32_t cap, uint32_t n_tiles,
             uint32_t* __restrict__ ranges) {
-  constexpr uint32_t kItems = 8;
+  constexpr uint32_t kItems = 16 / sizeof(TT), kAhead = 4, kRow = 256 * kItems;
   const uint32_t K = min(counters[kCntPairs], cap);
-  for (uint64_t k0 = ((uint64_t)blockIdx.x * 256u + threadIdx.x) * kItems; k0 < K;
-       k0 += (uint64_t)gridDim.x * 256u * kItems) {
-    TT q[kItems];
-    if (k0 + kItems <= K) {
-      if constexpr (sizeof(TT) == 2) {
-        *reinterpret_cast<uint4*>(q) = *reinterpret_cast<const uint4*>(tiles + k0);
-      } else {
-        reinterpret_cast<uint4*>(q)[0] = reinterpret_cast<const uint4*>(tiles + k0)[0];
-        reinterpret_cast<uint4*>(q)[1] = reinterpret_cast<const uint4*>(tiles + k0)[1];
-      }
-    } else {
+  const uint64_t share = ((uint64_t)div_up(K, gridDim.x) + kRow * kAhead - 1) / (kRow * kAhead) * (kRow * kAhead);
+  const uint64_t begin = blockIdx.x * share, end = min((uint64_t)K, begin + share);
+  auto boundary = [&](uint32_t prev, uint32_t tile, uint32_t k) {
+    if (tile < n_tiles) ranges[2 * (size_t)tile] = k;
+    else atomicOr(&counters[kCntError], 4u);
+    if (prev < n_tiles) ranges[2 * (size_t)prev + 1] = k;
+  };
+  auto item = [](const uint4& q, uint32_t u) -> uint32_t {
+    const uint32_t w = sizeof(TT) == 2 ? (u >> 1) : u;
+    const uint32_t x = w == 0 ? q.x : w == 1 ? q.y : w == 2 ? q.z : q.w;
+    return sizeof(TT) == 2 ? (x >> (16 * (u & 1))) & 0xFFFFu : x;
+  };
+  uint64_t base = begin;
+  for (; base + kRow * kAhead <= end; base += kRow * kAhead) {
+    uint4 q[kAhead];
+    uint32_t prev[kAhead];
 #pragma unroll
-      for (uint32_t u = 0; u < kItems; ++u) q[u] = tiles[min(k0 + u, (uint64_t)K - 1)];
+    for (uint32_t u = 0; u < kAhead; ++u) {
+      const uint64_t k0 = base + u * kRow + threadIdx.x * kItems;
+      q[u] = *reinterpret_cast<const uint4*>(tiles + k0);
+      prev[u] = k0 ? (uint32_t)tiles[k0 - 1] : 0xFFFFFFFFu;
     }
-    uint32_t prev = k0 ? (uint32_t)tiles[k0 - 1] : 0xFFFFFFFFu;
 #pragma unroll
-    for (uint32_t u = 0; u < kItems; ++u) {
-      const uint32_t k = (uint32_t)k0 + u;
-      if (k >= K) break;
-      const uint32_t tl = (uint32_t)q[u];
-      if (tl != prev) {
-        if (tl < n_tiles) ranges[2 * (size_t)tl] = k;
-        else atomicOr(&counters[kCntError], 4u);
-        if (prev < n_tiles) ranges[2 * (size_t)prev + 1] = k;
+    for (uint32_t u = 0; u < kAhead; ++u) {
+      if (item(q[u], kItems - 1) == prev[u]) continue;
+      const uint32_t k0 = (uint32_t)(base + u * kRow + threadIdx.x * kItems);
+      uint32_t p = prev[u];
+#pragma unroll
+      for (uint32_t x = 0; x < kItems; ++x) {
+        const uint32_t tile = item(q[u], x);
+        if (tile != p) boundary(p, tile, k0 + x);
+        p = tile;
       }
-      prev = tl;
-      if (k + 1 == K && tl < n_tiles) ranges[2 * (size_t)tl + 1] = K;
     }
+  }
+  for (uint64_t k = base + threadIdx.x; k < end; k += 256) {
+    const uint32_t tile = tiles[k], p = k ? (uint32_t)tiles[k - 1] : 0xFFFFFFFFu;
+    if (tile != p) boundary(p, tile, (uint32_t)k);
+  }
+  if (end == K && begin < end && threadIdx.x == 0) {  // the last run's end
+    const uint32_t tile = tiles[K - 1];
+    if (tile < n_tiles) ranges[2 * (size_t)tile + 1] = K;
   }
 }
 
@@ -924,7 +939,7 @@ hipError_t order_pairs(const OrderBufs& o, hipStream_t s) {
   for (int p = 0; p < np; ++p)
     pass(bits, g, tiles[p & 1], tiles[(p + 1) & 1], recs[p & 1], recs[(p + 1) & 1], o, p * bits,
                   p == np - 1 ? o.sel : nullptr, (uint32_t)(np & 1), s);
-  const uint32_t rg = std::min(div_up(o.cap, 256u * 8u), 8192u);
+  const uint32_t rg = std::min(div_up(o.cap, 256u * 8u * 4u), 2048u);
   hipLaunchKernelGGL(k_tile_runs<TT>, dim3(std::max(rg, 1u)), dim3(256), 0, s, tiles[np & 1], o.counters, o.cap,
                      o.n_tiles, o.ranges);
   return hipGetLastError();
