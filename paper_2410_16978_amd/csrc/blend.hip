@@ -665,7 +665,9 @@ hipError_t launch_batch_order(const uint32_t* batch_tile, uint32_t n_batches, ui
   return hipGetLastError();
 }
 
-__global__ void __launch_bounds__(256)
+// Six waves a SIMD (77 registers): five (83) took 1553 us on the 4M step
+// against 1449, seven spill.
+__global__ void __launch_bounds__(256, 6)
 k_blend_bwd(const ViewD* __restrict__ views, int n_views, const float* __restrict__ records, uint32_t n_rec,
             const uint32_t* __restrict__ pair_vals, const uint32_t* __restrict__ sel, uint32_t cap,
             const uint32_t* __restrict__ ranges, const float4* __restrict__ ckpt,
@@ -682,269 +684,273 @@ k_blend_bwd(const ViewD* __restrict__ views, int n_views, const float* __restric
   __shared__ float part[4][kGradSlots][kSubPad];
   __shared__ uint16_t s_blk[kBatch];  // block masks the forward left
   __shared__ uint32_t s_emit[kBatch], s_gauss[kBatch];  // where pair j's partial goes, its Gaussian
-  // block b takes the b-th batch of the heaviest-first order: the first wave
-  // scans the class counts and finds b's class
+  // Items are the batches the forward evaluated at a live pixel, heaviest
+  // first (the last class's batches - its pixels had stopped, or no pair's
+  // ellipse reaches one - have only zero partials: none is written, their
+  // alive flags stay 0).  Block b takes item b and every gridDim-th after it;
+  // the first wave scans the class counts and finds the item's class.
   __shared__ uint32_t s_bi;
-  if (threadIdx.x < 64) {
-    const uint32_t k = threadIdx.x;
-    const uint32_t cnt = k < kBatchClasses ? min(order_cnt[k], n_batches) : 0u;
-    const uint32_t inc = wave_scan_add(cnt);
-    const uint32_t b = blockIdx.x;
-    const bool here = k < kBatchClasses && b >= inc - cnt && b < inc;
-    if (here) s_bi = order_list[(size_t)k * n_batches + (b - (inc - cnt))];
-    if (__ballot(here) == 0ull && threadIdx.x == 0) s_bi = 0xFFFFFFFFu;
-  }
-  __syncthreads();
-  const uint32_t bi = s_bi;
-  if (bi >= n_batches) return;
-  const uint32_t word = batch_tile[bi];
-  const uint32_t tile_p1 = word & kBatchTileMask;
-  if (tile_p1 == 0) return;  // no tile's batch
-  const uint32_t tile = tile_p1 - 1u;
-  const uint32_t c = bi - first_batch(tile, ranges[2 * tile]);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const uint32_t t_end = min(ranges[2 * tile + 1], cap);
-  const uint32_t start = min(ranges[2 * tile] + c * kBatch, t_end);
-  const uint32_t end = min(start + kBatch, t_end);
-  const int n = (int)(end - start);
-  // The forward evaluated none of this batch's pairs at a live pixel (its
-  // pixels had stopped, or no pair's ellipse reaches one): every partial is
-  // zero, and none is written (their alive flags stay 0).
-  if ((word >> 24) == 0u) return;
-  const int vi = find_view(views, n_views, tile);
-  const ViewD& V = views[vi];
-  const uint32_t* vals = pair_vals + (*sel ? cap : 0u);
-
-  const uint32_t local = tile - V.tile_off;
-  const int tx = (int)(local % (uint32_t)V.tiles_x), ty = (int)(local / (uint32_t)V.tiles_x);
-  int px, py;
-  pixel_of(tid, tx, ty, px, py);
-  const bool inside = px < V.W && py < V.H;
-  const float fx = (float)px + 0.5f, fy = (float)py + 0.5f;
-  const size_t plane = (size_t)V.W * V.H;
-  const size_t pix = inside ? (size_t)py * V.W + px : 0;
-  const size_t vpix = (size_t)vi * plane;  // views of one call share a resolution
-  // lim: this pixel's pairs j < lim lie in front of its last blended pair
-  int lim = 0;
-  // With S the colour behind the current pair and T the transmittance behind
-  // it, dL/dalpha = Tb (G . c) - P / (1 - alpha) where P = sum_ch G_ch S_ch -
-  // GA Tfin.  The kernel carries Q = P / T instead: then dL/dalpha =
-  // Tb (G . c - Q) and, per blended pair, Q <- Q + alpha (G . c - Q), a convex
-  // combination of the pairs' G . c behind (and G . bg - GA), so Q keeps a
-  // relative error of a few roundings however deep the pixel, and only the
-  // factor Tb carries the transmittance rebuilt by division.  That division
-  // runs in double: in float each of up to 256 steps back from the batch end
-  // would add a rounding, several times the error a float forward leaves in
-  // T, which near-cancelling per-pixel terms turn into gradient error.
-  double T = 1.0;
-  float Tfin = 1.f, Q = 0.f, G0 = 0.f, G1 = 0.f, G2 = 0.f, GA = 0.f;
-  if (inside) {
-    const uint32_t plast = V.last[pix];
-    if (plast > start) {
-      lim = (int)min(plast - start, (uint32_t)n);
-      const float4 ps = reinterpret_cast<const float4*>(V.pix)[pix];
-      Tfin = ps.x;
-      // batch of the pixel's last blended pair (>= c)
-      const uint32_t tile_start = ranges[2 * tile];
-      const uint32_t c_last = (plast - 1 - tile_start) / kBatch;
-      const float4* tck = ckpt + (size_t)(bi - c) * kBatch + tid;
-      // transmittance at the end of this batch, colour behind it
-      T = (c_last == c) ? Tfin : tck[(size_t)(c + 1) * kBatch].x;
-      const float4 sb = tck[(size_t)c * kBatch];
-      if (dL_drgb) {
-        G0 = dL_drgb[3 * vpix + pix];
-        G1 = dL_drgb[3 * vpix + plane + pix];
-        G2 = dL_drgb[3 * vpix + 2 * plane + pix];
-      }
-      if (dL_dalpha) GA = dL_dalpha[vpix + pix];
-      Q = __fdiv_rn(fmaf(G2, sb.w, fmaf(G1, sb.z, fmaf(G0, sb.y, -GA * Tfin))), (float)T);
+  for (uint32_t b = blockIdx.x;; b += gridDim.x) {
+    __syncthreads();  // the previous item's LDS is read
+    if (threadIdx.x < 64) {
+      const uint32_t k = threadIdx.x;
+      const uint32_t cnt = k < kBatchClasses - 1 ? min(order_cnt[k], n_batches) : 0u;
+      const uint32_t inc = wave_scan_add(cnt);
+      const bool here = b >= inc - cnt && b < inc;
+      if (here) s_bi = order_list[(size_t)k * n_batches + (b - (inc - cnt))];
+      if (__ballot(here) == 0ull && threadIdx.x == 0) s_bi = 0xFFFFFFFFu;
     }
-  }
-  // thread t stages pair t and later combines its sums (sub-batch t / kSub
-  // runs on wave t / kSub)
-  const uint32_t my_rec = tid < n ? vals[start + tid] : n_rec;
-  put(L, fetch_record(records, n_rec, my_rec, tid < n), tid < n, tid);
-  {
-    const uint8_t* blk = reinterpret_cast<const uint8_t*>(pair_vals + (*sel ? 0u : cap)) + start + tid;
-    s_blk[tid] = tid < n ? (uint16_t)(blk[0] | (blk[cap] << 4) | (blk[2 * (size_t)cap] << 8) | (blk[3 * (size_t)cap] << 12))
-                         : (uint16_t)0;
-  }
-  // emission index of the pair, where its partial goes: as the per-tile sort
-  // left it, or (order-first) the record's first one plus the tile's place in
-  // its box.  One at or beyond the capacity is not written.
-  {
-    uint32_t emit = cap;
-    if (tid < n) {
-      if (!boxes) {
-        emit = pair_emit[start + tid];
-      } else if (my_rec < n_rec) {
-        const uint2 bx = boxes[my_rec];
-        emit = offsets[my_rec] + ((uint32_t)ty - (bx.x >> 16)) * (bx.y & 0xFFFFu) + ((uint32_t)tx - (bx.x & 0xFFFFu));
+    __syncthreads();
+    const uint32_t bi = s_bi;
+    if (bi >= n_batches) return;
+    const uint32_t tile_p1 = batch_tile[bi] & kBatchTileMask;
+    if (tile_p1 == 0) continue;  // no tile's batch
+    const uint32_t tile = tile_p1 - 1u;
+    const uint32_t c = bi - first_batch(tile, ranges[2 * tile]);
+    // (the thread index is taken afresh: what derives from it is then not kept
+    // across the items in registers the walk needs)
+    int tid = (int)threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t t_end = min(ranges[2 * tile + 1], cap);
+    const uint32_t start = min(ranges[2 * tile] + c * kBatch, t_end);
+    const uint32_t end = min(start + kBatch, t_end);
+    const int n = (int)(end - start);
+    const int vi = find_view(views, n_views, tile);
+    const ViewD& V = views[vi];
+    const uint32_t* vals = pair_vals + (*sel ? cap : 0u);
+
+    const uint32_t local = tile - V.tile_off;
+    const int tx = (int)(local % (uint32_t)V.tiles_x), ty = (int)(local / (uint32_t)V.tiles_x);
+    int px, py;
+    pixel_of(tid, tx, ty, px, py);
+    const bool inside = px < V.W && py < V.H;
+    const float fx = (float)px + 0.5f, fy = (float)py + 0.5f;
+    const size_t plane = (size_t)V.W * V.H;
+    const size_t pix = inside ? (size_t)py * V.W + px : 0;
+    const size_t vpix = (size_t)vi * plane;  // views of one call share a resolution
+    // lim: this pixel's pairs j < lim lie in front of its last blended pair
+    int lim = 0;
+    // With S the colour behind the current pair and T the transmittance behind
+    // it, dL/dalpha = Tb (G . c) - P / (1 - alpha) where P = sum_ch G_ch S_ch -
+    // GA Tfin.  The kernel carries Q = P / T instead: then dL/dalpha =
+    // Tb (G . c - Q) and, per blended pair, Q <- Q + alpha (G . c - Q), a convex
+    // combination of the pairs' G . c behind (and G . bg - GA), so Q keeps a
+    // relative error of a few roundings however deep the pixel, and only the
+    // factor Tb carries the transmittance rebuilt by division.  That division
+    // runs in double: in float each of up to 256 steps back from the batch end
+    // would add a rounding, several times the error a float forward leaves in
+    // T, which near-cancelling per-pixel terms turn into gradient error.
+    double T = 1.0;
+    float Tfin = 1.f, Q = 0.f, G0 = 0.f, G1 = 0.f, G2 = 0.f, GA = 0.f;
+    if (inside) {
+      const uint32_t plast = V.last[pix];
+      if (plast > start) {
+        lim = (int)min(plast - start, (uint32_t)n);
+        const float4 ps = reinterpret_cast<const float4*>(V.pix)[pix];
+        Tfin = ps.x;
+        // batch of the pixel's last blended pair (>= c)
+        const uint32_t tile_start = ranges[2 * tile];
+        const uint32_t c_last = (plast - 1 - tile_start) / kBatch;
+        const float4* tck = ckpt + (size_t)(bi - c) * kBatch + tid;
+        // transmittance at the end of this batch, colour behind it
+        T = (c_last == c) ? Tfin : tck[(size_t)(c + 1) * kBatch].x;
+        const float4 sb = tck[(size_t)c * kBatch];
+        if (dL_drgb) {
+          G0 = dL_drgb[3 * vpix + pix];
+          G1 = dL_drgb[3 * vpix + plane + pix];
+          G2 = dL_drgb[3 * vpix + 2 * plane + pix];
+        }
+        if (dL_dalpha) GA = dL_dalpha[vpix + pix];
+        Q = __fdiv_rn(fmaf(G2, sb.w, fmaf(G1, sb.z, fmaf(G0, sb.y, -GA * Tfin))), (float)T);
       }
     }
-    s_emit[tid] = emit;
-    s_gauss[tid] = my_rec < n_rec ? my_rec - V.rec_off : 0xFFFFFFFFu;
-  }
-  for (int i = tid; i < 4 * kGradSlots * kSubPad; i += 256) (&part[0][0][0])[i] = 0.f;
-  // the wave's 8 x 8 quadrant: 2 x 2 of the tile's 4 x 4 blocks, its upper
-  // half (lanes 0-31) in one band of the forward, its lower in the next
-  const uint32_t qmask = 3u << (2 * (wave & 1) + 8 * (wave >> 1));
-  // the halves' reach: no pair at or behind their pixels' last blended pair
-  // counts (nor was a band's mask written once all its pixels had stopped)
-  int n_up = lim;
+    // thread t stages pair t and later combines its sums (sub-batch t / kSub
+    // runs on wave t / kSub)
+    const uint32_t my_rec = tid < n ? vals[start + tid] : n_rec;
+    put(L, fetch_record(records, n_rec, my_rec, tid < n), tid < n, tid);
+    {
+      const uint8_t* blk = reinterpret_cast<const uint8_t*>(pair_vals + (*sel ? 0u : cap)) + start + tid;
+      s_blk[tid] = tid < n ? (uint16_t)(blk[0] | (blk[cap] << 4) | (blk[2 * (size_t)cap] << 8) | (blk[3 * (size_t)cap] << 12))
+                           : (uint16_t)0;
+    }
+    // emission index of the pair, where its partial goes: as the per-tile sort
+    // left it, or (order-first) the record's first one plus the tile's place in
+    // its box.  One at or beyond the capacity is not written.
+    {
+      uint32_t emit = cap;
+      if (tid < n) {
+        if (!boxes) {
+          emit = pair_emit[start + tid];
+        } else if (my_rec < n_rec) {
+          const uint2 bx = boxes[my_rec];
+          emit = offsets[my_rec] + ((uint32_t)ty - (bx.x >> 16)) * (bx.y & 0xFFFFu) + ((uint32_t)tx - (bx.x & 0xFFFFu));
+        }
+      }
+      s_emit[tid] = emit;
+      s_gauss[tid] = my_rec < n_rec ? my_rec - V.rec_off : 0xFFFFFFFFu;
+    }
+    for (int i = tid; i < 4 * kGradSlots * kSubPad; i += 256) (&part[0][0][0])[i] = 0.f;
+    // the wave's 8 x 8 quadrant: 2 x 2 of the tile's 4 x 4 blocks, its upper
+    // half (lanes 0-31) in one band of the forward, its lower in the next
+    const uint32_t qmask = 3u << (2 * (wave & 1) + 8 * (wave >> 1));
+    // the halves' reach: no pair at or behind their pixels' last blended pair
+    // counts (nor was a band's mask written once all its pixels had stopped)
+    int n_up = lim;
 #pragma unroll
-  for (int off = 16; off > 0; off >>= 1) n_up = max(n_up, __shfl_xor(n_up, off, 64));
-  const int n_low = __builtin_amdgcn_readlane(n_up, 32);
-  n_up = __builtin_amdgcn_readfirstlane(n_up);
-  __syncthreads();
+    for (int off = 16; off > 0; off >>= 1) n_up = max(n_up, __shfl_xor(n_up, off, 64));
+    const int n_low = __builtin_amdgcn_readlane(n_up, 32);
+    n_up = __builtin_amdgcn_readfirstlane(n_up);
+    __syncthreads();
 
-  // back to front in sub-batches of kSub pairs; after each, the four wave
-  // partials of its pairs are summed in a fixed order and written out
-  const int n_sub = (n + kSub - 1) / kSub;
-  // where the 18-value reduce-scatter leaves each sum: rows 0-1 hold the back
-  // pair of a step, rows 2-3 the front one; lane bits 3, 2 and the row's
-  // parity pick one of the first eight sums, lane bit 1 the ninth
-  const int row = lane >> 4;
-  const int q_lane = (lane & 2) ? 8 : 2 * (((lane >> 2) & 1) * 2 + ((lane >> 3) & 1)) + (row & 1);
-  const bool writer = !(lane & 1) && (!(lane & 2) || ((lane & 12) == 0 && !(row & 1)));
-  const bool front = row >= 2;
-  float* part_lane = &part[wave][q_lane][0];
-  struct PairLds {
-    float4 A, B;
-    float c;
-  };
-  auto load = [&](int j) -> PairLds { return PairLds{L.a[j], L.b[j], L.c[j]}; };
-  // one pair for this pixel: updates T and Q (back to front) and returns the
-  // nine per-pixel terms; inactive pairs give zeros
-  auto eval = [&](const PairLds& P, int j, bool valid, float (&v)[9], float& w) -> bool {
-    // branch-free: every lane evaluates the pair, selects keep what counts
-    const float4 A = P.A, B = P.B;
-    const float dx = A.x - fx, dy = A.y - fy;
-    const float power = pair_power(A, B, dx, dy);
-    const float G = pair_gauss(power);
-    const float oG = B.y * G;
-    const float alpha = fminf(kAlphaMax, oG);
-    const bool contrib = valid && j < lim && power <= 0.f && alpha >= kAlphaMin;
-    const bool has_grad = contrib && !(oG > kAlphaMax);  // alpha not clamped: it has a gradient
-    // ae is alpha where the pair blends and 0 elsewhere: with it the colour
-    // weight, the Q step and the transmittance need no further selects
-    const float ae = contrib ? alpha : 0.f;
-    // transmittance in front of this pair: T / (1 - alpha), alpha <= 0.99,
-    // the reciprocal refined by one Newton step (a few units of 2^-53)
-    const double om = 1.0 - (double)ae;
-    double inv1m = __builtin_amdgcn_rcp(om);
-    inv1m = fma(inv1m, fma(-om, inv1m, 1.0), inv1m);
-    const double Tbd = T * inv1m;
-    const float Tb = (float)Tbd;
-    const float gcol = fmaf(G2, P.c, fmaf(G1, B.w, G0 * B.z));  // G . c
-    const float dq = gcol - Q;
-    w = ae * Tb;
-    Q = fmaf(ae, dq, Q);
-    T = contrib ? Tbd : T;
-    const float h = (Tb * dq) * (has_grad ? oG : 0.f);  // dL/dalpha o G
-    const float hx = h * dx, hy = h * dy;
-    v[0] = hx;
-    v[1] = hy;
-    v[2] = hx * dx;
-    v[3] = hx * dy;
-    v[4] = hy * dy;
-    v[5] = h;
-    v[6] = G0 * w;
-    v[7] = G1 * w;
-    v[8] = G2 * w;
-    return contrib;
-  };
-  // highest pair of a wave-uniform bit set, removed from it
-  auto pop = [](uint64_t& m) -> int {
-    const int b = 63 - (int)__builtin_clzll(m);
-    m &= ~(1ull << b);
-    return b;
-  };
-  for (int sb = n_sub - 1; sb >= 0; --sb) {
-    const int j0 = sb * kSub;
-    // the wave's pairs of this sub-batch: lane l tests pair j0 + l, a ballot
-    // gives the set of those that can reach alpha >= 1/255 at a pixel centre
-    // of its quadrant in front of its pixels' last blended pair
-    const int jl = j0 + lane;
-    const uint32_t reach = s_blk[jl];
-    uint64_t m = ballot((jl < n_up && (reach & qmask) != 0u) || (jl < n_low && (reach & (qmask << 4)) != 0u));
-    // two pairs per step (the second, in front, may be absent)
-    while (m != 0ull) {
-      const int ja = pop(m);
-      const bool hb = m != 0ull;
-      const int jb = hb ? pop(m) : ja;
-      const PairLds pa = load(j0 + ja), pb = load(j0 + jb);
-      float va[9], vb[9], wa, wb;
-      const bool ca = eval(pa, j0 + ja, true, va, wa);
-      const bool cb = eval(pb, j0 + jb, hb, vb, wb);
-      if (ballot(ca || cb) != 0ull) {
-        // reduce-scatter: halves (back | front pair), then row pairs, then
-        // within rows by mirror exchanges that keep one operand per lane half
-        float X[9];
+    // back to front in sub-batches of kSub pairs; after each, the four wave
+    // partials of its pairs are summed in a fixed order and written out
+    const int n_sub = (n + kSub - 1) / kSub;
+    // where the 18-value reduce-scatter leaves each sum: rows 0-1 hold the back
+    // pair of a step, rows 2-3 the front one; lane bits 3, 2 and the row's
+    // parity pick one of the first eight sums, lane bit 1 the ninth
+    const int row = lane >> 4;
+    const int q_lane = (lane & 2) ? 8 : 2 * (((lane >> 2) & 1) * 2 + ((lane >> 3) & 1)) + (row & 1);
+    const bool writer = !(lane & 1) && (!(lane & 2) || ((lane & 12) == 0 && !(row & 1)));
+    const bool front = row >= 2;
+    float* part_lane = &part[wave][q_lane][0];
+    struct PairLds {
+      float4 A, B;
+      float c;
+    };
+    auto load = [&](int j) -> PairLds { return PairLds{L.a[j], L.b[j], L.c[j]}; };
+    // one pair for this pixel: updates T and Q (back to front) and returns the
+    // nine per-pixel terms; inactive pairs give zeros
+    auto eval = [&](const PairLds& P, int j, bool valid, float (&v)[9], float& w) -> bool {
+      // branch-free: every lane evaluates the pair, selects keep what counts
+      const float4 A = P.A, B = P.B;
+      const float dx = A.x - fx, dy = A.y - fy;
+      const float power = pair_power(A, B, dx, dy);
+      const float G = pair_gauss(power);
+      const float oG = B.y * G;
+      const float alpha = fminf(kAlphaMax, oG);
+      const bool contrib = valid && j < lim && power <= 0.f && alpha >= kAlphaMin;
+      const bool has_grad = contrib && !(oG > kAlphaMax);  // alpha not clamped: it has a gradient
+      // ae is alpha where the pair blends and 0 elsewhere: with it the colour
+      // weight, the Q step and the transmittance need no further selects
+      const float ae = contrib ? alpha : 0.f;
+      // transmittance in front of this pair: T / (1 - alpha), alpha <= 0.99,
+      // the reciprocal refined by one Newton step (a few units of 2^-53)
+      const double om = 1.0 - (double)ae;
+      double inv1m = __builtin_amdgcn_rcp(om);
+      inv1m = fma(inv1m, fma(-om, inv1m, 1.0), inv1m);
+      const double Tbd = T * inv1m;
+      const float Tb = (float)Tbd;
+      const float gcol = fmaf(G2, P.c, fmaf(G1, B.w, G0 * B.z));  // G . c
+      const float dq = gcol - Q;
+      w = ae * Tb;
+      Q = fmaf(ae, dq, Q);
+      T = contrib ? Tbd : T;
+      const float h = (Tb * dq) * (has_grad ? oG : 0.f);  // dL/dalpha o G
+      const float hx = h * dx, hy = h * dy;
+      v[0] = hx;
+      v[1] = hy;
+      v[2] = hx * dx;
+      v[3] = hx * dy;
+      v[4] = hy * dy;
+      v[5] = h;
+      v[6] = G0 * w;
+      v[7] = G1 * w;
+      v[8] = G2 * w;
+      return contrib;
+    };
+    // highest pair of a wave-uniform bit set, removed from it
+    auto pop = [](uint64_t& m) -> int {
+      const int b = 63 - (int)__builtin_clzll(m);
+      m &= ~(1ull << b);
+      return b;
+    };
+    for (int sb = n_sub - 1; sb >= 0; --sb) {
+      const int j0 = sb * kSub;
+      // the wave's pairs of this sub-batch: lane l tests pair j0 + l, a ballot
+      // gives the set of those that can reach alpha >= 1/255 at a pixel centre
+      // of its quadrant in front of its pixels' last blended pair
+      const int jl = j0 + lane;
+      const uint32_t reach = s_blk[jl];
+      uint64_t m = ballot((jl < n_up && (reach & qmask) != 0u) || (jl < n_low && (reach & (qmask << 4)) != 0u));
+      // two pairs per step (the second, in front, may be absent)
+      while (m != 0ull) {
+        const int ja = pop(m);
+        const bool hb = m != 0ull;
+        const int jb = hb ? pop(m) : ja;
+        const PairLds pa = load(j0 + ja), pb = load(j0 + jb);
+        float va[9], vb[9], wa, wb;
+        const bool ca = eval(pa, j0 + ja, true, va, wa);
+        const bool cb = eval(pb, j0 + jb, hb, vb, wb);
+        if (ballot(ca || cb) != 0ull) {
+          // reduce-scatter: halves (back | front pair), then row pairs, then
+          // within rows by mirror exchanges that keep one operand per lane half
+          float X[9];
 #pragma unroll
-        for (int q = 0; q < 9; ++q) X[q] = swap32_add(va[q], vb[q]);
-        const float Y0 = swap16_add(X[0], X[1]), Y1 = swap16_add(X[2], X[3]);
-        const float Y2 = swap16_add(X[4], X[5]), Y3 = swap16_add(X[6], X[7]);
-        const float Y4 = swap16_add(X[8], X[8]);
-        const bool b3 = lane & 8, b2 = lane & 4, b1 = lane & 2;
-        const float Z0 = (b3 ? Y1 : Y0) + dpp<0x140, 0xF>(b3 ? Y0 : Y1);  // row_mirror
-        const float Z1 = (b3 ? Y3 : Y2) + dpp<0x140, 0xF>(b3 ? Y2 : Y3);
-        const float Z2 = Y4 + dpp<0x140, 0xF>(Y4);
-        const float W0 = (b2 ? Z1 : Z0) + dpp<0x141, 0xF>(b2 ? Z0 : Z1);  // row_half_mirror
-        const float W1 = Z2 + dpp<0x141, 0xF>(Z2);
-        float R = (b1 ? W1 : W0) + dpp<0x4E, 0xF>(b1 ? W0 : W1);  // quad_perm [2,3,0,1]
-        R += qperm<0xB1>(R);                                        // quad_perm [1,0,3,2]
-        if (writer && (!front || hb)) part_lane[front ? jb : ja] = R;
-        if (g_max) {
-          const float mxa = wave_max63(wa);
-          const float mxb = wave_max63(wb);
-          if (lane == 63) {
-            part[wave][9][ja] = mxa;
-            if (hb) part[wave][9][jb] = mxb;
+          for (int q = 0; q < 9; ++q) X[q] = swap32_add(va[q], vb[q]);
+          const float Y0 = swap16_add(X[0], X[1]), Y1 = swap16_add(X[2], X[3]);
+          const float Y2 = swap16_add(X[4], X[5]), Y3 = swap16_add(X[6], X[7]);
+          const float Y4 = swap16_add(X[8], X[8]);
+          const bool b3 = lane & 8, b2 = lane & 4, b1 = lane & 2;
+          const float Z0 = (b3 ? Y1 : Y0) + dpp<0x140, 0xF>(b3 ? Y0 : Y1);  // row_mirror
+          const float Z1 = (b3 ? Y3 : Y2) + dpp<0x140, 0xF>(b3 ? Y2 : Y3);
+          const float Z2 = Y4 + dpp<0x140, 0xF>(Y4);
+          const float W0 = (b2 ? Z1 : Z0) + dpp<0x141, 0xF>(b2 ? Z0 : Z1);  // row_half_mirror
+          const float W1 = Z2 + dpp<0x141, 0xF>(Z2);
+          float R = (b1 ? W1 : W0) + dpp<0x4E, 0xF>(b1 ? W0 : W1);  // quad_perm [2,3,0,1]
+          R += qperm<0xB1>(R);                                        // quad_perm [1,0,3,2]
+          if (writer && (!front || hb)) part_lane[front ? jb : ja] = R;
+          if (g_max) {
+            const float mxa = wave_max63(wa);
+            const float mxb = wave_max63(wb);
+            if (lane == 63) {
+              part[wave][9][ja] = mxa;
+              if (hb) part[wave][9][jb] = mxb;
+            }
           }
         }
       }
-    }
-    __syncthreads();
-    // each column is combined by one thread, which also zeroes it for the
-    // next sub-batch (columns of no pair were never written and stay zero)
-    if (tid >= j0 && tid < j0 + kSub && tid < n) {
-      const int js = tid - j0;
-      float m9[9], o[12];
+      __syncthreads();
+      // each column is combined by one thread, which also zeroes it for the
+      // next sub-batch (columns of no pair were never written and stay zero)
+      if (tid >= j0 && tid < j0 + kSub && tid < n) {
+        const int js = tid - j0;
+        float m9[9], o[12];
 #pragma unroll
-      for (int q = 0; q < 9; ++q) m9[q] = ((part[0][q][js] + part[1][q][js]) + part[2][q][js]) + part[3][q][js];
-      const float4 A = L.a[tid], B = L.b[tid];
-      o[0] = -fmaf(A.z, m9[0], A.w * m9[1]);
-      o[1] = -fmaf(A.w, m9[0], B.x * m9[1]);
-      o[2] = -0.5f * m9[2];
-      o[3] = -m9[3];
-      o[4] = -0.5f * m9[4];
-      o[5] = B.y > 0.f ? m9[5] / B.y : 0.f;
-      o[6] = m9[6];
-      o[7] = m9[7];
-      o[8] = m9[8];
-      // the largest alpha T of the Gaussian over its pairs and views: weights
-      // are not negative, so the integer order of the bits is theirs, and a
-      // maximum does not depend on the order it is taken in
-      if (g_max && s_gauss[tid] != 0xFFFFFFFFu) {
-        const float w = fmaxf(fmaxf(part[0][9][js], part[1][9][js]), fmaxf(part[2][9][js], part[3][9][js]));
-        if (w > 0.f) atomicMax(&g_max[s_gauss[tid]], __float_as_uint(w));
+        for (int q = 0; q < 9; ++q) m9[q] = ((part[0][q][js] + part[1][q][js]) + part[2][q][js]) + part[3][q][js];
+        const float4 A = L.a[tid], B = L.b[tid];
+        o[0] = -fmaf(A.z, m9[0], A.w * m9[1]);
+        o[1] = -fmaf(A.w, m9[0], B.x * m9[1]);
+        o[2] = -0.5f * m9[2];
+        o[3] = -m9[3];
+        o[4] = -0.5f * m9[4];
+        o[5] = B.y > 0.f ? m9[5] / B.y : 0.f;
+        o[6] = m9[6];
+        o[7] = m9[7];
+        o[8] = m9[8];
+        // the largest alpha T of the Gaussian over its pairs and views: weights
+        // are not negative, so the integer order of the bits is theirs, and a
+        // maximum does not depend on the order it is taken in
+        if (g_max && s_gauss[tid] != 0xFFFFFFFFu) {
+          const float w = fmaxf(fmaxf(part[0][9][js], part[1][9][js]), fmaxf(part[2][9][js], part[3][9][js]));
+          if (w > 0.f) atomicMax(&g_max[s_gauss[tid]], __float_as_uint(w));
+        }
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+#pragma unroll
+          for (int q = 0; q < kGradSlots; ++q) part[w][q][js] = 0.f;
+        o[9] = o[10] = o[11] = 0.f;
+        const uint32_t emit = s_emit[tid];
+        if (emit < cap) {
+          float4* dst = reinterpret_cast<float4*>(g_pair + (size_t)emit * 12);
+          dst[0] = make_float4(o[0], o[1], o[2], o[3]);
+          dst[1] = make_float4(o[4], o[5], o[6], o[7]);
+          dst[2] = make_float4(o[8], o[9], o[10], o[11]);
+          alive[emit] = 1;
+        }
       }
-#pragma unroll
-      for (int w = 0; w < 4; ++w)
-#pragma unroll
-        for (int q = 0; q < kGradSlots; ++q) part[w][q][js] = 0.f;
-      o[9] = o[10] = o[11] = 0.f;
-      const uint32_t emit = s_emit[tid];
-      if (emit < cap) {
-        float4* dst = reinterpret_cast<float4*>(g_pair + (size_t)emit * 12);
-        dst[0] = make_float4(o[0], o[1], o[2], o[3]);
-        dst[1] = make_float4(o[4], o[5], o[6], o[7]);
-        dst[2] = make_float4(o[8], o[9], o[10], o[11]);
-        alive[emit] = 1;
-      }
+      __syncthreads();
     }
-    __syncthreads();
   }
 }
 
@@ -956,7 +962,12 @@ hipError_t launch_blend_bwd(const ViewD* views_dev, int n_views, const float* re
                             const uint32_t* offsets, float* g_pair, uint8_t* alive, uint32_t* g_max,
                             hipStream_t s) {
   if (n_batches == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_blend_bwd, dim3(n_batches), dim3(256), 0, s, views_dev, n_views, records, n_rec, pair_vals,
+  // at most kBwdBlocks blocks (above that they take several items): a launch
+  // has a batch index per 256 pair slots and per tile, on large scenes mostly
+  // of batches never reached (610k of 643k on the 4M step, whose blocks took
+  // 0.2 ms to come and go)
+  constexpr uint32_t kBwdBlocks = 32768;
+  hipLaunchKernelGGL(k_blend_bwd, dim3(std::min(n_batches, kBwdBlocks)), dim3(256), 0, s, views_dev, n_views, records, n_rec, pair_vals,
                      sel, cap, ranges, ckpt, batch_tile, n_batches, order_cnt, order_list, dL_drgb, dL_dalpha,
                      pair_emit, boxes, offsets, g_pair, alive, g_max);
   return hipGetLastError();
