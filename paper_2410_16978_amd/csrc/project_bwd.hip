@@ -63,15 +63,61 @@ __device__ __forceinline__ void record_grad(uint32_t e0, uint32_t e1, const floa
   }
 }
 
+// A Gaussian's activated scales, unit quaternion (iq: 1 over its stored
+// length) and rotation matrix.
+struct Axes {
+  double s[3], q[4], iq, R[9];
+};
+
+__device__ __forceinline__ Axes load_axes(const ModelD& m, int i) {
+  const size_t n = m.n;
+  Axes a;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) a.s[k] = act_scale(m.scale[k * n + i], m.raw);
+  double qw = m.quat[i], qx = m.quat[n + i], qy = m.quat[2 * n + i], qz = m.quat[3 * n + i];
+  const double qn = sqrt(qw * qw + qx * qx + qy * qy + qz * qz);
+  a.iq = qn > 0.0 ? 1.0 / qn : 0.0;
+  qw *= a.iq; qx *= a.iq; qy *= a.iq; qz *= a.iq;
+  a.q[0] = qw; a.q[1] = qx; a.q[2] = qy; a.q[3] = qz;
+  a.R[0] = 1.0 - 2.0 * (qy * qy + qz * qz);
+  a.R[1] = 2.0 * (qx * qy - qw * qz);
+  a.R[2] = 2.0 * (qx * qz + qw * qy);
+  a.R[3] = 2.0 * (qx * qy + qw * qz);
+  a.R[4] = 1.0 - 2.0 * (qx * qx + qz * qz);
+  a.R[5] = 2.0 * (qy * qz - qw * qx);
+  a.R[6] = 2.0 * (qx * qz - qw * qy);
+  a.R[7] = 2.0 * (qy * qz + qw * qx);
+  a.R[8] = 1.0 - 2.0 * (qx * qx + qy * qy);
+  return a;
+}
+
 // Geometry: opacity, and the centre / covariance chain to mean, scale and
 // quaternion, in double: the chain rule takes differences of products of
 // the covariance terms (a nearly isotropic splat's rotation gradient is a
 // small difference of large ones), which float32 would leave with a relative
-// error far above the per-pixel terms' own.  The kernel is bound by the
-// loads of the pair partials, so the double arithmetic costs no time.  The
-// colour gradient of each visible record (zero on clamped channels) is left
-// in g_col[r][3] for the SH kernel.
-__global__ void __launch_bounds__(256)
+// error far above the per-pixel terms' own.  The colour gradient of each
+// visible record (zero on clamped channels) is left in g_col[r][3] for the
+// SH kernel.
+//
+// Bound by latency: a view is a chain of dependent loads (flags and range,
+// alive flags, partials), so what counts is the waves in flight.  Across the
+// views a thread keeps the covariance and the sums only (the symmetrised
+// gradient of the covariance, not that of its factor): 152 registers, three
+// waves a SIMD, against 215 and two with factor, scales and rotation kept
+// (200k, one view 29.5 -> 28.2 us; 500k of 4M trained, 8 views 491 -> 427).
+// Four waves (128 registers) spill inside the views' loop: 34.9 and 484 us.
+//
+// NW == 1: a thread takes a Gaussian and walks its views.  NW > 1: a block
+// takes 64 Gaussians, wave w the views w, w + NW, ...; the waves' sums meet
+// in LDS and are added in wave order.  That is faster while the Gaussians
+// alone leave wave slots empty, 64 x 3 x 4 x 256 = 196608 of them, and slower
+// where the chip is full (one thread against split, us: 8k x 8 views 27.5 /
+// 11.2; 60k x 2 17.3 / 13.4; 60k x 3 25.9 / 15.3; 125k x 2 22.5 / 21.2;
+// 250k x 2 28.9 / 29.9; 1M x 8 283 / 310).
+constexpr uint32_t kGeomSplit = 1u << 17;
+
+template <int NW>
+__global__ void __launch_bounds__(NW == 1 ? 256 : 64 * NW)
 k_project_bwd_geom(JobD job, const ViewD* __restrict__ views, const float* __restrict__ records,
                    const uint32_t* __restrict__ offsets, const float* __restrict__ g_pair,
                    const uint8_t* __restrict__ alive, uint32_t cap, const uint32_t* __restrict__ counters,
@@ -79,45 +125,35 @@ k_project_bwd_geom(JobD job, const ViewD* __restrict__ views, const float* __res
                    float* __restrict__ g_quat, float* __restrict__ g_opacity, float* __restrict__ g_col,
                    const uint32_t* __restrict__ g_max, float* __restrict__ max_contrib,
                    float* __restrict__ dens_grad, float* __restrict__ dens_cnt) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  const int wave = NW == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int i = NW == 1 ? (int)(blockIdx.x * blockDim.x + threadIdx.x) : (int)(blockIdx.x * 64u + (threadIdx.x & 63u));
   const ModelD& m = job.m;
-  if (i >= m.n) return;
   const int n = m.n;
-  const uint32_t layer = m.layer[i];
+  // (with several waves a lane past the last Gaussian stays for the barrier)
+  if (NW == 1 && i >= n) return;
+  const uint32_t layer = i < n ? m.layer[i] : 0xFFu;
   const bool train = layer < 32u && ((trainable >> layer) & 1u);
   const uint32_t K = min(counters[kCntPairs], cap);
   double gm[3] = {0.0, 0.0, 0.0}, gs[3] = {0.0, 0.0, 0.0}, gq[4] = {0.0, 0.0, 0.0, 0.0}, go = 0.0;
   double dgs = 0.0, dgc = 0.0;
+  double D[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};  // dSigma + dSigma^T, its upper triangle by rows
   if (train) {
-    const double mx = m.mean[i], my = m.mean[n + i], mz = m.mean[2 * n + i];
-    const double s[3] = {act_scale(m.scale[i], m.raw), act_scale(m.scale[n + i], m.raw),
-                         act_scale(m.scale[2 * n + i], m.raw)};
-    double qw = m.quat[i], qx = m.quat[n + i], qy = m.quat[2 * n + i], qz = m.quat[3 * n + i];
-    const double qn = sqrt(qw * qw + qx * qx + qy * qy + qz * qz);
-    const double iq = qn > 0.0 ? 1.0 / qn : 0.0;
-    qw *= iq; qx *= iq; qy *= iq; qz *= iq;
-    double Rq[9];
-    Rq[0] = 1.0 - 2.0 * (qy * qy + qz * qz);
-    Rq[1] = 2.0 * (qx * qy - qw * qz);
-    Rq[2] = 2.0 * (qx * qz + qw * qy);
-    Rq[3] = 2.0 * (qx * qy + qw * qz);
-    Rq[4] = 1.0 - 2.0 * (qx * qx + qz * qz);
-    Rq[5] = 2.0 * (qy * qz - qw * qx);
-    Rq[6] = 2.0 * (qx * qz - qw * qy);
-    Rq[7] = 2.0 * (qy * qz + qw * qx);
-    Rq[8] = 1.0 - 2.0 * (qx * qx + qy * qy);
-    double M[9], S[9];
+    const float fmx = m.mean[i], fmy = m.mean[n + i], fmz = m.mean[2 * n + i];
+    double S[9];
+    {
+      const Axes ax = load_axes(m, i);
+      double M[9];
 #pragma unroll
-    for (int r = 0; r < 3; ++r)
+      for (int r = 0; r < 3; ++r)
 #pragma unroll
-      for (int c = 0; c < 3; ++c) M[3 * r + c] = Rq[3 * r + c] * s[c];
+        for (int c = 0; c < 3; ++c) M[3 * r + c] = ax.R[3 * r + c] * ax.s[c];
 #pragma unroll
-    for (int r = 0; r < 3; ++r)
+      for (int r = 0; r < 3; ++r)
 #pragma unroll
-      for (int c = 0; c < 3; ++c)
-        S[3 * r + c] = M[3 * r] * M[3 * c] + M[3 * r + 1] * M[3 * c + 1] + M[3 * r + 2] * M[3 * c + 2];
-    double dM[9] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    for (int jv = 0; jv < job.n_views; ++jv) {
+        for (int c = 0; c < 3; ++c)
+          S[3 * r + c] = M[3 * r] * M[3 * c] + M[3 * r + 1] * M[3 * c + 1] + M[3 * r + 2] * M[3 * c + 2];
+    }
+    for (int jv = wave; jv < job.n_views; jv += NW) {
       const ViewD& V = views[job.view[jv]];
       const uint32_t r = V.rec_off + (uint32_t)i;
       const float* rec = records + (size_t)r * kRecordFloats;
@@ -139,6 +175,7 @@ k_project_bwd_geom(JobD job, const ViewD* __restrict__ views, const float* __res
       }
 #pragma unroll
       for (int ch = 0; ch < 3; ++ch) g_col[(size_t)r * 3 + ch] = ((clamp_bits >> ch) & 1u) ? 0.f : (float)g[6 + ch];
+      const double mx = fmx, my = fmy, mz = fmz;
       double W[9];
 #pragma unroll
       for (int k = 0; k < 9; ++k) W[k] = V.R[k];
@@ -152,7 +189,6 @@ k_project_bwd_geom(JobD job, const ViewD* __restrict__ views, const float* __res
       float xr_f, yr_f;
       {
         const float* Wf = V.R;
-        const float fmx = m.mean[i], fmy = m.mean[n + i], fmz = m.mean[2 * n + i];
         const float ftx = __fadd_rn(__fadd_rn(__fadd_rn(__fmul_rn(Wf[0], fmx), __fmul_rn(Wf[1], fmy)),
                                               __fmul_rn(Wf[2], fmz)), V.t[0]);
         const float fty = __fadd_rn(__fadd_rn(__fadd_rn(__fmul_rn(Wf[3], fmx), __fmul_rn(Wf[4], fmy)),
@@ -200,22 +236,13 @@ k_project_bwd_geom(JobD job, const ViewD* __restrict__ views, const float* __res
         dT0[r2] = 2.0 * da * ST0[r2] + db * ST1[r2];
         dT1[r2] = db * ST0[r2] + 2.0 * dc * ST1[r2];
       }
-      // dSigma (symmetrised) and dM = (dS + dS^T) M
-      double dS[9];
+      // dSigma, symmetrised
 #pragma unroll
-      for (int r2 = 0; r2 < 3; ++r2)
+      for (int r2 = 0, e = 0; r2 < 3; ++r2)
 #pragma unroll
-        for (int q2 = 0; q2 < 3; ++q2)
-          dS[3 * r2 + q2] = da * Tm[r2] * Tm[q2] + db * Tm[r2] * Tm[3 + q2] + dc * Tm[3 + r2] * Tm[3 + q2];
-#pragma unroll
-      for (int r2 = 0; r2 < 3; ++r2)
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-          double acc = 0.0;
-#pragma unroll
-          for (int j = 0; j < 3; ++j) acc += (dS[3 * r2 + j] + dS[3 * j + r2]) * M[3 * j + k];
-          dM[3 * r2 + k] += acc;
-        }
+        for (int q2 = r2; q2 < 3; ++q2, ++e)
+          D[e] += 2.0 * (da * Tm[r2] * Tm[q2] + dc * Tm[3 + r2] * Tm[3 + q2]) +
+                  db * (Tm[r2] * Tm[3 + q2] + Tm[q2] * Tm[3 + r2]);
       // ---- Jacobian and projected centre -> camera-space centre
       double dJ00 = 0.0, dJ02 = 0.0, dJ11 = 0.0, dJ12 = 0.0;
 #pragma unroll
@@ -247,7 +274,55 @@ k_project_bwd_geom(JobD job, const ViewD* __restrict__ views, const float* __res
       gm[1] += W[1] * dtx + W[4] * dty + W[7] * dtz;
       gm[2] += W[2] * dtx + W[5] * dty + W[8] * dtz;
     }
-    // ---- M = Rq diag(s) -> scale, rotation -> quaternion
+  }
+  if constexpr (NW > 1) {
+    // every wave sees the same 64 Gaussians
+    __shared__ double part[NW - 1][12][64];
+    if (__ballot(train) != 0ull) {
+      const int lane = threadIdx.x & 63;
+      if (wave > 0) {
+        double(&p)[12][64] = part[wave - 1];
+#pragma unroll
+        for (int k = 0; k < 6; ++k) p[k][lane] = D[k];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) p[6 + k][lane] = gm[k];
+        p[9][lane] = go;
+        p[10][lane] = dgs;
+        p[11][lane] = dgc;
+      }
+      __syncthreads();
+      if (wave == 0) {
+#pragma unroll
+        for (int w = 0; w < NW - 1; ++w) {
+#pragma unroll
+          for (int k = 0; k < 6; ++k) D[k] += part[w][k][lane];
+#pragma unroll
+          for (int k = 0; k < 3; ++k) gm[k] += part[w][6 + k][lane];
+          go += part[w][9][lane];
+          dgs += part[w][10][lane];
+          dgc += part[w][11][lane];
+        }
+      }
+    }
+    if (wave > 0 || i >= n) return;
+  }
+  if (train) {
+    // ---- Sigma = M M^T, M = R diag(s) -> scale, rotation -> quaternion
+    // (scale and quaternion read again, by an index the compiler cannot match
+    // with the first: kept across the views they would cost 34 registers)
+    int i2 = i;
+    asm volatile("" : "+v"(i2));
+    const Axes ax = load_axes(m, i2);
+    const double(&Rq)[9] = ax.R;
+    const double(&s)[3] = ax.s;
+    const double qw = ax.q[0], qx = ax.q[1], qy = ax.q[2], qz = ax.q[3], iq = ax.iq;
+    const double DD[9] = {D[0], D[1], D[2], D[1], D[3], D[4], D[2], D[4], D[5]};
+    double dM[9];  // (dSigma + dSigma^T) M
+#pragma unroll
+    for (int r = 0; r < 3; ++r)
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+        dM[3 * r + k] = (DD[3 * r] * Rq[k] + DD[3 * r + 1] * Rq[3 + k] + DD[3 * r + 2] * Rq[6 + k]) * s[k];
     double dR[9];
 #pragma unroll
     for (int r = 0; r < 3; ++r)
@@ -389,7 +464,13 @@ hipError_t launch_project_bwd(const JobD& job, const ViewD* views_dev, const flo
                               float* activity, float* dens_grad, float* dens_cnt, hipStream_t s) {
   if (job.m.n <= 0) return hipSuccess;
   const dim3 grid(div_up((uint32_t)job.m.n, 256u)), block(256);
-  hipLaunchKernelGGL(k_project_bwd_geom, grid, block, 0, s, job, views_dev, records, offsets, g_pair, alive,
+  const int nw = (uint32_t)job.m.n <= kGeomSplit ? std::min(job.n_views, 4) : 1;
+  const auto geom = nw <= 1   ? k_project_bwd_geom<1>
+                    : nw == 2 ? k_project_bwd_geom<2>
+                    : nw == 3 ? k_project_bwd_geom<3>
+                              : k_project_bwd_geom<4>;
+  const dim3 ggrid(nw <= 1 ? grid.x : div_up((uint32_t)job.m.n, 64u)), gblock(nw <= 1 ? 256u : 64u * (uint32_t)nw);
+  hipLaunchKernelGGL(geom, ggrid, gblock, 0, s, job, views_dev, records, offsets, g_pair, alive,
                      pair_capacity, counters, trainable, g_mean, g_scale, g_quat, g_opacity, g_col, g_max, max_contrib,
                      dens_grad, dens_cnt);
   switch (job.m.D) {
