@@ -155,6 +155,27 @@ __device__ __forceinline__ uint32_t wave_scan_add(uint32_t x) {
   return x;
 }
 
+// Lanes of the wave whose valid digit of BITS bits equals this lane's.  Per
+// bit b: m = all ones if this lane's bit is set, and the lanes that agree
+// with it are ~(ballot ^ m); each half of the 64-lane mask is narrowed with
+// one three-input bit operation (truth table 0x82: acc & ~(bal ^ m)).  The
+// bit is extracted by name: left to itself, the compiler takes two shifts
+// for it, a fifth instruction a bit.
+template <int BITS>
+__device__ __forceinline__ uint64_t match_digit(uint32_t d, bool valid) {
+  const uint64_t vb = __ballot(valid);
+  uint32_t lo = (uint32_t)vb, hi = (uint32_t)(vb >> 32);
+#pragma unroll
+  for (int b = 0; b < BITS; ++b) {
+    uint32_t m;
+    asm("v_bfe_i32 %0, %1, %2, 1" : "=v"(m) : "v"(d), "i"(b));
+    const uint64_t bal = __ballot(m != 0u);
+    lo = __builtin_amdgcn_bitop3_b32((uint32_t)bal, m, lo, 0x82);
+    hi = __builtin_amdgcn_bitop3_b32((uint32_t)(bal >> 32), m, hi, 0x82);
+  }
+  return ((uint64_t)hi << 32) | lo;
+}
+
 // Bitwise OR over the wave, returned to every lane.
 __device__ __forceinline__ uint32_t wave_or(uint32_t x) {
   x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, false);

@@ -43,21 +43,6 @@ __device__ __forceinline__ uint64_t ord_lanes_below() {
   return lane == 0 ? 0ull : (~0ull >> (64 - lane));
 }
 
-// Lanes whose valid digit of BITS bits equals this lane's.
-template <int BITS>
-__device__ __forceinline__ uint64_t ord_match(uint32_t d, bool valid) {
-  const uint64_t vb = __ballot(valid);
-  uint32_t lo = (uint32_t)vb, hi = (uint32_t)(vb >> 32);
-#pragma unroll
-  for (int b = 0; b < BITS; ++b) {
-    const uint32_t s = (uint32_t)__builtin_amdgcn_sbfe((int)d, (unsigned)b, 1u);
-    const uint64_t bal = __ballot(s != 0u);
-    lo = __builtin_amdgcn_bitop3_b32((uint32_t)bal, s, lo, 0x82);
-    hi = __builtin_amdgcn_bitop3_b32((uint32_t)(bal >> 32), s, hi, 0x82);
-  }
-  return ((uint64_t)hi << 32) | lo;
-}
-
 // The view that owns block `blk` of the record passes (sort_blk) or of the
 // emission (seq_blk): the last whose first block is not beyond it.  A view
 // without blocks (a follower in the record passes, an empty model) starts
@@ -273,7 +258,7 @@ k_rec_small(const ViewD* __restrict__ views, const uint32_t* __restrict__ keys, 
       key[r] = ok ? s_keys[i] : 0u;
       val[r] = ok ? s_vals[i] : 0u;
       const uint32_t d = (key[r] >> (8 * pass)) & 255u;
-      const uint64_t peers = ord_match<8>(d, ok);
+      const uint64_t peers = match_digit<8>(d, ok);
       const uint64_t front = peers & ord_lanes_below();
       uint32_t pre = 0;
       if (ok) pre = wave_cnt[wave][d];
@@ -406,7 +391,7 @@ k_rec_pass(const ViewD* __restrict__ views, int n_views, uint32_t* __restrict__ 
 #pragma unroll
   for (int r = 0; r < kRecItems; ++r) {
     const uint32_t d = (key[r] >> shift) & 255u;
-    const uint64_t peers = ord_match<8>(d, ok[r]);
+    const uint64_t peers = match_digit<8>(d, ok[r]);
     const uint64_t front = peers & ord_lanes_below();
     uint32_t pre = 0;
     if (ok[r]) pre = wave_cnt[wave][d];
@@ -790,7 +775,7 @@ k_pair_pass(const TT* __restrict__ tin, TT* __restrict__ tout, const uint32_t* _
     for (int r = 0; r < kPairItems; ++r) {
       const bool ok = base + wbase + r * 64 < end;
       const uint32_t d = (til[r] >> shift) & mask;
-      const uint64_t peers = ord_match<BITS>(d, ok);
+      const uint64_t peers = match_digit<BITS>(d, ok);
       const uint64_t front = peers & ord_lanes_below();
       uint32_t pre = 0;
       if (ok) pre = wave_cnt[wave][d];

@@ -36,38 +36,6 @@ __device__ __forceinline__ uint64_t lanemask_lt() {
   return (lane == 0) ? 0ull : (~0ull >> (64 - lane));
 }
 
-// Lanes of the wave whose valid 8-bit digit equals this lane's.  Per bit b:
-// s = all ones if this lane's bit is set, and the lanes that agree with it
-// are ~(ballot ^ s); each half of the 64-lane mask is narrowed with one
-// three-input bit operation (truth table 0x82: acc & ~(bal ^ s)).
-__device__ __forceinline__ uint64_t match_digit(uint32_t d, bool valid) {
-  const uint64_t vb = __ballot(valid);
-  uint32_t lo = (uint32_t)vb, hi = (uint32_t)(vb >> 32);
-#pragma unroll
-  for (int b = 0; b < 8; ++b) {
-    const uint32_t s = (uint32_t)__builtin_amdgcn_sbfe((int)d, (unsigned)b, 1u);
-    const uint64_t bal = __ballot(s != 0u);
-    lo = __builtin_amdgcn_bitop3_b32((uint32_t)bal, s, lo, 0x82);
-    hi = __builtin_amdgcn_bitop3_b32((uint32_t)(bal >> 32), s, hi, 0x82);
-  }
-  return ((uint64_t)hi << 32) | lo;
-}
-
-// Digit of DBITS bits: the lanes holding the same digit (and valid).
-template <int DBITS>
-__device__ __forceinline__ uint64_t match_digit_bits(uint32_t d, bool valid) {
-  const uint64_t vb = __ballot(valid);
-  uint32_t lo = (uint32_t)vb, hi = (uint32_t)(vb >> 32);
-#pragma unroll
-  for (int b = 0; b < DBITS; ++b) {
-    const uint32_t s = (uint32_t)__builtin_amdgcn_sbfe((int)d, (unsigned)b, 1u);
-    const uint64_t bal = __ballot(s != 0u);
-    lo = __builtin_amdgcn_bitop3_b32((uint32_t)bal, s, lo, 0x82);
-    hi = __builtin_amdgcn_bitop3_b32((uint32_t)(bal >> 32), s, hi, 0x82);
-  }
-  return ((uint64_t)hi << 32) | lo;
-}
-
 __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x) { return wave_scan_add(x); }
 
 // ---------------------------------------------------------------- histogram
@@ -195,7 +163,7 @@ k_sort_pass(uint64_t* __restrict__ keys0, uint64_t* __restrict__ keys1, uint32_t
   for (int r = 0; r < kSortItems; ++r) {
     const bool valid = (wbase + r * 64 + lane) < K;
     const uint32_t d = (uint32_t)(key[r] >> shift) & 255u;
-    const uint64_t peers = match_digit(d, valid);
+    const uint64_t peers = match_digit<8>(d, valid);
     const uint64_t before = peers & lanemask_lt();
     uint32_t pre = 0;
     if (valid) pre = wave_cnt[wave][d];
@@ -478,7 +446,7 @@ k_tile_pass12(const uint64_t* __restrict__ kin, uint64_t* __restrict__ kout, con
   for (int r = 0; r < kT12Items; ++r) {
     const bool valid = (wbase + r * 64 + lane) < K;
     const uint32_t d = (uint32_t)(key[r] >> 32) & (uint32_t)(kT12Digits - 1);
-    const uint64_t peers = match_digit_bits<12>(d, valid);
+    const uint64_t peers = match_digit<12>(d, valid);
     const uint64_t before = peers & lanemask_lt();
     uint32_t pre = 0;
     if (valid) pre = wave_cnt[wave][d];
@@ -716,7 +684,7 @@ __device__ __forceinline__ uint32_t seg_rank_p(SegLdsP<THREADS, DBITS, BIG>& L, 
     const uint32_t idx = (uint32_t)(wave * I + r) * 64u + lane;
     const bool valid = idx < n;
     const uint32_t d = (uint32_t)(item[r] >> shift) & (uint32_t)(D - 1);
-    const uint64_t peers = match_digit_bits<DBITS>(d, valid);
+    const uint64_t peers = match_digit<DBITS>(d, valid);
     const uint64_t before = peers & lanemask_lt();
     uint32_t pre = 0;
     if (valid) pre = L.cnt[wave][d];
@@ -973,7 +941,7 @@ __device__ void sort_segment_big(SegLdsBig& L, const SegArgs& a, uint32_t tile, 
       if (valid) kother[s0 + i] = ((uint64_t)k[r] << 32) | v[r];
       for (int p = 0; p < passes; ++p) {
         const uint32_t d = (k[r] >> (DB * p)) & (uint32_t)(D - 1);
-        const uint64_t peers = match_digit_bits<DB>(d, valid);
+        const uint64_t peers = match_digit<DB>(d, valid);
         if (valid && (peers & lanemask_lt()) == 0) atomicAdd(&L.base[p][d], (uint32_t)__popcll(peers));
       }
     }
@@ -1080,16 +1048,23 @@ constexpr int kSegWaveDigitBits = 8;
 constexpr int kSegBlockDigitBits = 9;
 constexpr int kSegSmallWaves = 16;           // small tiles per block item, one per wave
 constexpr uint32_t kSegBlockClasses = 15;  // classes with floor(2 log2 n) >= 18, i.e. n >= 512
-constexpr uint32_t kSegSingleClasses = 9;  // n >= 4096: a whole block; below, two tiles per block (halves)
+constexpr uint32_t kSegSingleClasses = 9;  // n >= 4096: always a whole block
 constexpr int kSegHalfThreads = 512;
 static_assert(kSegWaveMax == 512 && kSegBlockClasses < kTileClasses, "size classes of k_tile_order");
 
 // One launch of G blocks of 1024 threads for every tile (the size classes of
 // k_tile_order, largest first).  Items, in about descending cost: the tiles
 // of at least 4096 pairs, one per block; the tiles of at most kSegWaveMax
-// pairs in groups of kSegSmallWaves, one per wave (a wave on ~500 pairs
+// pairs in groups of up to kSegSmallWaves, one per wave (a wave on ~500 pairs
 // takes about as long as a block on a large tile); then the tiles in
 // between two per block, one per 512-thread half, the halves in lockstep.
+// A segment is a chain of ranking steps, one per key a lane holds and pass,
+// so blocks to spare are used to shorten it: while every item still has a
+// block of its own, smaller classes are sorted by halves too, then by whole
+// blocks, and the tiles left are spread over the blocks left, as few waves
+// in each as that takes (before and after, us: 64 tiles of up to 461 pairs
+// 16.9 / 13.0; 672 of up to 2787 21.5 / 16.9; 2500 of up to 6966 33 / 30.5;
+// a 6669-pair tile alone bounds the 3042 of a three-view step, 29.0 / 28.8).
 // Block b starts with item b; later items go to whichever block is free
 // first, so a block holding one of the largest tiles takes nothing else.
 __global__ void __launch_bounds__(1024) k_sort_segments(SegArgs a) {
@@ -1100,20 +1075,37 @@ __global__ void __launch_bounds__(1024) k_sort_segments(SegArgs a) {
     SegLdsP<kSegHalfThreads, kSegBlockDigitBits> half[2];
   } L;
   __shared__ uint32_t s_end[kTileClasses];  // inclusive prefix of the class counts (empty tiles left out)
-  __shared__ uint32_t s_next, s_passes;
+  __shared__ uint32_t s_next, s_passes, s_single, s_big;
   const uint32_t K = min(a.counters[kCntPairs], a.cap);
   if (threadIdx.x < 64) {
     const uint32_t k = threadIdx.x;
     const uint32_t cnt = k + 1 < kTileClasses ? min(a.class_count[k], a.n_tiles) : 0u;
     const uint32_t inc = wave_scan_add(cnt);
     if (k < kTileClasses) s_end[k] = inc;
+    // lane k: the tiles of the first k + 1 classes by halves (or blocks), then
+    // by blocks; the last lane whose items fit the grid decides
+    auto at = [&](uint32_t c) { return (uint32_t)__shfl((int)inc, (int)c, 64); };
+    const uint32_t all = at(kTileClasses - 1);
+    uint32_t single = at(kSegSingleClasses - 1), big = at(kSegBlockClasses - 1);
+    uint64_t fit = __ballot(k >= kSegBlockClasses && k < kTileClasses &&
+                            single + div_up(inc - single, 2u) + div_up(all - inc, (uint32_t)kSegSmallWaves) <= gridDim.x);
+    if (fit) big = at(63u - (uint32_t)__builtin_clzll(fit));
+    fit = __ballot(k >= kSegSingleClasses && k < kTileClasses && inc <= big &&
+                   inc + div_up(big - inc, 2u) + div_up(all - big, (uint32_t)kSegSmallWaves) <= gridDim.x);
+    if (fit) single = at(63u - (uint32_t)__builtin_clzll(fit));
+    if (k == 0) {
+      s_single = single;
+      s_big = big;
+    }
   }
   __syncthreads();
-  const uint32_t n_single = s_end[kSegSingleClasses - 1];
-  const uint32_t n_big = s_end[kSegBlockClasses - 1];
+  const uint32_t n_single = s_single;
+  const uint32_t n_big = s_big;
   const uint32_t n_all = s_end[kTileClasses - 1];
-  const uint32_t n_groups = div_up(n_all - n_big, (uint32_t)kSegSmallWaves);
-  const uint32_t n_pairs = div_up(n_big - n_single, 2u);
+  const uint32_t n_pairs = div_up(n_big - n_single, 2u), n_blocks = n_single + n_pairs;
+  const uint32_t group = n_blocks < gridDim.x ? min(div_up(n_all - n_big, gridDim.x - n_blocks), (uint32_t)kSegSmallWaves)
+                                              : (uint32_t)kSegSmallWaves;  // tiles in one
+  const uint32_t n_groups = group ? div_up(n_all - n_big, group) : 0u;
   const uint32_t total = n_single + n_groups + n_pairs;
   // the idx-th tile of the class order (idx < n_all) and its segment
   auto segment = [&](uint32_t idx, uint32_t& tile, uint32_t& s0, uint32_t& s1) {
@@ -1144,8 +1136,8 @@ __global__ void __launch_bounds__(1024) k_sort_segments(SegArgs a) {
       }
     } else if (i < n_single + n_groups) {
       const uint32_t wave = seg_thread() >> 6, lane = seg_thread() & 63u;
-      const uint32_t idx = n_big + (i - n_single) * kSegSmallWaves + wave;
-      if (idx < n_all) {
+      const uint32_t idx = n_big + (i - n_single) * group + wave;
+      if (wave < group && idx < n_all) {
         const bool ok = segment(idx, tile, s0, s1) && s1 - s0 <= kSegWaveMax;
         if (!ok) {
           if (lane == 0) atomicOr(a.err, 32u);
