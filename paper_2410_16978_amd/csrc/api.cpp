@@ -85,7 +85,7 @@ struct PipeBufs {
   uint32_t* sort_keys = nullptr;  // [2][S]
   uint32_t* sort_vals = nullptr;  // [2][S]
   uint32_t* pair_tiles = nullptr;  // [2][P]
-  uint32_t* pair_counts = nullptr;  // [blocks][256], [256]
+  uint32_t* pair_counts = nullptr;  // [blocks + 1][256], above 65536 tiles [blocks + 1][512]
   uint32_t* order_ctl = nullptr;
   size_t order_ctl_words = 0;
 };
@@ -133,7 +133,7 @@ size_t carve(Carver& c, PipeBufs& b, size_t n_views, size_t R, size_t P, size_t 
     b.sort_keys = c.take<uint32_t>(2 * std::max<size_t>(op.S, 1));
     b.sort_vals = c.take<uint32_t>(2 * std::max<size_t>(op.S, 1));
     b.pair_tiles = c.take<uint32_t>(2 * (std::max<size_t>(P, 1) + 4));
-    b.pair_counts = c.take<uint32_t>(256 * ((size_t)pair_pass_blocks((uint32_t)P) + 1));
+    b.pair_counts = c.take<uint32_t>((X > 65536 ? (size_t)1 << kPairBits : 256) * ((size_t)pair_pass_blocks((uint32_t)P) + 1));
     b.order_ctl_words = order_ctl_words(op, n_views);
     b.order_ctl = c.take<uint32_t>(b.order_ctl_words);
   } else {
@@ -297,7 +297,6 @@ OrderBufs order_bufs(const PipeBufs& b, const OrderPlan& op, int n_views, size_t
   w += 4 * 256 * (size_t)n_views;
   o.rec_status = w;
   o.pair_counts = b.pair_counts;
-  o.tile_total = b.pair_counts + 256 * (size_t)pair_pass_blocks(P);
   return o;
 }
 

@@ -94,10 +94,10 @@ constexpr uint32_t kRecSmall = 8192;  // units up to this size are sorted by one
 constexpr uint32_t kEmitTile = 4096, kEmitTileSmall = 1024;
 inline uint32_t emit_tile(uint64_t records) { return records > (8u << 20) ? kEmitTile : kEmitTileSmall; }
 constexpr uint32_t kPairBlocks = 512;  // blocks of a tile-digit pass at most
+constexpr int kPairBits = 9;           // bits of a tile digit at most (above 65536 tiles; 8 up to them)
 // pairs a block of a tile-digit pass handles at a time
 constexpr uint32_t kPairStep = 8192, kPairStepSmall = 2048;
 inline uint32_t pair_step(uint32_t cap) { return cap > kPairBlocks * kPairStepSmall ? kPairStep : kPairStepSmall; }
-constexpr int kMaxTilePasses = 4;     // tile digits of at most 8 bits
 
 constexpr int kFmtF32 = 0, kFmtHalfPacked = 1, kFmtHalfCodebook = 2;
 struct ModelD {
@@ -237,8 +237,7 @@ struct OrderBufs {
   uint32_t *tile_a, *tile_b;      // tiles by pair (2 or 4 bytes each), double-buffered
   uint32_t *rec_a, *rec_b;        // records by pair, double-buffered
   uint64_t* emit_status;          // [seq_blocks]
-  uint32_t* pair_counts;          // [pair_pass_blocks][256]
-  uint32_t* tile_total;           // [256]
+  uint32_t* pair_counts;          // [pair_pass_blocks + 1][256 or 512]: by block, then all
   uint32_t* tickets;              // [8]: record passes, emission, byte passes some unit needs
   uint32_t* ranges;
   uint32_t* sel;

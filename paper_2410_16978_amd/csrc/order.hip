@@ -14,7 +14,7 @@
 //                records (k_rec_small instead for units of at most 8192)
 //   k_emit       the pairs (tile, record) in the sorted order, with the scan
 //                of the tile counts (decoupled look-back) in the same launch
-//   k_pair_*     stable passes over the tile digits (at most 8 bits each):
+//   k_pair_*     stable passes over the tile digits (at most 9 bits each):
 //                count, scan, scatter
 //   k_tile_runs  the tiles' [start, end)
 //
@@ -631,6 +631,10 @@ k_emit(const ViewD* __restrict__ views, int n_views, uint32_t n_blk, const uint3
 constexpr int kPairThreads = 512;
 constexpr int kPairWaves = kPairThreads / 64;
 
+// Words of a block's counts: the digits of a pass of `bits` bits, 256 at least.
+constexpr uint32_t digit_stride(int bits) { return bits > 8 ? 1u << bits : 256u; }
+static_assert(digit_stride(kPairBits) <= (uint32_t)kPairThreads, "a thread owns at most one digit");
+
 // Block b's share of K pairs: whole steps.
 __device__ __forceinline__ void pair_share(uint32_t K, uint32_t b, uint32_t g, uint32_t step, uint32_t& begin,
                                            uint32_t& end) {
@@ -639,17 +643,17 @@ __device__ __forceinline__ void pair_share(uint32_t K, uint32_t b, uint32_t g, u
   end = (uint32_t)min((uint64_t)K, (uint64_t)begin + per);
 }
 
-// counts[block][256] of the digit at `shift` of the block's share.
-template <typename TT>
+// counts[block][S] of the digit at `shift` of the block's share.
+template <typename TT, uint32_t S>
 __global__ void __launch_bounds__(kPairThreads)
 k_pair_count(const TT* __restrict__ tiles, const uint32_t* __restrict__ counters, uint32_t cap, uint32_t step,
              int shift, uint32_t mask, uint32_t* __restrict__ counts) {
   // eight counters per digit, by lane: the second pass meets runs of few
   // digits (one view's tile rows), whose additions would queue on one word
   constexpr uint32_t kRep = 8;
-  __shared__ uint32_t lh[256 * kRep];
+  __shared__ uint32_t lh[S * kRep];
   const int t = threadIdx.x;
-  for (int i = t; i < (int)(256 * kRep); i += kPairThreads) lh[i] = 0;
+  for (int i = t; i < (int)(S * kRep); i += kPairThreads) lh[i] = 0;
   __syncthreads();
   const uint32_t rep = (uint32_t)t % kRep;
   const uint32_t K = min(counters[kCntPairs], cap);
@@ -668,17 +672,18 @@ k_pair_count(const TT* __restrict__ tiles, const uint32_t* __restrict__ counters
   }
   for (; k < end; k += kPairThreads) atomicAdd(&lh[(((uint32_t)tiles[k] >> shift) & mask) * kRep + rep], 1u);
   __syncthreads();
-  if (t < 256) {
+  if (t < (int)S) {
     uint32_t c = 0;
 #pragma unroll
     for (uint32_t r = 0; r < kRep; ++r) c += lh[t * kRep + r];
-    counts[(size_t)blockIdx.x * 256 + t] = c;
+    counts[(size_t)blockIdx.x * S + t] = c;
   }
 }
 
 // counts[b][d] becomes the count of digit d in the blocks before b, total[d]
 // the digit's count.  A block takes four digits, 256 threads per digit split
 // the g blocks.
+template <uint32_t S>
 __global__ void __launch_bounds__(1024)
 k_pair_scan(uint32_t* __restrict__ counts, uint32_t g, uint32_t* __restrict__ total) {
   __shared__ uint32_t s_w[16];
@@ -686,7 +691,7 @@ k_pair_scan(uint32_t* __restrict__ counts, uint32_t g, uint32_t* __restrict__ to
   const int lane = t & 63, wave = t >> 6;
   const uint32_t per = div_up(g, 256u), b0 = min(g, q * per), b1 = min(g, b0 + per);
   uint32_t sum = 0;
-  for (uint32_t b = b0; b < b1; ++b) sum += counts[(size_t)b * 256 + d];
+  for (uint32_t b = b0; b < b1; ++b) sum += counts[(size_t)b * S + d];
   const uint32_t inc = wave_scan_add(sum);
   if (lane == 63) s_w[wave] = inc;
   __syncthreads();
@@ -698,8 +703,8 @@ k_pair_scan(uint32_t* __restrict__ counts, uint32_t g, uint32_t* __restrict__ to
     all += c;
   }
   for (uint32_t b = b0; b < b1; ++b) {
-    const uint32_t c = counts[(size_t)b * 256 + d];
-    counts[(size_t)b * 256 + d] = run;
+    const uint32_t c = counts[(size_t)b * S + d];
+    counts[(size_t)b * S + d] = run;
     run += c;
   }
   if (q == 0) total[d] = all;
@@ -717,10 +722,10 @@ k_pair_pass(const TT* __restrict__ tin, TT* __restrict__ tout, const uint32_t* _
             uint32_t* __restrict__ rout, const uint32_t* __restrict__ counters, uint32_t cap,
             const uint32_t* __restrict__ before, const uint32_t* __restrict__ total, int shift, uint32_t mask,
             uint32_t* __restrict__ sel_out, uint32_t sel, uint32_t* __restrict__ err) {
-  constexpr uint32_t D = 1u << BITS, kStep = kPairThreads * kPairItems;
+  constexpr uint32_t D = 1u << BITS, S = digit_stride(BITS), kStep = kPairThreads * kPairItems;
   __shared__ uint16_t wave_cnt[kPairWaves][D];
   __shared__ uint32_t s_global[D];
-  __shared__ uint32_t s_w[4];
+  __shared__ uint32_t s_w[S / 64];
   __shared__ TT s_tile[kStep];
   __shared__ uint32_t s_rec[kStep];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
@@ -733,15 +738,15 @@ k_pair_pass(const TT* __restrict__ tin, TT* __restrict__ tout, const uint32_t* _
   uint32_t next = 0;
   {
     uint32_t c = 0, inc = 0, bef = 0;
-    if (t < 256) {
+    if (t < (int)S) {
       if (total) {
         c = total[t];
-        bef = before[(size_t)blockIdx.x * 256 + t];
+        bef = before[(size_t)blockIdx.x * S + t];
       } else {
         for (uint32_t b = 0; b < gridDim.x; b += 8) {
           uint32_t x[8];
 #pragma unroll
-          for (uint32_t u = 0; u < 8; ++u) x[u] = b + u < gridDim.x ? before[(size_t)(b + u) * 256 + t] : 0u;
+          for (uint32_t u = 0; u < 8; ++u) x[u] = b + u < gridDim.x ? before[(size_t)(b + u) * S + t] : 0u;
 #pragma unroll
           for (uint32_t u = 0; u < 8; ++u) {
             c += x[u];
@@ -753,7 +758,7 @@ k_pair_pass(const TT* __restrict__ tin, TT* __restrict__ tout, const uint32_t* _
       if (lane == 63) s_w[wave] = inc;
     }
     __syncthreads();
-    if (t < 256) {
+    if (t < (int)S) {
       next = inc - c + bef;
       for (int w = 0; w < wave; ++w) next += s_w[w];
     }
@@ -789,7 +794,7 @@ k_pair_pass(const TT* __restrict__ tin, TT* __restrict__ tout, const uint32_t* _
     __syncthreads();
     // thread t < D: digit t's place in the block, wave by wave
     uint32_t cw[kPairWaves], cnt = 0, inc = 0;
-    if (t < 256) {
+    if (t < (int)S) {
       if (t < (int)D) {
 #pragma unroll
         for (int w = 0; w < kPairWaves; ++w) cw[w] = wave_cnt[w][t];
@@ -894,18 +899,27 @@ k_tile_runs(const TT* __restrict__ tiles, uint32_t* __restrict__ counters, uint3
 int device_cus();
 
 namespace {
+template <typename TT, int BITS, int ITEMS>
+void pair_pass_bits(uint32_t g, const TT* tin, TT* tout, const uint32_t* rin, uint32_t* rout, const OrderBufs& o,
+                    int shift, uint32_t mask, uint32_t* sel_out, uint32_t sel, hipStream_t s) {
+  constexpr uint32_t S = digit_stride(BITS);
+  hipLaunchKernelGGL((k_pair_count<TT, S>), dim3(g), dim3(kPairThreads), 0, s, tin, o.counters, o.cap,
+                     (uint32_t)(kPairThreads * ITEMS), shift, mask, o.pair_counts);
+  uint32_t* total = g > kScanInline ? o.pair_counts + (size_t)S * g : nullptr;
+  if (total) hipLaunchKernelGGL(k_pair_scan<S>, dim3(S / 4), dim3(1024), 0, s, o.pair_counts, g, total);
+  hipLaunchKernelGGL((k_pair_pass<TT, BITS, ITEMS>), dim3(g), dim3(kPairThreads), 0, s, tin, tout, rin, rout,
+                     o.counters, o.cap, o.pair_counts, total, shift, mask, sel_out, sel, o.counters + kCntError);
+}
+
 template <typename TT, int ITEMS>
 void pair_pass(int bits, uint32_t g, const TT* tin, TT* tout, const uint32_t* rin, uint32_t* rout,
                const OrderBufs& o, int shift, uint32_t* sel_out, uint32_t sel, hipStream_t s) {
   const uint32_t mask = (1u << bits) - 1u;
-  hipLaunchKernelGGL(k_pair_count<TT>, dim3(g), dim3(kPairThreads), 0, s, tin, o.counters, o.cap,
-                     (uint32_t)(kPairThreads * ITEMS), shift, mask, o.pair_counts);
-  const bool scan = g > kScanInline;
-  if (scan) hipLaunchKernelGGL(k_pair_scan, dim3(64), dim3(1024), 0, s, o.pair_counts, g, o.tile_total);
-  const auto k = bits <= 6 ? k_pair_pass<TT, 6, ITEMS> : bits == 7 ? k_pair_pass<TT, 7, ITEMS>
-                                                                   : k_pair_pass<TT, 8, ITEMS>;
-  hipLaunchKernelGGL(k, dim3(g), dim3(kPairThreads), 0, s, tin, tout, rin, rout, o.counters, o.cap, o.pair_counts,
-                     scan ? o.tile_total : nullptr, shift, mask, sel_out, sel, o.counters + kCntError);
+  const auto pass = bits <= 6   ? pair_pass_bits<TT, 6, ITEMS>
+                    : bits == 7 ? pair_pass_bits<TT, 7, ITEMS>
+                    : bits == 8 ? pair_pass_bits<TT, 8, ITEMS>
+                                : pair_pass_bits<TT, sizeof(TT) == 2 ? 8 : kPairBits, ITEMS>;
+  pass(g, tin, tout, rin, rout, o, shift, mask, sel_out, sel, s);
 }
 
 template <typename TT>
@@ -932,11 +946,12 @@ hipError_t order_pairs(const OrderBufs& o, hipStream_t s) {
 }  // namespace
 
 // Digits of the tile grouping: np passes of `bits` bits each (the last may
-// see fewer).
+// see fewer).  Nine bits where they save a pass: 44M pairs of 70560 tiles took
+// 3 x (168 us + 49 of counting) with six, 2 x (221 + 51) with nine.
 void tile_passes(uint32_t n_tiles, int* bits, int* np) {
   int b = 1;
   while (b < 32 && (1ull << b) < n_tiles) ++b;
-  *np = (b + 7) / 8;
+  *np = b <= 2 * kPairBits ? (b + 7) / 8 - (b > 16) : (b + 7) / 8;
   *bits = (b + *np - 1) / *np;
 }
 

@@ -68,6 +68,8 @@ CASES = [
     (9, 1, 1030, 1025, 0.5, False, 3),       # boxes of the whole image
     (3000, 1, 300, 200, -4.0, False, 4),     # no layer active: no pair
     (300, 1, 4112, 4100, -5.0, False, 3),    # 257 x 257 tiles: four-byte tile ids
+    (600, 2, 4112, 4100, -5.0, False, 3),    # 2 x 66049 tiles: digits of nine bits
+    (300, 4, 4112, 4112, -5.0, False, 3),    # 4 x 66049 tiles: three passes
 ]
 
 
