@@ -205,11 +205,16 @@ typedef struct {
  *   pair_emit   uint32[P]     emission index of each sorted pair; or, in
  *                             calls that order their records before pairing
  *                             them (P >= 2 R, and P >= 2^20 with more than
- *                             4096 tiles or P >= 2^21), uint32[R][2]: each
- *                             record's first tile x | y << 16 and tile box
- *                             width | height << 16 in its view (0: culled),
- *                             from which the backward has the index.  Not
- *                             written by a shared depth order
+ *                             4096 tiles or P >= 2^21; with full tiles, P >=
+ *                             R, and P >= 2^20 and 768 X or P >= 3 * 2^16 and
+ *                             2048 X), each record's tile box,
+ *                             from which the backward has the index: its
+ *                             first tile and its size in its view (0:
+ *                             culled), uint32[R] x | y << 8 | width << 16 |
+ *                             height << 24 where the views have at most 255
+ *                             tiles a side, else uint32[R][2] x | y << 16,
+ *                             width | height << 16.  Not written by a shared
+ *                             depth order
  *   ranges      uint32[X][2]  [start, end) of each tile's pairs
  *   pixel_state float[Q][4]   transmittance left behind the last blended
  *                             splat, then the composited colour before the

@@ -81,7 +81,7 @@ struct PipeBufs {
   // order-first (order.hip): the record sort, the pairs, and the control
   // words (cleared in one range: tickets, digit counts, unit words, the
   // look-back words of the record passes and the emission)
-  uint2* boxes = nullptr;  // null: in the state's pair_emit
+  uint32_t* boxes = nullptr;  // null: in the state's pair_emit
   uint32_t* sort_keys = nullptr;  // [2][S]
   uint32_t* sort_vals = nullptr;  // [2][S]
   uint32_t* pair_tiles = nullptr;  // [2][P]
@@ -93,6 +93,7 @@ struct PipeBufs {
 // Sizes of a call that orders its records before it pairs them.
 struct OrderPlan {
   bool on = false;
+  bool box4 = false;       // tile boxes of four bytes (no view beyond 255 tiles a side)
   bool own_boxes = false;  // tile boxes in the workspace, not in the state's pair_emit
   size_t S = 0;            // sort slots: records of all sort units
   size_t rec_blocks = 0, seq_blocks = 0;
@@ -105,15 +106,29 @@ struct OrderPlan {
 // times and 6 a pair twice, where the per-tile path moves 12 a pair twice (up
 // to 4096 tiles once) and then sorts every tile; its 12 launches cost about
 // 30 us more than the other's on small calls.  Measured, per-tile against
-// order-first, whole frames: beyond 4096 tiles 197 / 192 us at 1.0M pairs and
+// order-first, whole frames, us: beyond 4096 tiles 197 / 192 at 1.0M pairs and
 // 158 / 169 at 0.5M (1100 x 1000), 1141 / 860 at 12.5M (2 x 1M records); up
 // to 4096 tiles 165 / 190 at 1.0M, 247 / 241 at 2.0M and 870 / 621 at 10M
-// (1024 x 1024).  Below two pair slots a record the record passes outweigh
-// the pairs (and the boxes of all records, which the backward reads from the
-// pair_emit array, would not fit there).
-constexpr uint32_t kOrderMinPairs = 1u << 20;
-bool order_first(uint64_t X, uint32_t P, uint64_t R) {
-  return P >= (tile_sort12(X, P) ? 2 * kOrderMinPairs : kOrderMinPairs) && (uint64_t)P >= 2 * R;
+// (1024 x 1024).
+//
+// With many pairs a tile the per-tile sort has few blocks at work, and a tile
+// beyond 8192 pairs passes through global memory in one of them; how uneven
+// the tiles are is not known here.  From 2048 pairs a tile on, order-first is
+// ahead even of evenly filled tiles (158 / 145 at 200 tiles, 223 / 172 at 72),
+// and far ahead of layered shells (286 / 183 at 100 tiles of 1815 pairs on
+// average, 2606 / 1106 at 64 of 30k); at 1200 to 1600 evenly filled ones are
+// faster sorted by tile (113 / 157), shells are not (299 / 219).  Between 1M
+// and 2M pairs it takes 768 a tile (440 / 359 at 985; 175 / 183 at 392; the
+// evenly filled tiles of a narrow view, 1015 each at 2.1M pairs, 204 / 220).
+//
+// Below two pair slots a record the record passes outweigh the pairs, unless
+// tiles are that full; and the boxes of all records, which the backward reads
+// from the pair_emit array, fit there if they are of four bytes.
+constexpr uint32_t kOrderMinPairs = 1u << 20, kOrderMinPairsFull = 3u << 16;
+bool order_first(uint64_t X, uint32_t P, uint64_t R, bool box4) {
+  const bool full = (P >= kOrderMinPairsFull && P >= 2048 * X) || (P >= kOrderMinPairs && P >= 768 * X);
+  if (P < (full && box4 ? R : 2 * R)) return false;
+  return full || P >= (tile_sort12(X, P) ? 2 * kOrderMinPairs : kOrderMinPairs);
 }
 
 // Words of the order-first path that are zero on entry.
@@ -129,7 +144,7 @@ size_t carve(Carver& c, PipeBufs& b, size_t n_views, size_t R, size_t P, size_t 
   b.scan_status = c.take<uint64_t>(scan_tiles((uint32_t)R));
   b.ctl = c.take<SortCtl>(1);
   if (op.on) {
-    if (op.own_boxes) b.boxes = c.take<uint2>(std::max<size_t>(R, 1));
+    if (op.own_boxes) b.boxes = c.take<uint32_t>((op.box4 ? 1 : 2) * std::max<size_t>(R, 1));
     b.sort_keys = c.take<uint32_t>(2 * std::max<size_t>(op.S, 1));
     b.sort_vals = c.take<uint32_t>(2 * std::max<size_t>(op.S, 1));
     b.pair_tiles = c.take<uint32_t>(2 * (std::max<size_t>(P, 1) + 4));
@@ -261,7 +276,7 @@ void plan_order(OrderPlan& op, std::vector<ViewD>& views, const std::vector<int>
   }
 }
 
-OrderBufs order_bufs(const PipeBufs& b, const OrderPlan& op, int n_views, size_t X, uint32_t P, const uint2* boxes,
+OrderBufs order_bufs(const PipeBufs& b, const OrderPlan& op, int n_views, size_t X, uint32_t P, const uint32_t* boxes,
                      uint32_t* pair_vals, uint32_t* counters, uint32_t* ranges, uint32_t* sel) {
   OrderBufs o;
   std::memset(&o, 0, sizeof(o));
@@ -278,6 +293,7 @@ OrderBufs order_bufs(const PipeBufs& b, const OrderPlan& op, int n_views, size_t
   o.vals_a = b.sort_vals;
   o.vals_b = b.sort_vals + std::max<size_t>(op.S, 1);
   o.boxes = boxes;
+  o.box4 = op.box4;
   o.counters = counters;
   o.cap = P;
   o.tile_a = b.pair_tiles;
@@ -330,9 +346,12 @@ bool view_ok(const gsr_view_state& v) {
 }
 
 // Order-first sizes of a call of n_views views of one model.
-OrderPlan single_plan(int64_t n, int n_views, uint64_t X, uint32_t P, bool shared) {
+OrderPlan single_plan(int64_t n, int n_views, int32_t width, int32_t height, uint32_t P, bool shared) {
   OrderPlan op;
-  op.on = shared || order_first(X, P, (uint64_t)n * n_views);
+  const uint32_t tx = div_up((uint32_t)width, (uint32_t)kTile), ty = div_up((uint32_t)height, (uint32_t)kTile);
+  const uint64_t X = (uint64_t)tx * ty * n_views;
+  op.box4 = tx <= (uint32_t)kBox4Tiles && ty <= (uint32_t)kBox4Tiles;
+  op.on = shared || order_first(X, P, (uint64_t)n * n_views, op.box4);
   if (!op.on) return op;
   op.own_boxes = shared;  // a forward that shares an order has no backward
   const int units = shared ? 1 : n_views;
@@ -527,11 +546,11 @@ size_t gsr_workspace_size(int32_t n, int32_t n_views, int32_t width, int32_t hei
   PipeBufs b;
   const size_t X = (size_t)n_views * (size_t)((width + kTile - 1) / kTile) * (size_t)((height + kTile - 1) / kTile);
   const size_t own = carve(c, b, (size_t)n_views, (size_t)n * n_views, pair_capacity, 0, false, X, true,
-                           single_plan(n, n_views, X, pair_capacity, false));
+                           single_plan(n, n_views, width, height, pair_capacity, false));
   if (!shared_order) return own;
   Carver cs(nullptr);
   return std::max(own, carve(cs, b, (size_t)n_views, (size_t)n * n_views, pair_capacity, 0, false, X, true,
-                             single_plan(n, n_views, X, pair_capacity, true)));
+                             single_plan(n, n_views, width, height, pair_capacity, true)));
 }
 
 gsr_status gsr_adam_step(int32_t n, int32_t sh_degree, uint32_t trainable_layers, const uint8_t* layer,
@@ -598,7 +617,7 @@ gsr_status forward_impl(const gsr_model* model, int32_t n_views, const gsr_camer
   const size_t plane = (size_t)W * H;
   // one depth order for all views: by the depth in views[0].sort_cam
   const bool shared = views[0].sort_shared != 0;
-  OrderPlan op = single_plan(n, n_views, X, P, shared);
+  OrderPlan op = single_plan(n, n_views, W, H, P, shared);
   Carver c(ws);
   PipeBufs b;
   if (carve(c, b, n_views, R, P, 0, false, X, backward_layout, op) > ws_bytes) return GSR_ENOSPACE;
@@ -616,9 +635,9 @@ gsr_status forward_impl(const gsr_model* model, int32_t n_views, const gsr_camer
     hv[v] = d;
     ids[v] = v;
   }
-  uint2* boxes = nullptr;
+  uint32_t* boxes = nullptr;
   if (op.on) {
-    boxes = op.own_boxes ? b.boxes : reinterpret_cast<uint2*>(state->pair_emit);
+    boxes = op.own_boxes ? b.boxes : state->pair_emit;
     std::vector<int> lead(ids);
     std::vector<const gsr_camera*> cam(n_views, nullptr);
     if (shared) {
@@ -638,7 +657,7 @@ gsr_status forward_impl(const gsr_model* model, int32_t n_views, const gsr_camer
   {
     StageScope sc(timer, GSR_STAGE_PROJECT, s);
     for (const JobD& j : make_jobs(md, ids))
-      HIP_TRY(launch_project(j, b.views, state->records, b.n_tiles, b.tile_box, boxes, b.sort_keys, state->counters,
+      HIP_TRY(launch_project(j, b.views, state->records, b.n_tiles, b.tile_box, boxes, op.box4, b.sort_keys, state->counters,
                              s));
   }
   OrderBufs o;
@@ -792,7 +811,7 @@ gsr_status gsr_rasterize_forward_noalloc(const gsr_model* model, int32_t n_views
   PipeBufs b;
   const size_t need =
       std::max(carve(per_tile, b, (size_t)n_views, R, P, 0, false, X, false, OrderPlan{}) + (shared ? 24 * (n + R) : 0),
-               carve(own, b, (size_t)n_views, R, P, 0, false, X, false, single_plan(model->n, n_views, X, P, shared)));
+               carve(own, b, (size_t)n_views, R, P, 0, false, X, false, single_plan(model->n, n_views, cams[0].width, cams[0].height, P, shared)));
   if (need > kNoallocScratchBytes) return GSR_ENOSPACE;
   void* ws = nullptr;
   const gsr_status st = scratch_of_current_device(&ws);
@@ -838,7 +857,7 @@ gsr_status gsr_rasterize_backward(const gsr_model* model, int32_t n_views, const
   const size_t plane = (size_t)W * H;
   Carver c(ws);
   PipeBufs b;
-  const OrderPlan op = single_plan(n, n_views, X, P, false);
+  const OrderPlan op = single_plan(n, n_views, W, H, P, false);
   if (carve(c, b, n_views, R, P, 0, false, X, true, op) > ws_bytes)
     return GSR_ENOSPACE;
   std::vector<ViewD> hv(n_views);
@@ -881,7 +900,7 @@ gsr_status gsr_rasterize_backward(const gsr_model* model, int32_t n_views, const
     HIP_TRY(launch_blend_bwd(b.views, n_views, state->records, R, state->pair_vals, state->sort_sel, P,
                              state->ranges, reinterpret_cast<const float4*>(state->checkpoints), batch_tile,
                              n_batches, b.order_cnt, b.order_list, dL_drgb, dL_dalpha, state->pair_emit,
-                             op.on ? reinterpret_cast<const uint2*>(state->pair_emit) : nullptr, state->offsets,
+                             op.on ? state->pair_emit : nullptr, op.box4, state->offsets,
                              b.g_pair, reinterpret_cast<uint8_t*>(b.alive), max_contrib ? b.g_max : nullptr, s));
   }
   const ModelD md = make_model(*model);
@@ -937,7 +956,9 @@ bool plan_batch(const gsr_model* models, int32_t n_models, const gsr_request* re
   if (bp.R >= (1ull << 31) || bp.X >= (1ull << 31)) return false;
   bool shared = false;
   for (int q = 0; q < n_req; ++q) shared = shared || reqs[q].vs.sort_shared != 0;
-  bp.order.on = shared || order_first(bp.X, pair_capacity, bp.R);
+  bp.order.box4 = true;
+  for (const ViewD& d : bp.views) bp.order.box4 = bp.order.box4 && d.tiles_x <= kBox4Tiles && d.tiles_y <= kBox4Tiles;
+  bp.order.on = shared || order_first(bp.X, pair_capacity, bp.R, bp.order.box4);
   if (bp.order.on) {
     bp.order.own_boxes = true;
     bp.order.seq_tile = emit_tile(bp.R);
@@ -1005,7 +1026,7 @@ gsr_status gsr_render_batch(const gsr_model* models, int32_t n_models, const gsr
       if (ids.empty()) continue;
       const ModelD md = make_model(models[m]);
       for (const JobD& j : make_jobs(md, ids))
-        HIP_TRY(launch_project(j, b.views, b.records, b.n_tiles, b.tile_box, b.boxes, b.sort_keys, b.counters, s));
+        HIP_TRY(launch_project(j, b.views, b.records, b.n_tiles, b.tile_box, b.boxes, bp.order.box4, b.sort_keys, b.counters, s));
     }
   }
   OrderBufs o;

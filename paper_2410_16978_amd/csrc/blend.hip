@@ -10,11 +10,11 @@
 // alpha >= 1/255 (the conic's minimum over the wave's pixel rectangle) meets
 // its pixels, and walks only that list.
 //
-// Forward: one block per tile walks its batches in order (below).
+// Forward: one block per band of a tile walks its batches in order (below).
 //
-// Backward: one block per (tile, batch) - the heavy tiles' lists are walked
-// by many blocks at once, one pixel per thread, each wave an 8 x 8 quadrant.
-// Each block starts at the end of its batch: the transmittance there is the
+// Backward: a block walks one (tile, batch) at a time - the heavy tiles' lists
+// are walked by many blocks at once, one pixel per thread, each wave an 8 x 8
+// quadrant.  It starts at the end of its batch: the transmittance there is the
 // next batch's checkpoint (or the final one), the colour behind it is the
 // background term plus the later batches' colours, summed from the back.  It
 // walks the batch back to front, rebuilding T by division by (1 - alpha)
@@ -25,7 +25,7 @@
 // by a reduce-scatter with the lane-half and row swaps (each step halves the
 // values a lane carries), the ninth and the max with DPP - the four wave sums
 // in a fixed order through LDS, and written as the pair's partial gradient:
-// no atomics, bitwise reproducible.
+// no sum is atomic, bitwise reproducible.
 #include <algorithm>
 
 #include "common.hpp"
@@ -674,7 +674,7 @@ k_blend_bwd(const ViewD* __restrict__ views, int n_views, const float* __restric
             const uint32_t* __restrict__ batch_tile, uint32_t n_batches, const uint32_t* __restrict__ order_cnt,
             const uint32_t* __restrict__ order_list, const float* __restrict__ dL_drgb,
             const float* __restrict__ dL_dalpha, const uint32_t* __restrict__ pair_emit,
-            const uint2* __restrict__ boxes, const uint32_t* __restrict__ offsets, float* __restrict__ g_pair,
+            const uint32_t* __restrict__ boxes, bool box4, const uint32_t* __restrict__ offsets, float* __restrict__ g_pair,
             uint8_t* __restrict__ alive, uint32_t* __restrict__ g_max) {
   __shared__ BatchLds L;
   constexpr int kSub = 64;  // pairs whose wave partials are held in LDS at a time
@@ -783,7 +783,7 @@ k_blend_bwd(const ViewD* __restrict__ views, int n_views, const float* __restric
         if (!boxes) {
           emit = pair_emit[start + tid];
         } else if (my_rec < n_rec) {
-          const uint2 bx = boxes[my_rec];
+          const uint2 bx = load_box(boxes, my_rec, box4);
           emit = offsets[my_rec] + ((uint32_t)ty - (bx.x >> 16)) * (bx.y & 0xFFFFu) + ((uint32_t)tx - (bx.x & 0xFFFFu));
         }
       }
@@ -958,7 +958,7 @@ hipError_t launch_blend_bwd(const ViewD* views_dev, int n_views, const float* re
                             const uint32_t* pair_vals, const uint32_t* sel, uint32_t cap, const uint32_t* ranges,
                             const float4* ckpt, const uint32_t* batch_tile, uint32_t n_batches,
                             const uint32_t* order_cnt, const uint32_t* order_list, const float* dL_drgb,
-                            const float* dL_dalpha, const uint32_t* pair_emit, const uint2* boxes,
+                            const float* dL_dalpha, const uint32_t* pair_emit, const uint32_t* boxes, bool box4,
                             const uint32_t* offsets, float* g_pair, uint8_t* alive, uint32_t* g_max,
                             hipStream_t s) {
   if (n_batches == 0) return hipSuccess;
@@ -969,7 +969,7 @@ hipError_t launch_blend_bwd(const ViewD* views_dev, int n_views, const float* re
   constexpr uint32_t kBwdBlocks = 32768;
   hipLaunchKernelGGL(k_blend_bwd, dim3(std::min(n_batches, kBwdBlocks)), dim3(256), 0, s, views_dev, n_views, records, n_rec, pair_vals,
                      sel, cap, ranges, ckpt, batch_tile, n_batches, order_cnt, order_list, dL_drgb, dL_dalpha,
-                     pair_emit, boxes, offsets, g_pair, alive, g_max);
+                     pair_emit, boxes, box4, offsets, g_pair, alive, g_max);
   return hipGetLastError();
 }
 

@@ -83,6 +83,23 @@ struct ViewD {
   float mip_var;
 };
 constexpr uint32_t kSortNone = 0, kSortOwn = 1, kSortCamera = 2, kSortFollow = 3;
+// Tile boxes by record, {x0 | y0 << 16, w | h << 16} in tiles of the view, or
+// where no view has more than 255 tiles a side four bytes {x0, y0, w, h}: the
+// emission gathers them in depth order, by the cache line.
+constexpr int32_t kBox4Tiles = 255;
+__device__ __forceinline__ uint2 load_box(const uint32_t* __restrict__ boxes, uint32_t r, bool box4) {
+  if (box4) {
+    const uint32_t q = boxes[r];
+    return make_uint2((q & 0xFFu) | (((q >> 8) & 0xFFu) << 16), ((q >> 16) & 0xFFu) | ((q >> 24) << 16));
+  }
+  return reinterpret_cast<const uint2*>(boxes)[r];
+}
+__device__ __forceinline__ void store_box(uint32_t* __restrict__ boxes, uint32_t r, bool box4, uint2 b) {
+  if (box4)
+    boxes[r] = (b.x & 0xFFu) | ((b.x >> 16) << 8) | ((b.y & 0xFFu) << 16) | ((b.y >> 16) << 24);
+  else
+    reinterpret_cast<uint2*>(boxes)[r] = b;
+}
 constexpr uint32_t kSortCulled = 0xFFFFFFFFu;  // sort key of a record no view of its unit keeps (never a depth)
 // Records per block of a record pass: the blocks' look-back chain bounds a
 // pass over many records, the number of blocks one over few.
@@ -212,7 +229,8 @@ hipError_t launch_upload(uint32_t* dst, const void* src, size_t n_words, hipStre
 hipError_t launch_activate(const ModelD& m, float* scale_out, float* opacity_out, hipStream_t s);
 hipError_t launch_clear_u32(uint32_t* p, size_t n, hipStream_t s);
 hipError_t launch_project(const JobD& job, const ViewD* views_dev, float* records, uint32_t* n_tiles,
-                          uint4* tile_box, uint2* boxes, uint32_t* sort_keys, uint32_t* counters, hipStream_t s);
+                          uint4* tile_box, uint32_t* boxes, bool box4, uint32_t* sort_keys, uint32_t* counters,
+                          hipStream_t s);
 uint32_t scan_tiles(uint32_t n);
 hipError_t launch_scan(const uint32_t* in, uint32_t* out, uint64_t* status, uint32_t* ticket, uint32_t n,
                        uint32_t* counters, uint32_t pair_capacity, hipStream_t s);
@@ -231,7 +249,8 @@ struct OrderBufs {
   uint32_t* rec_hist;             // [n_views][4][256]
   uint32_t* rec_status;           // [4][rec_blocks][256]
   uint32_t* unit;                 // [n_views][2]
-  const uint2* boxes;             // [R] x0 | y0 << 16, w | h << 16 in tiles of the view
+  const uint32_t* boxes;          // [R] tile boxes (load_box), of four bytes each if box4
+  bool box4;
   uint32_t* counters;
   uint32_t cap;
   uint32_t *tile_a, *tile_b;      // tiles by pair (2 or 4 bytes each), double-buffered
@@ -308,8 +327,8 @@ hipError_t launch_blend_bwd(const ViewD* views_dev, int n_views, const float* re
                             const float4* ckpt, const uint32_t* batch_tile, uint32_t n_batches,
                             const uint32_t* order_cnt, const uint32_t* order_list,
                             const float* dL_drgb, const float* dL_dalpha, const uint32_t* pair_emit,
-                            const uint2* boxes, const uint32_t* offsets, float* g_pair, uint8_t* alive,
-                            uint32_t* g_max, hipStream_t s);
+                            const uint32_t* boxes, bool box4, const uint32_t* offsets, float* g_pair,
+                            uint8_t* alive, uint32_t* g_max, hipStream_t s);
 hipError_t launch_project_bwd(const JobD& job, const ViewD* views_dev, const float* records,
                               const uint32_t* offsets, const float* g_pair, const uint8_t* alive,
                               uint32_t pair_capacity,

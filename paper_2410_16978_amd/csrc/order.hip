@@ -491,7 +491,7 @@ __device__ __forceinline__ void wave_lds_fence() {
 template <typename TT, int ROUNDS>
 __global__ void __launch_bounds__(kEmitThreads)
 k_emit(const ViewD* __restrict__ views, int n_views, uint32_t n_blk, const uint32_t* __restrict__ vals0,
-       const uint32_t* __restrict__ vals1, const uint32_t* __restrict__ unit, const uint2* __restrict__ boxes,
+       const uint32_t* __restrict__ vals1, const uint32_t* __restrict__ unit, const uint32_t* __restrict__ boxes, bool box4,
        uint32_t* __restrict__ counters, uint32_t cap, TT* __restrict__ tiles, uint32_t* __restrict__ recs,
        uint64_t* __restrict__ status, uint32_t* __restrict__ ticket) {
   __shared__ uint32_t s_bid, s_w[kEmitWaves];
@@ -528,8 +528,13 @@ k_emit(const ViewD* __restrict__ views, int n_views, uint32_t n_blk, const uint3
       rec[r] = 0xFFFFFFFFu;
     }
   }
+  if (box4) {  // (uniform; apart, so that a thread's loads are in flight together)
 #pragma unroll
-  for (int r = 0; r < ROUNDS; ++r) bx[r] = rec[r] != 0xFFFFFFFFu ? boxes[rec[r]] : make_uint2(0u, 0u);
+    for (int r = 0; r < ROUNDS; ++r) bx[r] = rec[r] != 0xFFFFFFFFu ? load_box(boxes, rec[r], true) : make_uint2(0u, 0u);
+  } else {
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) bx[r] = rec[r] != 0xFFFFFFFFu ? load_box(boxes, rec[r], false) : make_uint2(0u, 0u);
+  }
   const uint32_t tx = (uint32_t)V.tiles_x, toff = V.tile_off;
   uint32_t sum = 0;
 #pragma unroll
@@ -932,7 +937,7 @@ hipError_t order_pairs(const OrderBufs& o, hipStream_t s) {
   const auto emit = o.seq_tile == kEmitTile ? k_emit<TT, (int)kEmitTile / kEmitThreads>
                                             : k_emit<TT, (int)kEmitTileSmall / kEmitThreads>;
   hipLaunchKernelGGL(emit, dim3(o.seq_blocks), dim3(kEmitThreads), 0, s, o.views, o.n_views, o.seq_blocks, o.vals_a,
-                     o.vals_b, o.unit, o.boxes, o.counters, o.cap, tiles[0], recs[0], o.emit_status, &o.tickets[4]);
+                     o.vals_b, o.unit, o.boxes, o.box4, o.counters, o.cap, tiles[0], recs[0], o.emit_status, &o.tickets[4]);
   const auto pass = pair_step(o.cap) == kPairStep ? pair_pass<TT, (int)kPairStep / kPairThreads>
                                                   : pair_pass<TT, (int)kPairStepSmall / kPairThreads>;
   for (int p = 0; p < np; ++p)
@@ -1024,7 +1029,7 @@ k_debug_emit(OrderBufs o, uint32_t n_rec, const float* __restrict__ records, con
   const bool side = o.unit[2 * lead + 1] != 0;
   const uint32_t rec = V.rec_off + ((side ? o.vals_b : o.vals_a)[L.sort_off + p] - L.rec_off);
   const uint32_t key = (side ? o.keys_b : o.keys_a)[L.sort_off + p];
-  const uint2 bx = o.boxes[rec];
+  const uint2 bx = load_box(o.boxes, rec, o.box4);
   const uint32_t w = bx.y & 0xFFFFu, h = bx.y >> 16, tx = (uint32_t)V.tiles_x;
   if (w * h == 0) return;
   const uint32_t first = V.tile_off + (bx.x >> 16) * tx + (bx.x & 0xFFFFu);
@@ -1050,7 +1055,7 @@ k_debug_sorted(OrderBufs o, const TT* __restrict__ tiles, const uint32_t* __rest
   if (k >= K) return;
   const uint32_t tile = tiles[k], rec = recs[k];
   const ViewD& V = o.views[view_of_rec(o.views, o.n_views, rec)];
-  const uint2 bx = o.boxes[rec];
+  const uint2 bx = load_box(o.boxes, rec, o.box4);
   const uint32_t tx = (uint32_t)V.tiles_x, local = tile - V.tile_off;
   const uint32_t e = offsets[rec] + (local / tx - (bx.x >> 16)) * (bx.y & 0xFFFFu) + (local % tx - (bx.x & 0xFFFFu));
   keys_sorted[k] = ((uint64_t)tile << 32) | (e < o.cap ? depth_emit[e] : 0u);

@@ -208,7 +208,7 @@ __device__ __forceinline__ bool view_may_keep(const ViewD& V, uint32_t layer, fl
 template <int D, int F>
 __global__ void __launch_bounds__(256)
 k_project(JobD job, const ViewD* __restrict__ views, float* __restrict__ records,
-          uint32_t* __restrict__ n_tiles_out, uint4* __restrict__ tile_box, uint2* __restrict__ boxes,
+          uint32_t* __restrict__ n_tiles_out, uint4* __restrict__ tile_box, uint32_t* __restrict__ boxes, bool box4,
           uint32_t* __restrict__ sort_keys, uint32_t* __restrict__ counters) {
   constexpr int NC = (D + 1) * (D + 1);
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -387,7 +387,7 @@ k_project(JobD job, const ViewD* __restrict__ views, float* __restrict__ records
       kept |= 1u << jv;
     } while (false);
     if (boxes) {
-      boxes[r] = box;
+      store_box(boxes, r, box4, box);
       if (V.sort_mode == kSortOwn) sort_keys[V.sort_off + (uint32_t)i] = own_key;
     }
     n_tiles_out[r] = nt;
@@ -416,34 +416,34 @@ k_project(JobD job, const ViewD* __restrict__ views, float* __restrict__ records
 namespace {
 template <int F>
 void launch_project_fmt(const JobD& job, const ViewD* views_dev, float* records, uint32_t* n_tiles,
-                        uint4* tile_box, uint2* boxes, uint32_t* sort_keys, uint32_t* counters, hipStream_t s) {
+                        uint4* tile_box, uint32_t* boxes, bool box4, uint32_t* sort_keys, uint32_t* counters, hipStream_t s) {
   const dim3 grid(div_up((uint32_t)job.m.n, 256u)), block(256);
   switch (job.m.D) {
     case 0: hipLaunchKernelGGL((k_project<0, F>), grid, block, 0, s, job, views_dev, records, n_tiles, tile_box,
-                               boxes, sort_keys, counters); break;
+                               boxes, box4, sort_keys, counters); break;
     case 1: hipLaunchKernelGGL((k_project<1, F>), grid, block, 0, s, job, views_dev, records, n_tiles, tile_box,
-                               boxes, sort_keys, counters); break;
+                               boxes, box4, sort_keys, counters); break;
     case 2: hipLaunchKernelGGL((k_project<2, F>), grid, block, 0, s, job, views_dev, records, n_tiles, tile_box,
-                               boxes, sort_keys, counters); break;
+                               boxes, box4, sort_keys, counters); break;
     default: hipLaunchKernelGGL((k_project<3, F>), grid, block, 0, s, job, views_dev, records, n_tiles, tile_box,
-                                boxes, sort_keys, counters); break;
+                                boxes, box4, sort_keys, counters); break;
   }
 }
 }  // namespace
 
 hipError_t launch_project(const JobD& job, const ViewD* views_dev, float* records, uint32_t* n_tiles,
-                          uint4* tile_box, uint2* boxes, uint32_t* sort_keys, uint32_t* counters, hipStream_t s) {
+                          uint4* tile_box, uint32_t* boxes, bool box4, uint32_t* sort_keys, uint32_t* counters, hipStream_t s) {
   if (job.m.n <= 0 || job.n_views <= 0) return hipSuccess;
   switch (job.m.fmt) {
     case kFmtHalfPacked:
-      launch_project_fmt<kFmtHalfPacked>(job, views_dev, records, n_tiles, tile_box, boxes, sort_keys, counters, s);
+      launch_project_fmt<kFmtHalfPacked>(job, views_dev, records, n_tiles, tile_box, boxes, box4, sort_keys, counters, s);
       break;
     case kFmtHalfCodebook:
-      launch_project_fmt<kFmtHalfCodebook>(job, views_dev, records, n_tiles, tile_box, boxes, sort_keys, counters,
+      launch_project_fmt<kFmtHalfCodebook>(job, views_dev, records, n_tiles, tile_box, boxes, box4, sort_keys, counters,
                                            s);
       break;
     default:
-      launch_project_fmt<kFmtF32>(job, views_dev, records, n_tiles, tile_box, boxes, sort_keys, counters, s);
+      launch_project_fmt<kFmtF32>(job, views_dev, records, n_tiles, tile_box, boxes, box4, sort_keys, counters, s);
       break;
   }
   return hipGetLastError();

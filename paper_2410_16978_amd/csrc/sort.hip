@@ -1,4 +1,5 @@
-// Pair sort: (tile << 32 | depth bits) keys, stable, in two stages.
+// Pair sort of calls that do not order their records first: (tile << 32 |
+// depth bits) keys, stable, in two stages.
 //
 // 1. The tile digits: stable LSD radix passes over the whole pair array,
 //    8-bit digits, in the single-pass-per-digit style of OneSweep (Adinets
@@ -6,8 +7,8 @@
 //    read of the keys counts the digits of every pass, then each pass ranks
 //    a tile of keys per block and finds the tile's global digit offsets by
 //    decoupled look-back over the preceding tiles.
-// 2. The depth digits, per screen tile: one block per screen tile sorts its
-//    segment by the 32 depth bits with block-local LSD passes (in LDS when
+// 2. The depth digits, per screen tile: a wave, half a block or a block sorts
+//    a tile's segment by the 32 depth bits with block-local LSD passes (in LDS when
 //    the segment fits, else chunk by chunk through global memory), stable,
 //    so that equal depths keep emission order -- the same order a stable
 //    sort of the full 64-bit keys gives.  Its last pass writes the record id

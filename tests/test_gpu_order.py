@@ -14,7 +14,7 @@ from paper_2410_16978_amd import scenes
 
 pytestmark = pytest.mark.gpu
 
-SMALL_CAP, ORDER_CAP = 1 << 19, 1 << 21
+SMALL_CAP, ORDER_CAP = (3 << 16) - 1, 1 << 21
 
 
 @pytest.fixture(scope="module", autouse=True)
@@ -87,6 +87,22 @@ def test_order_first_equals_the_per_tile_path(n, n_views, W, H, ls, equal, mask)
         np.testing.assert_array_equal(ordered[k], v, err_msg=f"{k} of n={n}")
 
 
+def test_full_tiles_with_few_slots_a_record():
+    """Full tiles are ordered first from as many pair slots as records, the
+    boxes of all records then filling the emission array."""
+    from paper_2410_16978_amd import rasterizer as rz
+    cap = 3 << 16
+    for n in (cap, cap - 1, 150_000):
+        model = rz.to_device(_scene(n, seed=4, log_scale=-6.0))
+        cam = scenes.orbit_camera(scenes.random_direction(np.random.default_rng(4)), 120, 100)
+        vs = scenes.view_state(1, bg=(0.2, 0.1, 0.3))
+        K0, per_tile = _products(model, [cam], [vs], cap - 1)
+        K1, ordered = _products(model, [cam], [vs], cap)
+        assert K0 == K1 > 0
+        for k, v in per_tile.items():
+            np.testing.assert_array_equal(ordered[k], v, err_msg=f"{k} of n={n}")
+
+
 def test_order_first_matches_the_oracle(orc):
     from paper_2410_16978_amd import rasterizer as rz
     rng = np.random.default_rng(1)
@@ -120,6 +136,6 @@ def test_batch_cut_at_a_request():
     for q in range(len(reqs)):
         if fits[q]:
             continue
-        rgb, alpha, st = rz.rasterize_forward(model, reqs[q]["cams"], [vs], capacity=(1 << 21) - 1)
+        rgb, alpha, st = rz.rasterize_forward(model, reqs[q]["cams"], [vs], capacity=1_000_000)
         np.testing.assert_array_equal(out[q][0][0].cpu().numpy(), rgb[0].cpu().numpy())
         np.testing.assert_array_equal(out[q][1][0].cpu().numpy(), alpha[0].cpu().numpy())
