@@ -195,20 +195,15 @@ int tile_pass_end(uint64_t total_tiles) {
   return kDepthPasses + (b + 7) / 8;
 }
 
-// The views array goes to the device in the arguments of the clear launch
-// when it is small enough (one launch), else in upload launches of their own;
+// The views array goes to the device in the arguments of the clear launch as
+// far as they hold it (four views), the rest in upload launches of its own;
 // never by a copy from pageable host memory.
 hipError_t upload_views(ViewD* dst, const ViewD* src, int n_views, WordUpload& up, hipStream_t s) {
-  const size_t bytes = sizeof(ViewD) * (size_t)n_views;
-  up.dst = nullptr;
-  up.n = 0;
-  if (bytes <= sizeof(up.w)) {
-    up.dst = reinterpret_cast<uint32_t*>(dst);
-    up.n = (uint32_t)(bytes / 4);
-    std::memcpy(up.w, src, bytes);
-    return hipSuccess;
-  }
-  return launch_upload(reinterpret_cast<uint32_t*>(dst), src, bytes / 4, s);
+  const size_t words = sizeof(ViewD) / 4 * (size_t)n_views, here = std::min(words, sizeof(up.w) / 4);
+  up.dst = reinterpret_cast<uint32_t*>(dst);
+  up.n = (uint32_t)here;
+  std::memcpy(up.w, src, 4 * here);
+  return launch_upload(up.dst + here, reinterpret_cast<const uint32_t*>(src) + here, words - here, s);
 }
 
 hipError_t clear_workspace(const PipeBufs& b, uint32_t* counters, bool sticky_flags, uint32_t* ranges, size_t X,
