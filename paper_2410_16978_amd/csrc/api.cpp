@@ -148,7 +148,8 @@ size_t carve(Carver& c, PipeBufs& b, size_t n_views, size_t R, size_t P, size_t 
     b.sort_keys = c.take<uint32_t>(2 * std::max<size_t>(op.S, 1));
     b.sort_vals = c.take<uint32_t>(2 * std::max<size_t>(op.S, 1));
     b.pair_tiles = c.take<uint32_t>(2 * (std::max<size_t>(P, 1) + 4));
-    b.pair_counts = c.take<uint32_t>((X > 65536 ? (size_t)1 << kPairBits : 256) * ((size_t)pair_pass_blocks((uint32_t)P) + 1));
+    b.pair_counts = c.take<uint32_t>((X > 65536 ? (size_t)1 << kPairBits : 256) *
+                                     ((size_t)pair_pass_blocks((uint32_t)P) + 1));
     b.order_ctl_words = order_ctl_words(op, n_views);
     b.order_ctl = c.take<uint32_t>(b.order_ctl_words);
   } else {
