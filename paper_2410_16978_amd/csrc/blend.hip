@@ -169,10 +169,15 @@ __device__ __forceinline__ uint64_t lanes_below() {
 // reaches its block (bit `col` of the band's nibbles); each lane tests
 // one pair per round, a ballot compacts the hits.  Returns the
 // (wave-uniform) count.  Pairs not in the list cannot reach alpha >= 1/255 on
-// any of the wave's pixels, so skipping them changes nothing.
+// any of the wave's pixels, so skipping them changes nothing.  The list is
+// filled up to a multiple of four with its last pair: the walk reads four
+// entries a step, and a masked-out lane still multiplies its pair's colour by
+// zero, so that pair has to be one of the list (a slot beyond the batch's
+// pairs may hold the unwritten record of a culled Gaussian, NaN for all one
+// knows).
 __device__ __forceinline__ int wave_list(const uint8_t* nib, int col, uint8_t* list, int n) {
   const int lane = threadIdx.x & 63;
-  int cnt = 0;
+  int cnt = 0, end = 0;
 #pragma unroll
   for (int r = 0; r < kBatch / 64; ++r) {
     const int j = r * 64 + lane;
@@ -180,7 +185,9 @@ __device__ __forceinline__ int wave_list(const uint8_t* nib, int col, uint8_t* l
     const uint64_t m = __ballot(hit);
     if (hit) list[cnt + __popcll(m & lanes_below())] = (uint8_t)j;
     cnt += __popcll(m);
+    if (m != 0ull) end = r * 64 + 63 - (int)__builtin_clzll(m);
   }
+  if (lane < (-cnt & 3)) list[cnt + lane] = (uint8_t)end;
   __builtin_amdgcn_wave_barrier();
   return cnt;
 }
@@ -451,7 +458,7 @@ __global__ void __launch_bounds__(256, 8) k_blend_fwd(FwdArgs args) {
       const int cnt = live ? wave_list(nib, wave, list, n) : 0;
       int t0 = 0;
       for (; t0 < cnt && live != 0ull; t0 += 4) {
-        // past the list's end an old entry is read and masked out
+        // past the list's end its last pair is read again and masked out
         const int j = (int)list[t0 + slot];
         const float4 A = L.a[j], B = L.b[j];
         const float cb = L.c[j];
