@@ -192,7 +192,8 @@ typedef struct {
  *                             count (as uint32; 0 = culled).  Record
  *                             r = v * n + i.
  *   offsets     uint32[R+1]   first pair (emission order) of each record;
- *                             offsets[R] = pair count
+ *                             offsets[R] = pair count (2^32 - 1: that or
+ *                             more)
  *   pair_vals   uint32[2][P]  sorted record ids; which half holds the result
  *                             is recorded on the device in *sort_sel.  A
  *                             forward leaves in the other half, as

@@ -791,7 +791,8 @@ k_blend_bwd(const ViewD* __restrict__ views, int n_views, const float* __restric
           emit = pair_emit[start + tid];
         } else if (my_rec < n_rec) {
           const uint2 bx = load_box(boxes, my_rec, box4);
-          emit = offsets[my_rec] + ((uint32_t)ty - (bx.x >> 16)) * (bx.y & 0xFFFFu) + ((uint32_t)tx - (bx.x & 0xFFFFu));
+          const uint32_t e0 = offsets[my_rec];
+          if (e0 < cap) emit = e0 + ((uint32_t)ty - (bx.x >> 16)) * (bx.y & 0xFFFFu) + ((uint32_t)tx - (bx.x & 0xFFFFu));
         }
       }
       s_emit[tid] = emit;

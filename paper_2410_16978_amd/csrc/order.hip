@@ -499,8 +499,8 @@ k_emit(const ViewD* __restrict__ views, int n_views, uint32_t n_blk, const uint3
        const uint32_t* __restrict__ vals1, const uint32_t* __restrict__ unit, const uint32_t* __restrict__ boxes, bool box4,
        uint32_t* __restrict__ counters, uint32_t cap, TT* __restrict__ tiles, uint32_t* __restrict__ recs,
        uint64_t* __restrict__ status, uint32_t* __restrict__ ticket) {
-  __shared__ uint32_t s_bid, s_w[kEmitWaves];
-  __shared__ uint64_t s_excl;
+  __shared__ uint32_t s_bid;
+  __shared__ uint64_t s_excl, s_w[kEmitWaves];  // (a block's 4096 records of 2^20 tiles each pass 2^32)
   // of a wave's records: first pair among its 64's, first tile less that, box width, record
   __shared__ uint4 s_rec[kEmitWaves][ROUNDS * 64];
   __shared__ uint32_t s_mark[kEmitWaves][64];  // 1 + the index of the record that starts at each of 64 pairs
@@ -541,7 +541,7 @@ k_emit(const ViewD* __restrict__ views, int n_views, uint32_t n_blk, const uint3
     for (int r = 0; r < ROUNDS; ++r) bx[r] = rec[r] != 0xFFFFFFFFu ? load_box(boxes, rec[r], false) : make_uint2(0u, 0u);
   }
   const uint32_t tx = (uint32_t)V.tiles_x, toff = V.tile_off;
-  uint32_t sum = 0;
+  uint64_t sum = 0;
 #pragma unroll
   for (int r = 0; r < ROUNDS; ++r) {
     const uint32_t nt = (bx[r].y & 0xFFFFu) * (bx[r].y >> 16);
@@ -555,7 +555,7 @@ k_emit(const ViewD* __restrict__ views, int n_views, uint32_t n_blk, const uint3
   if (lane == 0) s_w[wave] = sum;
   __syncthreads();
   if (wave == 0) {
-    uint32_t total = 0;
+    uint64_t total = 0;
 #pragma unroll
     for (int w = 0; w < kEmitWaves; ++w) total += s_w[w];
     if (lane == 0)

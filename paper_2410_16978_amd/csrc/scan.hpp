@@ -6,17 +6,19 @@
 
 namespace gsr {
 
-// Block-wide exclusive scan of one value per thread.
+// Block-wide exclusive scan of one value below 2^38 per thread.  The wave
+// scans it in two parts of 26 and 12 bits, whose sums stay in 32.
 template <int THREADS>
-__device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t x, uint32_t* lds_waves, uint32_t* total) {
+__device__ __forceinline__ uint64_t block_exclusive_scan(uint64_t x, uint64_t* lds_waves, uint64_t* total) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const uint32_t inc = wave_scan_add(x);
+  const uint32_t lo = wave_scan_add((uint32_t)x & ((1u << 26) - 1u)), hi = wave_scan_add((uint32_t)(x >> 26));
+  const uint64_t inc = (uint64_t)lo + ((uint64_t)hi << 26);
   if (lane == 63) lds_waves[wave] = inc;
   __syncthreads();
-  uint32_t wave_off = 0, tot = 0;
+  uint64_t wave_off = 0, tot = 0;
 #pragma unroll
   for (int w = 0; w < THREADS / 64; ++w) {
-    const uint32_t c = lds_waves[w];
+    const uint64_t c = lds_waves[w];
     if (w < wave) wave_off += c;
     tot += c;
   }
@@ -30,7 +32,9 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t x, uint32_t* l
 // tile's total, and the first wave looks back over 64 predecessors at a time
 // for the nearest inclusive prefix.  Status words: flag in the top 2 bits,
 // 62-bit value.  The last tile writes the total K and the capacity check to
-// counters.
+// counters.  Sums are of 64 bits (a block's 32768 records of 2^17 tiles each
+// pass 2^32); an offset or a count beyond 32 bits is written as 2^32 - 1,
+// which is beyond every capacity.
 constexpr uint64_t kScanAgg = 1ull << 62;
 constexpr uint64_t kScanIncl = 2ull << 62;
 constexpr uint64_t kScanValue = (1ull << 62) - 1;
@@ -41,7 +45,8 @@ template <int THREADS, int ITEMS>
 __device__ __forceinline__ void scan_block(const uint32_t* __restrict__ in, uint32_t n, uint32_t* __restrict__ out,
                                            uint64_t* __restrict__ status, uint32_t* __restrict__ ticket,
                                            uint32_t* __restrict__ counters, uint32_t pair_capacity, uint32_t nb) {
-  __shared__ uint32_t lds[THREADS / 64];
+  static_assert(ITEMS <= 64, "a thread's sum stays below 2^38");
+  __shared__ uint64_t lds[THREADS / 64];
   __shared__ uint32_t s_bid;
   __shared__ uint64_t s_excl;
   if (threadIdx.x == 0) s_bid = atomicAdd(ticket, 1u);
@@ -64,11 +69,11 @@ __device__ __forceinline__ void scan_block(const uint32_t* __restrict__ in, uint
 #pragma unroll
     for (int k = 0; k < ITEMS; ++k) v[k] = (base + k < n) ? in[base + k] : 0u;
   }
-  uint32_t sum = 0;
+  uint64_t sum = 0;
 #pragma unroll
   for (int k = 0; k < ITEMS; ++k) sum += v[k];
-  uint32_t total;
-  const uint32_t local = block_exclusive_scan<THREADS>(sum, lds, &total);
+  uint64_t total;
+  const uint64_t local = block_exclusive_scan<THREADS>(sum, lds, &total);
   if (threadIdx.x < 64) {
     const int lane = threadIdx.x;
     if (lane == 0)
@@ -117,8 +122,9 @@ __device__ __forceinline__ void scan_block(const uint32_t* __restrict__ in, uint
     }
   }
   __syncthreads();
-  uint32_t run = (uint32_t)s_excl + local;
-  if (base + ITEMS <= n && (reinterpret_cast<uintptr_t>(out) & 15) == 0) {
+  const uint64_t first = s_excl + local;
+  if (base + ITEMS <= n && (reinterpret_cast<uintptr_t>(out) & 15) == 0 && (first + sum) >> 32 == 0) {
+    uint32_t run = (uint32_t)first;
     uint4* out4 = reinterpret_cast<uint4*>(out + base);
 #pragma unroll
     for (int k = 0; k < ITEMS / 4; ++k) {
@@ -134,14 +140,15 @@ __device__ __forceinline__ void scan_block(const uint32_t* __restrict__ in, uint
       out4[k] = q;
     }
   } else {
+    uint64_t run = first;
 #pragma unroll
     for (int k = 0; k < ITEMS; ++k) {
-      if (base + k < n) out[base + k] = run;
+      if (base + k < n) out[base + k] = (uint32_t)min(run, (uint64_t)0xFFFFFFFFull);
       run += v[k];
     }
+    // out[n] = total, written by the thread that owns the end
+    if (base <= n && n < base + ITEMS) out[n] = (uint32_t)min(run, (uint64_t)0xFFFFFFFFull);
   }
-  // out[n] = total, written by the thread that owns the end
-  if (base <= n && n < base + ITEMS) out[n] = run;
 }
 
 }  // namespace gsr
