@@ -1,5 +1,6 @@
 """What a call reports of its pair count: totals beyond 32 bits are an overflow
-of the capacity, not counted modulo 2^32."""
+of the capacity, not counted modulo 2^32, and a batch marks exactly the
+requests whose pairs end beyond the capacity."""
 import numpy as np
 import pytest
 
@@ -57,3 +58,25 @@ def test_batch_total_beyond_32_bits(capacity):
             {"model": 0, "cams": [cam], "view": scenes.view_state()}]
     _, status, _ = rz.render_batch([model, small], reqs, capacity)
     assert status.cpu().tolist() == [0, rz.GSR_ENOSPACE]
+
+
+@pytest.mark.parametrize("capacity", [1 << 21, 1 << 18])  # records ordered first, pairs sorted by tile
+def test_batch_status_is_the_running_sum(capacity):
+    from paper_2410_16978_amd import rasterizer as rz
+    rng = np.random.default_rng(5)
+    n = 30000 if capacity > 1 << 20 else 9000
+    sc = scenes.shell_scene(n // 2, 2, 1, seed=5, log_scale_mu=-2.5, log_scale_sigma=0.5)
+    model, vs = rz.to_device(sc), scenes.view_state(3, bg=(0.1, 0.2, 0.3))
+    reqs, ends = [], []
+    for q in range(6):
+        W, H = ((400, 320), (160, 90), (333, 200))[q % 3]
+        cams = [scenes.orbit_camera(scenes.random_direction(rng), W, H)]
+        reqs.append({"model": 0, "cams": cams, "view": vs})
+        ends.append((ends[-1] if ends else 0) + rz.rasterize_forward(model, cams, [vs])[2].n_pairs)
+    assert ends[0] <= capacity < ends[-1], ends
+    _, status, _ = rz.render_batch([model], reqs, capacity)
+    assert status.cpu().tolist() == [0 if e <= capacity else rz.GSR_ENOSPACE for e in ends], ends
+    exact = ends[2]  # a capacity that a request's pairs fill to the last slot, and one less
+    for cap in (exact, exact - 1):
+        _, status, _ = rz.render_batch([model], reqs, cap)
+        assert status.cpu().tolist() == [0 if e <= cap else rz.GSR_ENOSPACE for e in ends], (cap, ends)
