@@ -300,9 +300,13 @@ gsr_status gsr_timer_read(gsr_timer* t, float* ms /* [GSR_N_STAGES] */, uint32_t
 
 /* Bytes of scratch workspace a forward or backward of n_views views of a
  * model with n Gaussians at width x height needs, for a pair capacity of
- * pair_capacity; shared_order != 0 adds the buffers of a forward with a
- * shared depth order (gsr_view_state.sort_shared: about 24 B per Gaussian
- * and 24 B per record more).  Returns 0 on bad arguments. */
+ * pair_capacity; shared_order != 0: also a forward with a shared depth order
+ * (gsr_view_state.sort_shared), which needs more only where the records
+ * outnumber the pair slots several times.  A call takes one of two paths by
+ * its sizes; the size is the larger path's, and it never shrinks as an
+ * argument grows, so a workspace sized for a call holds every smaller one.  A
+ * call on less is GSR_ENOSPACE whichever path it would take.  Returns 0 on bad
+ * arguments. */
 size_t gsr_workspace_size(int32_t n, int32_t n_views, int32_t width, int32_t height,
                           uint32_t pair_capacity, int32_t shared_order);
 
@@ -417,7 +421,9 @@ typedef struct {
 } gsr_request;
 
 /* Bytes of workspace gsr_render_batch needs for these requests at a total
- * pair capacity of pair_capacity (0 on bad arguments). */
+ * pair capacity of pair_capacity (0 on bad arguments).  At most the sum of
+ * the sizes of batches holding the requests one by one at capacities of that
+ * sum, and no less for more requests or pair slots. */
 size_t gsr_batch_workspace_size(const gsr_model* models, int32_t n_models, const gsr_request* reqs,
                                 int32_t n_req, uint32_t pair_capacity);
 

@@ -99,6 +99,7 @@ struct OrderPlan {
   size_t rec_blocks = 0, seq_blocks = 0;
   uint32_t rec_tile = 0, seq_tile = 0;  // rec_tile, emit_tile of the call's records
   bool small = true;       // every unit has at most kRecSmall records
+  bool bound = false;      // for workspace_bytes: the largest sizes of either path's buffers
 };
 
 // Whether a call orders its records before it pairs them (one that shares an
@@ -148,8 +149,11 @@ size_t carve(Carver& c, PipeBufs& b, size_t n_views, size_t R, size_t P, size_t 
     b.sort_keys = c.take<uint32_t>(2 * std::max<size_t>(op.S, 1));
     b.sort_vals = c.take<uint32_t>(2 * std::max<size_t>(op.S, 1));
     b.pair_tiles = c.take<uint32_t>(2 * (std::max<size_t>(P, 1) + 4));
-    b.pair_counts = c.take<uint32_t>((X > 65536 ? (size_t)1 << kPairBits : 256) *
-                                     ((size_t)pair_pass_blocks((uint32_t)P) + 1));
+    b.pair_counts =
+        op.bound ? c.take<uint32_t>(((size_t)1 << kPairBits) *
+                                    (std::min<size_t>(P / kPairStepSmall + 1, kPairBlocks) + 1))
+                 : c.take<uint32_t>((X > 65536 ? (size_t)1 << kPairBits : 256) *
+                                    ((size_t)pair_pass_blocks((uint32_t)P) + 1));
     b.order_ctl_words = order_ctl_words(op, n_views);
     b.order_ctl = c.take<uint32_t>(b.order_ctl_words);
   } else {
@@ -157,8 +161,10 @@ size_t carve(Carver& c, PipeBufs& b, size_t n_views, size_t R, size_t P, size_t 
     b.keys_a = c.take<uint64_t>(std::max<size_t>(P, 1));
     b.keys_b = c.take<uint64_t>(std::max<size_t>(P, 1));
     b.rec_of = c.take<uint32_t>(std::max<size_t>(P, 1));
-    b.status = c.take<uint32_t>(std::max(sort_status_words((uint32_t)P),
-                                          tile_sort12(X, (uint32_t)P) ? tile_sort12_status_words((uint32_t)P) : 0));
+    b.status = c.take<uint32_t>(std::max(
+        sort_status_words((uint32_t)P),
+        op.bound || tile_sort12(X, (uint32_t)P)
+            ? tile_sort12_status_words((uint32_t)std::min<size_t>(P, kT12MaxPairs)) : 0));
   }
   b.class_list = c.take<uint32_t>(kTileClasses * std::max<size_t>(X, 1));
   if (backward) {
@@ -178,6 +184,35 @@ size_t carve(Carver& c, PipeBufs& b, size_t n_views, size_t R, size_t P, size_t 
     b.sel = c.take<uint32_t>(1);
   }
   return c.off + kAlign;
+}
+
+// The order-first plan of the largest buffers: R records in `rec_blocks`
+// short pass blocks, own_boxes if any call of the kind keeps its boxes in the
+// workspace.
+OrderPlan bound_plan(size_t R, size_t rec_blocks, size_t seq_blocks, bool own_boxes) {
+  OrderPlan op;
+  op.on = op.bound = true;
+  op.own_boxes = own_boxes;
+  op.S = R;
+  op.rec_blocks = rec_blocks;
+  op.seq_blocks = seq_blocks;
+  return op;
+}
+
+// Bytes a workspace of a call has to have.  Which path a call takes turns on
+// its sizes, and a pair slot takes 8 bytes on one and 20 or more on the other;
+// so that a workspace sized for a call also holds every smaller one, and a
+// batch needs no more than the sum of its requests alone (what a server
+// budgets), the size is that of the larger layout, with buffers that only
+// grow with the sizes, whichever path the call takes.
+size_t workspace_bytes(size_t n_views, size_t R, size_t P, size_t n_req, bool batch, size_t X,
+                       const OrderPlan& bound) {
+  Carver by_tile(nullptr), by_record(nullptr);
+  PipeBufs b;
+  OrderPlan off;
+  off.bound = true;
+  return std::max(carve(by_tile, b, n_views, R, P, n_req, batch, X, !batch, off),
+                  carve(by_record, b, n_views, R, P, n_req, batch, X, !batch, bound));
 }
 
 // One launch zeroes everything a call expects to start at zero: the sort
@@ -360,6 +395,14 @@ OrderPlan single_plan(int64_t n, int n_views, int32_t width, int32_t height, uin
   return op;
 }
 
+// workspace_bytes of such a call; shared: of a forward that shares an order too.
+size_t single_workspace_bytes(int64_t n, int n_views, int32_t width, int32_t height, uint32_t P, bool shared) {
+  const size_t X = (size_t)n_views * div_up((uint32_t)width, (uint32_t)kTile) * div_up((uint32_t)height, (uint32_t)kTile);
+  return workspace_bytes((size_t)n_views, (size_t)n * n_views, P, 0, false, X,
+                         bound_plan((size_t)n * n_views, (size_t)n_views * div_up((uint32_t)n, kRecTileSmall),
+                                    (size_t)n_views * div_up((uint32_t)n, kEmitTileSmall), shared));
+}
+
 uint32_t tiles_of(const gsr_camera& c) {
   return div_up((uint32_t)c.width, (uint32_t)kTile) * div_up((uint32_t)c.height, (uint32_t)kTile);
 }
@@ -538,15 +581,7 @@ uint32_t gsr_batch_capacity(uint32_t pair_capacity, uint32_t total_tiles) {
 size_t gsr_workspace_size(int32_t n, int32_t n_views, int32_t width, int32_t height, uint32_t pair_capacity,
                           int32_t shared_order) {
   if (n < 0 || n_views <= 0 || width <= 0 || height <= 0 || pair_capacity >= (1u << 30)) return 0;
-  Carver c(nullptr);
-  PipeBufs b;
-  const size_t X = (size_t)n_views * (size_t)((width + kTile - 1) / kTile) * (size_t)((height + kTile - 1) / kTile);
-  const size_t own = carve(c, b, (size_t)n_views, (size_t)n * n_views, pair_capacity, 0, false, X, true,
-                           single_plan(n, n_views, width, height, pair_capacity, false));
-  if (!shared_order) return own;
-  Carver cs(nullptr);
-  return std::max(own, carve(cs, b, (size_t)n_views, (size_t)n * n_views, pair_capacity, 0, false, X, true,
-                             single_plan(n, n_views, width, height, pair_capacity, true)));
+  return single_workspace_bytes(n, n_views, width, height, pair_capacity, shared_order != 0);
 }
 
 gsr_status gsr_adam_step(int32_t n, int32_t sh_degree, uint32_t trainable_layers, const uint8_t* layer,
@@ -614,6 +649,7 @@ gsr_status forward_impl(const gsr_model* model, int32_t n_views, const gsr_camer
   // one depth order for all views: by the depth in views[0].sort_cam
   const bool shared = views[0].sort_shared != 0;
   OrderPlan op = single_plan(n, n_views, W, H, P, shared);
+  if (backward_layout && single_workspace_bytes(n, n_views, W, H, P, shared) > ws_bytes) return GSR_ENOSPACE;
   Carver c(ws);
   PipeBufs b;
   if (carve(c, b, n_views, R, P, 0, false, X, backward_layout, op) > ws_bytes) return GSR_ENOSPACE;
@@ -854,7 +890,8 @@ gsr_status gsr_rasterize_backward(const gsr_model* model, int32_t n_views, const
   Carver c(ws);
   PipeBufs b;
   const OrderPlan op = single_plan(n, n_views, W, H, P, false);
-  if (carve(c, b, n_views, R, P, 0, false, X, true, op) > ws_bytes)
+  if (single_workspace_bytes(n, n_views, W, H, P, false) > ws_bytes ||
+      carve(c, b, n_views, R, P, 0, false, X, true, op) > ws_bytes)
     return GSR_ENOSPACE;
   std::vector<ViewD> hv(n_views);
   std::vector<int> ids(n_views);
@@ -919,6 +956,7 @@ struct BatchPlan {
   std::vector<ViewD> views;
   std::vector<uint32_t> req_rec;
   uint64_t R = 0, X = 0;
+  uint64_t rec_blocks = 0, seq_blocks = 0;  // of short blocks (bound_plan)
   // with any request sharing one depth order between its eyes, or where
   // order_first says so, the records are ordered before they are paired
   OrderPlan order;
@@ -945,6 +983,8 @@ bool plan_batch(const gsr_model* models, int32_t n_models, const gsr_request* re
       d.alpha = r.alpha[e];
       bp.views.push_back(d);
       bp.R += (uint64_t)models[r.model].n;
+      bp.rec_blocks += div_up((uint32_t)models[r.model].n, kRecTileSmall);
+      bp.seq_blocks += div_up((uint32_t)models[r.model].n, kEmitTileSmall);
       bp.X += tiles_of(r.cam[e]);
     }
   }
@@ -985,15 +1025,18 @@ bool plan_batch(const gsr_model* models, int32_t n_models, const gsr_request* re
   return true;
 }
 
+size_t batch_workspace_bytes(const BatchPlan& bp, int32_t n_req, uint32_t P) {
+  return workspace_bytes(bp.views.size(), bp.R, P, n_req, true, bp.X,
+                         bound_plan(bp.R, bp.rec_blocks, bp.seq_blocks, true));
+}
+
 }  // namespace
 
 size_t gsr_batch_workspace_size(const gsr_model* models, int32_t n_models, const gsr_request* reqs, int32_t n_req,
                                 uint32_t pair_capacity) {
   BatchPlan bp;
   if (!plan_batch(models, n_models, reqs, n_req, pair_capacity, bp) || pair_capacity >= (1u << 30)) return 0;
-  Carver c(nullptr);
-  PipeBufs b;
-  return carve(c, b, bp.views.size(), bp.R, pair_capacity, n_req, true, bp.X, false, bp.order);
+  return batch_workspace_bytes(bp, n_req, pair_capacity);
 }
 
 gsr_status gsr_render_batch(const gsr_model* models, int32_t n_models, const gsr_request* reqs, int32_t n_req,
@@ -1008,7 +1051,9 @@ gsr_status gsr_render_batch(const gsr_model* models, int32_t n_models, const gsr
   const int n_views = (int)bp.views.size();
   Carver c(ws);
   PipeBufs b;
-  if (carve(c, b, n_views, R, P, n_req, true, bp.X, false, bp.order) > ws_bytes) return GSR_ENOSPACE;
+  if (batch_workspace_bytes(bp, n_req, P) > ws_bytes ||
+      carve(c, b, n_views, R, P, n_req, true, bp.X, false, bp.order) > ws_bytes)
+    return GSR_ENOSPACE;
   WordUpload up;
   HIP_TRY(upload_views(b.views, bp.views.data(), n_views, up, s));
   HIP_TRY(launch_upload(b.req_rec, bp.req_rec.data(), (size_t)n_req + 1, s));
