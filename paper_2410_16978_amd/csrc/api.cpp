@@ -833,17 +833,30 @@ gsr_status gsr_rasterize_forward_noalloc(const gsr_model* model, int32_t n_views
   if (!single_view_args_ok(model, n_views, cams, views) || !state || !rgb || !alpha || !state_ok(state))
     return GSR_EINVAL;
   const uint64_t X = (uint64_t)tiles_of(cams[0]) * (uint64_t)n_views;
-  // the limit holds for the per-tile path's scratch (a shared order: 24 bytes
-  // a Gaussian and a record more), whichever path the call takes: the
-  // order-first one needs less, and a size is refused or not by one rule
+  // One rule refuses a size or not, whichever path the call takes: the
+  // per-tile path's scratch and, of a shared order, what one takes that sorts
+  // the Gaussians and pairs each view in their order (two buffers of keys and
+  // values, the sort's words, and the records' sequence).  The order-first
+  // path needs less.
   const bool shared = views[0].sort_shared != 0;
   const size_t n = (size_t)model->n, R = n * (size_t)n_views;
   const uint32_t P = state->pair_capacity;
-  Carver per_tile(nullptr), own(nullptr);
+  Carver rule(nullptr), own(nullptr);
   PipeBufs b;
-  const size_t need =
-      std::max(carve(per_tile, b, (size_t)n_views, R, P, 0, false, X, false, OrderPlan{}) + (shared ? 24 * (n + R) : 0),
-               carve(own, b, (size_t)n_views, R, P, 0, false, X, false, single_plan(model->n, n_views, cams[0].width, cams[0].height, P, shared)));
+  size_t need = carve(rule, b, (size_t)n_views, R, P, 0, false, X, false, OrderPlan{});
+  if (shared) {
+    const size_t keys = std::max<size_t>(n, 1), recs = std::max<size_t>(R, 1);
+    for (int half = 0; half < 2; ++half) rule.take<uint64_t>(keys);
+    for (int half = 0; half < 2; ++half) rule.take<uint32_t>(keys);
+    rule.take<SortCtl>(1);
+    rule.take<uint32_t>(sort_status_words((uint32_t)keys));
+    rule.take<uint32_t>(4);
+    for (int words = 0; words < 2; ++words) rule.take<uint32_t>(recs);
+    rule.take<uint4>(recs);
+    need = rule.off + kAlign;
+  }
+  need = std::max(need, carve(own, b, (size_t)n_views, R, P, 0, false, X, false,
+                              single_plan(model->n, n_views, cams[0].width, cams[0].height, P, shared)));
   if (need > kNoallocScratchBytes) return GSR_ENOSPACE;
   void* ws = nullptr;
   const gsr_status st = scratch_of_current_device(&ws);
