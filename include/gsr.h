@@ -205,10 +205,11 @@ typedef struct {
  *   sort_sel    uint32[1]
  *   pair_emit   uint32[P]     emission index of each sorted pair; or, in
  *                             calls that order their records before pairing
- *                             them (P >= 2 R, and P >= 2^20 with more than
- *                             4096 tiles or P >= 2^21; with full tiles, P >=
- *                             R, and P >= 2^20 and 768 X or P >= 3 * 2^16 and
- *                             2048 X), each record's tile box,
+ *                             them (P >= 2 R and P >= 2^20 with more than
+ *                             4096 tiles, else P >= 2^21; and full tiles,
+ *                             P >= 3 * 2^16 and P >= 2048 X, with P >= R where
+ *                             the views have at most 255 tiles a side and
+ *                             P >= 2 R where not), each record's tile box,
  *                             from which the backward has the index: its
  *                             first tile and its size in its view (0:
  *                             culled), uint32[R] x | y << 8 | width << 16 |

@@ -115,19 +115,24 @@ struct OrderPlan {
 // With many pairs a tile the per-tile sort has few blocks at work, and a tile
 // beyond 8192 pairs passes through global memory in one of them; how uneven
 // the tiles are is not known here.  From 2048 pairs a tile on, order-first is
-// ahead even of evenly filled tiles (158 / 145 at 200 tiles, 223 / 172 at 72),
-// and far ahead of layered shells (286 / 183 at 100 tiles of 1815 pairs on
-// average, 2606 / 1106 at 64 of 30k); at 1200 to 1600 evenly filled ones are
-// faster sorted by tile (113 / 157), shells are not (299 / 219).  Between 1M
-// and 2M pairs it takes 768 a tile (440 / 359 at 985; 175 / 183 at 392; the
-// evenly filled tiles of a narrow view, 1015 each at 2.1M pairs, 204 / 220).
+// ahead even of evenly filled tiles (158 / 145 at 200 tiles, 223 / 172 at 72;
+// level at 1024 tiles, 169 / 201 at 2413 a tile and 343 / 321 at 6035), and
+// far ahead of layered shells (286 / 183 at 100 tiles of 1815 pairs on
+// average, 2606 / 1106 at 64 of 30k).  Below, evenly filled tiles are faster
+// sorted by tile (122 / 167 at 1024 tiles of 1208; a step of four views, 676
+// tiles of 1530, 298 / 345), shells are not (291 / 214 at 1024 of 1409): one
+// would lose more than it did before this path was there, the other only
+// stays what it was, so these are sorted by tile.  Up to 4096 tiles the same
+// holds above 2^21 pairs in a smaller measure (2500 tiles, evenly filled 158 /
+// 190 at 2.2M and 352 / 338 at 11M; shells 254 / 221 at 2.1M, 741 / 493 at
+// 7.9M).
 //
 // Below two pair slots a record the record passes outweigh the pairs, unless
 // tiles are that full; and the boxes of all records, which the backward reads
 // from the pair_emit array, fit there if they are of four bytes.
 constexpr uint32_t kOrderMinPairs = 1u << 20, kOrderMinPairsFull = 3u << 16;
 bool order_first(uint64_t X, uint32_t P, uint64_t R, bool box4) {
-  const bool full = (P >= kOrderMinPairsFull && P >= 2048 * X) || (P >= kOrderMinPairs && P >= 768 * X);
+  const bool full = P >= kOrderMinPairsFull && P >= 2048 * X;
   if (P < (full && box4 ? R : 2 * R)) return false;
   return full || P >= (tile_sort12(X, P) ? 2 * kOrderMinPairs : kOrderMinPairs);
 }
