@@ -209,7 +209,9 @@ typedef struct {
  *                             4096 tiles, else P >= 2^21; and full tiles,
  *                             P >= 3 * 2^16 and P >= 2048 X, with P >= R where
  *                             the views have at most 255 tiles a side and
- *                             P >= 2 R where not), each record's tile box,
+ *                             P >= 2 R where not; also if such a call reads
+ *                             its pair count back, finds too few pairs and
+ *                             sorts them by tile), each record's tile box,
  *                             from which the backward has the index: its
  *                             first tile and its size in its view (0:
  *                             culled), uint32[R] x | y << 8 | width << 16 |

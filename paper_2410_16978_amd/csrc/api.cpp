@@ -115,10 +115,10 @@ struct OrderPlan {
 // With many pairs a tile the per-tile sort has few blocks at work, and a tile
 // beyond 8192 pairs passes through global memory in one of them; how uneven
 // the tiles are is not known here.  From 2048 pairs a tile on, order-first is
-// ahead even of evenly filled tiles (158 / 145 at 200 tiles, 223 / 172 at 72;
-// level at 1024 tiles, 169 / 201 at 2413 a tile and 343 / 321 at 6035), and
-// far ahead of layered shells (286 / 183 at 100 tiles of 1815 pairs on
-// average, 2606 / 1106 at 64 of 30k).  Below, evenly filled tiles are faster
+// ahead of few evenly filled tiles (158 / 145 at 200, 223 / 172 at 72; of more
+// only well beyond, at 1024 169 / 201 with 2413 a tile and 343 / 321 with
+// 6035) and far ahead of layered shells (286 / 183 at 100 tiles of 1815 pairs
+// on average, 2606 / 1106 at 64 of 30k).  Below, evenly filled tiles are faster
 // sorted by tile (122 / 167 at 1024 tiles of 1208; a step of four views, 676
 // tiles of 1530, 298 / 345), shells are not (291 / 214 at 1024 of 1409): one
 // would lose more than it did before this path was there, the other only
@@ -130,11 +130,28 @@ struct OrderPlan {
 // Below two pair slots a record the record passes outweigh the pairs, unless
 // tiles are that full; and the boxes of all records, which the backward reads
 // from the pair_emit array, fit there if they are of four bytes.
-constexpr uint32_t kOrderMinPairs = 1u << 20, kOrderMinPairsFull = 3u << 16;
+//
+// All of that is in pairs, and only a call that reads its pair count back knows
+// them before it orders anything; any other goes by its slots, as the caller
+// sized them.  One that reads it starts by its slots too and turns to the
+// per-tile path if the pairs do not pay: the default capacity of four slots a
+// Gaussian and view is often a quarter filled.  One layer of four shown, wall
+// time of such a call before there were two paths / ordered first / turned:
+// 186 / 215 / 171 at 531k pairs and 231 / 265 / 206 at 1.0M of 800 x 800, 256
+// / 286 / 216 at 695k of 512 x 512, 173 / 188 / 142 at 178k of 400 x 400.  Up
+// to 256 tiles, one a compute unit, it stays: the largest tile bounds the
+// per-tile sort, and ordering first was ahead at any filling (262 / 238 / 207
+// for one layer of four at 256 x 256 and 256k pairs, but 1975 / 1103 / 1397
+// for the innermost of eight, 472k pairs in few of the tiles).
+constexpr uint32_t kOrderMinPairs = 1u << 20, kOrderMinPairsFull = 3u << 16, kOrderFewTiles = 256;
+bool order_full(uint64_t X, uint64_t pairs) {
+  return pairs >= kOrderMinPairsFull && pairs >= 2048 * X;
+}
+bool order_pays(uint64_t X, uint32_t pairs) {
+  return order_full(X, pairs) || pairs >= (tile_sort12(X, pairs) ? 2 * kOrderMinPairs : kOrderMinPairs);
+}
 bool order_first(uint64_t X, uint32_t P, uint64_t R, bool box4) {
-  const bool full = P >= kOrderMinPairsFull && P >= 2048 * X;
-  if (P < (full && box4 ? R : 2 * R)) return false;
-  return full || P >= (tile_sort12(X, P) ? 2 * kOrderMinPairs : kOrderMinPairs);
+  return P >= (order_full(X, P) && box4 ? R : 2 * R) && order_pays(X, P);
 }
 
 // Words of the order-first path that are zero on entry.
@@ -162,7 +179,7 @@ size_t carve(Carver& c, PipeBufs& b, size_t n_views, size_t R, size_t P, size_t 
     b.order_ctl_words = order_ctl_words(op, n_views);
     b.order_ctl = c.take<uint32_t>(b.order_ctl_words);
   } else {
-    b.tile_box = c.take<uint4>(std::max<size_t>(R, 1));
+    b.tile_box = c.take<uint4>(std::max<size_t>(R, 1));  // (where sort_keys is: forward_impl may turn)
     b.keys_a = c.take<uint64_t>(std::max<size_t>(P, 1));
     b.keys_b = c.take<uint64_t>(std::max<size_t>(P, 1));
     b.rec_of = c.take<uint32_t>(std::max<size_t>(P, 1));
@@ -247,6 +264,16 @@ hipError_t upload_views(ViewD* dst, const ViewD* src, int n_views, WordUpload& u
   return launch_upload(up.dst + here, reinterpret_cast<const uint32_t*>(src) + here, words - here, s);
 }
 
+// The look-back words of the per-tile path's radix passes, as the next range
+// of a clear.  (The one-pass grouping's block counts are written before they
+// are read.)
+void tile_pass_words(const PipeBufs& b, size_t X, uint32_t P, ClearSet& cs) {
+  const size_t stride = sort_status_stride(P);
+  const int pb = kDepthPasses, pe = tile_pass_end(X);
+  cs.p[cs.n_ranges] = b.status + (size_t)pb * stride;
+  cs.n[cs.n_ranges++] = (size_t)(pe - pb) * stride;
+}
+
 hipError_t clear_workspace(const PipeBufs& b, uint32_t* counters, bool sticky_flags, uint32_t* ranges, size_t X,
                            size_t R, uint32_t P, uint32_t* sel, hipStream_t s, const WordUpload* up,
                            uint32_t* batch_tile = nullptr, size_t n_batches = 0) {
@@ -259,22 +286,15 @@ hipError_t clear_workspace(const PipeBufs& b, uint32_t* counters, bool sticky_fl
   cs.n[2] = 2 * X;
   cs.p[3] = reinterpret_cast<uint32_t*>(b.scan_status);
   cs.n[3] = 2 * (size_t)scan_tiles((uint32_t)R);
-  // look-back words of the tile passes, and the sorted-buffer selector
+  cs.p[4] = sel;  // the sorted-buffer selector
+  cs.n[4] = 1;
+  cs.n_ranges = 5;
   if (b.order_ctl) {
-    cs.p[4] = b.order_ctl;
-    cs.n[4] = b.order_ctl_words;
-  } else if (tile_sort12(X, P)) {  // block counts: written before they are read, no clearing
-    cs.p[4] = nullptr;
-    cs.n[4] = 0;
-  } else {
-    const size_t stride = sort_status_stride(P);
-    const int pb = kDepthPasses, pe = tile_pass_end(X);
-    cs.p[4] = b.status + (size_t)pb * stride;
-    cs.n[4] = (size_t)(pe - pb) * stride;
+    cs.p[cs.n_ranges] = b.order_ctl;
+    cs.n[cs.n_ranges++] = b.order_ctl_words;
+  } else if (!tile_sort12(X, P)) {
+    tile_pass_words(b, X, P, cs);
   }
-  cs.p[5] = sel;
-  cs.n[5] = 1;
-  cs.n_ranges = 6;
   if (batch_tile && n_batches) {
     cs.p[cs.n_ranges] = batch_tile;
     cs.n[cs.n_ranges++] = n_batches;
@@ -707,6 +727,7 @@ gsr_status forward_impl(const gsr_model* model, int32_t n_views, const gsr_camer
     else
       HIP_TRY(launch_scan(b.n_tiles, state->offsets, b.scan_status, &b.ctl->scan_ticket, R, state->counters, P, s));
   }
+  BoxSource by_box{};
   if (n_pairs_host) {
     // the pair count, and the sticky error word (this call's scan, or an
     // earlier call on this state that nobody checked)
@@ -718,6 +739,24 @@ gsr_status forward_impl(const gsr_model* model, int32_t n_views, const gsr_camer
     if (cnt[kCntPairs] > P) {
       HIP_TRY(launch_clear_u32(state->counters + kCntOverflow, 1, s));  // this call's overflow is reported now
       return GSR_ENOSPACE;
+    }
+    // Too few pairs to order the records first: by tile from here on, in that
+    // path's layout of the workspace, which holds the views, counts and sort
+    // words where they are and the depth keys in its tile boxes' place.  The
+    // boxes stay in pair_emit, where the backward looks for them.  (An
+    // inspected call stays: the debug copies are of the path it started on.)
+    if (op.on && !shared && !debug && X > kOrderFewTiles && !order_pays(X, cnt[kCntPairs])) {
+      Carver ct(ws);
+      PipeBufs bt;
+      if (carve(ct, bt, n_views, R, P, 0, false, X, backward_layout, OrderPlan{}) > ws_bytes) return GSR_ENOSPACE;
+      by_box = BoxSource{boxes, b.sort_keys, n, tiles_per_view, (uint32_t)hv[0].tiles_x, op.box4};
+      b = bt;
+      op.on = false;
+      if (!tile_sort12(X, P)) {
+        ClearSet cs{};
+        tile_pass_words(b, X, P, cs);
+        HIP_TRY(launch_clear_multi(cs, s, nullptr));
+      }
     }
   }
   if (op.on) {
@@ -736,7 +775,7 @@ gsr_status forward_impl(const gsr_model* model, int32_t n_views, const gsr_camer
     {
       StageScope sc(timer, GSR_STAGE_DUPLICATE, s);
       HIP_TRY(launch_duplicate(b.n_tiles, state->offsets, b.tile_box, R, state->counters, P, b.keys_a,
-                               state->pair_vals, b.rec_of, s));
+                               state->pair_vals, b.rec_of, by_box, s));
     }
     if (debug) {
       if (debug->keys_emit) HIP_TRY(hipMemcpyAsync(debug->keys_emit, b.keys_a, 8ull * P, hipMemcpyDeviceToDevice, s));
@@ -763,7 +802,8 @@ gsr_status forward_impl(const gsr_model* model, int32_t n_views, const gsr_camer
     {
       StageScope sc(timer, GSR_STAGE_SORT, s);
       HIP_TRY(launch_sort_segments(b.keys_a, b.keys_b, state->pair_vals, state->pair_vals + P, state->sort_sel,
-                                   state->ranges, (uint32_t)X, b.rec_of, state->counters, P, state->pair_emit,
+                                   state->ranges, (uint32_t)X, b.rec_of, state->counters, P,
+                                   by_box.boxes ? nullptr : state->pair_emit,
                                    debug ? debug->keys_sorted : nullptr, b.ctl->tile_class, b.class_list,
                                    &b.ctl->seg_ticket, state->counters + kCntError, s));
     }
@@ -1110,7 +1150,8 @@ gsr_status gsr_render_batch(const gsr_model* models, int32_t n_models, const gsr
   } else {
     {
       StageScope sc(timer, GSR_STAGE_DUPLICATE, s);
-      HIP_TRY(launch_duplicate(b.n_tiles, b.offsets, b.tile_box, R, b.counters, P, b.keys_a, b.vals, b.rec_of, s));
+      HIP_TRY(launch_duplicate(b.n_tiles, b.offsets, b.tile_box, R, b.counters, P, b.keys_a, b.vals, b.rec_of,
+                               BoxSource{}, s));
     }
     {
       StageScope sc(timer, GSR_STAGE_SORT, s);

@@ -234,9 +234,17 @@ hipError_t launch_project(const JobD& job, const ViewD* views_dev, float* record
 uint32_t scan_tiles(uint32_t n);
 hipError_t launch_scan(const uint32_t* in, uint32_t* out, uint64_t* status, uint32_t* ticket, uint32_t n,
                        uint32_t* counters, uint32_t pair_capacity, hipStream_t s);
+// Tile boxes and depth bits by record of a call that projected for the
+// order-first path (views of n records and one size); null: a uint4 tile_box.
+struct BoxSource {
+  const uint32_t* boxes;
+  const uint32_t* depth;
+  uint32_t n, tiles_per_view, tiles_x;
+  bool box4;
+};
 hipError_t launch_duplicate(const uint32_t* n_tiles, const uint32_t* offsets, const uint4* tile_box,
                             uint32_t n_rec, const uint32_t* counters, uint32_t pair_capacity,
-                            uint64_t* keys, uint32_t* vals, uint32_t* rec_of, hipStream_t s);
+                            uint64_t* keys, uint32_t* vals, uint32_t* rec_of, const BoxSource& src, hipStream_t s);
 // Buffers of the order-first path (order.hip).
 struct OrderBufs {
   const ViewD* views;

@@ -39,7 +39,7 @@ __global__ void __launch_bounds__(256)
 k_duplicate(const uint32_t* __restrict__ n_tiles, const uint32_t* __restrict__ offsets,
             const uint4* __restrict__ tile_box, uint32_t n_rec, const uint32_t* __restrict__ counters,
             uint32_t pair_capacity, uint64_t* __restrict__ keys, uint32_t* __restrict__ vals,
-            uint32_t* __restrict__ rec_of) {
+            uint32_t* __restrict__ rec_of, BoxSource src) {
   const uint32_t r = blockIdx.x * blockDim.x + threadIdx.x;
   const int lane = threadIdx.x & 63;
   const uint32_t lim = min(pair_capacity, counters[kCntPairs]);
@@ -47,7 +47,15 @@ k_duplicate(const uint32_t* __restrict__ n_tiles, const uint32_t* __restrict__ o
   const uint32_t cnt = valid ? n_tiles[r] : 0u;
   const uint32_t off = valid ? offsets[r] : 0xFFFFFFFFu;  // invalid lanes never own a pair
   uint4 tb = make_uint4(0u, 0u, 0u, 0u);
-  if (cnt) tb = tile_box[r];
+  if (cnt) {
+    if (src.boxes) {
+      const uint2 q = load_box(src.boxes, r, src.box4);
+      tb = make_uint4(r / src.n * src.tiles_per_view + (q.x >> 16) * src.tiles_x + (q.x & 0xFFFFu), q.y, src.depth[r],
+                      src.tiles_x);
+    } else {
+      tb = tile_box[r];
+    }
+  }
   uint32_t end = valid ? off + cnt : 0u;
 #pragma unroll
   for (int s = 32; s > 0; s >>= 1) end = max(end, (uint32_t)__shfl_xor((int)end, s, 64));
@@ -89,10 +97,10 @@ k_duplicate(const uint32_t* __restrict__ n_tiles, const uint32_t* __restrict__ o
 
 hipError_t launch_duplicate(const uint32_t* n_tiles, const uint32_t* offsets, const uint4* tile_box,
                             uint32_t n_rec, const uint32_t* counters, uint32_t pair_capacity,
-                            uint64_t* keys, uint32_t* vals, uint32_t* rec_of, hipStream_t s) {
+                            uint64_t* keys, uint32_t* vals, uint32_t* rec_of, const BoxSource& src, hipStream_t s) {
   if (n_rec == 0) return hipSuccess;
   hipLaunchKernelGGL(k_duplicate, dim3(div_up(n_rec, 256u)), dim3(256), 0, s, n_tiles, offsets, tile_box,
-                     n_rec, counters, pair_capacity, keys, vals, rec_of);
+                     n_rec, counters, pair_capacity, keys, vals, rec_of, src);
   return hipGetLastError();
 }
 
