@@ -210,10 +210,6 @@ __device__ __forceinline__ float pair_power(const float4 A, const float4 B, floa
 
 __device__ __forceinline__ float pair_gauss(float power) { return __builtin_amdgcn_exp2f(power); }
 
-__device__ __forceinline__ float pair_alpha(const float4 B, float power) {
-  return fminf(kAlphaMax, B.y * pair_gauss(power));
-}
-
 // Wave ballot of a condition (no round trip of the flag through a VGPR).
 __device__ __forceinline__ uint64_t ballot(bool x) { return __builtin_amdgcn_ballot_w64(x); }
 
@@ -560,26 +556,15 @@ hipError_t launch_blend_fwd(const ViewD* views_dev, int n_views, uint32_t total_
 }
 
 // ---------------------------------------------------------------- backward
-// Wave64 reductions with DPP: quad swaps, half-row and row mirrors, then the
-// row broadcasts 15 and 31; lane 63 ends with the result.
-
-__device__ __forceinline__ float wave_sum63(float v) {
-  v += dpp<0xB1, 0xF>(v);   // quad_perm [1,0,3,2]
-  v += dpp<0x4E, 0xF>(v);   // quad_perm [2,3,0,1]
-  v += dpp<0x141, 0xF>(v);  // row_half_mirror
-  v += dpp<0x140, 0xF>(v);  // row_mirror
-  v += dpp<0x142, 0xA>(v);  // row_bcast15 into rows 1 and 3
-  v += dpp<0x143, 0xC>(v);  // row_bcast31 into rows 2 and 3
-  return v;
-}
-
 template <unsigned CTRL, unsigned ROW_MASK>
 __device__ __forceinline__ uint32_t dpp_u32(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROW_MASK, 0xF, false);
 }
 
-// For v >= 0 the float order is the order of the bit patterns: an integer
-// max, which takes its DPP operand directly.
+// Maximum over the wave with DPP: quad swaps, half-row and row mirrors, then
+// the row broadcasts 15 and 31; lane 63 ends with it.  For v >= 0 the float
+// order is the order of the bit patterns: an integer max, which takes its DPP
+// operand directly.
 __device__ __forceinline__ float wave_max63(float v) {
   uint32_t u = __float_as_uint(v);
   u = max(u, dpp_u32<0xB1, 0xF>(u));
@@ -605,15 +590,6 @@ __device__ __forceinline__ float swap32_add(float x, float y) {
 __device__ __forceinline__ float swap16_add(float x, float y) {
   const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
-// Sum over the 16 lanes of each row; every lane of the row ends with it.
-__device__ __forceinline__ float row_sum16(float v) {
-  v += dpp<0xB1, 0xF>(v);   // quad_perm [1,0,3,2]
-  v += dpp<0x4E, 0xF>(v);   // quad_perm [2,3,0,1]
-  v += dpp<0x141, 0xF>(v);  // row_half_mirror
-  v += dpp<0x140, 0xF>(v);  // row_mirror
-  return v;
 }
 
 // Per pair, the wave sums of: h dx, h dy, h dx^2, h dx dy, h dy^2, h, and the

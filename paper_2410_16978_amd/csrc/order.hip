@@ -495,7 +495,7 @@ __device__ __forceinline__ void wave_lds_fence() {
 
 template <typename TT, int ROUNDS>
 __global__ void __launch_bounds__(kEmitThreads)
-k_emit(const ViewD* __restrict__ views, int n_views, uint32_t n_blk, const uint32_t* __restrict__ vals0,
+k_emit(const ViewD* __restrict__ views, int n_views, const uint32_t* __restrict__ vals0,
        const uint32_t* __restrict__ vals1, const uint32_t* __restrict__ unit, const uint32_t* __restrict__ boxes, bool box4,
        uint32_t* __restrict__ counters, uint32_t cap, TT* __restrict__ tiles, uint32_t* __restrict__ recs,
        uint64_t* __restrict__ status, uint32_t* __restrict__ ticket) {
@@ -942,7 +942,7 @@ hipError_t order_pairs(const OrderBufs& o, hipStream_t s) {
   uint32_t* recs[2] = {o.rec_a, o.rec_b};
   const auto emit = o.seq_tile == kEmitTile ? k_emit<TT, (int)kEmitTile / kEmitThreads>
                                             : k_emit<TT, (int)kEmitTileSmall / kEmitThreads>;
-  hipLaunchKernelGGL(emit, dim3(o.seq_blocks), dim3(kEmitThreads), 0, s, o.views, o.n_views, o.seq_blocks, o.vals_a,
+  hipLaunchKernelGGL(emit, dim3(o.seq_blocks), dim3(kEmitThreads), 0, s, o.views, o.n_views, o.vals_a,
                      o.vals_b, o.unit, o.boxes, o.box4, o.counters, o.cap, tiles[0], recs[0], o.emit_status, &o.tickets[4]);
   const auto pass = pair_step(o.cap) == kPairStep ? pair_pass<TT, (int)kPairStep / kPairThreads>
                                                   : pair_pass<TT, (int)kPairStepSmall / kPairThreads>;
