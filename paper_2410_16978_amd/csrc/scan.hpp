@@ -69,11 +69,14 @@ __device__ __forceinline__ void scan_block(const uint32_t* __restrict__ in, uint
 #pragma unroll
     for (int k = 0; k < ITEMS; ++k) v[k] = (base + k < n) ? in[base + k] : 0u;
   }
-  uint64_t sum = 0;
+  uint32_t lo = 0, hi = 0;  // in halves (64-bit additions took 70 registers more)
 #pragma unroll
-  for (int k = 0; k < ITEMS; ++k) sum += v[k];
+  for (int k = 0; k < ITEMS; ++k) {
+    lo += v[k] & 0xFFFFu;
+    hi += v[k] >> 16;
+  }
   uint64_t total;
-  const uint64_t local = block_exclusive_scan<THREADS>(sum, lds, &total);
+  const uint64_t local = block_exclusive_scan<THREADS>(lo + ((uint64_t)hi << 16), lds, &total);
   if (threadIdx.x < 64) {
     const int lane = threadIdx.x;
     if (lane == 0)
@@ -122,33 +125,32 @@ __device__ __forceinline__ void scan_block(const uint32_t* __restrict__ in, uint
     }
   }
   __syncthreads();
-  const uint64_t first = s_excl + local;
-  if (base + ITEMS <= n && (reinterpret_cast<uintptr_t>(out) & 15) == 0 && (first + sum) >> 32 == 0) {
-    uint32_t run = (uint32_t)first;
+  // (saturating: past 2^32 - 1 the offsets stay there)
+  uint32_t run = (uint32_t)min(s_excl + local, (uint64_t)0xFFFFFFFFull);
+  if (base + ITEMS <= n && (reinterpret_cast<uintptr_t>(out) & 15) == 0) {
     uint4* out4 = reinterpret_cast<uint4*>(out + base);
 #pragma unroll
     for (int k = 0; k < ITEMS / 4; ++k) {
       uint4 q;
       q.x = run;
-      run += v[4 * k];
+      run = __builtin_elementwise_add_sat(run, v[4 * k]);
       q.y = run;
-      run += v[4 * k + 1];
+      run = __builtin_elementwise_add_sat(run, v[4 * k + 1]);
       q.z = run;
-      run += v[4 * k + 2];
+      run = __builtin_elementwise_add_sat(run, v[4 * k + 2]);
       q.w = run;
-      run += v[4 * k + 3];
+      run = __builtin_elementwise_add_sat(run, v[4 * k + 3]);
       out4[k] = q;
     }
   } else {
-    uint64_t run = first;
 #pragma unroll
     for (int k = 0; k < ITEMS; ++k) {
-      if (base + k < n) out[base + k] = (uint32_t)min(run, (uint64_t)0xFFFFFFFFull);
-      run += v[k];
+      if (base + k < n) out[base + k] = run;
+      run = __builtin_elementwise_add_sat(run, v[k]);
     }
-    // out[n] = total, written by the thread that owns the end
-    if (base <= n && n < base + ITEMS) out[n] = (uint32_t)min(run, (uint64_t)0xFFFFFFFFull);
   }
+  // out[n] = total, written by the thread that owns the end
+  if (base <= n && n < base + ITEMS) out[n] = run;
 }
 
 }  // namespace gsr
