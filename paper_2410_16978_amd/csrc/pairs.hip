@@ -35,6 +35,7 @@ hipError_t launch_scan(const uint32_t* in, uint32_t* out, uint64_t* status, uint
 // overflow flag or the batch status already records it).  The sort carries
 // each pair's emission index as its value; rec_of[e] keeps the record of
 // emission index e.
+template <bool BY_BOX>
 __global__ void __launch_bounds__(256)
 k_duplicate(const uint32_t* __restrict__ n_tiles, const uint32_t* __restrict__ offsets,
             const uint4* __restrict__ tile_box, uint32_t n_rec, const uint32_t* __restrict__ counters,
@@ -48,7 +49,7 @@ k_duplicate(const uint32_t* __restrict__ n_tiles, const uint32_t* __restrict__ o
   const uint32_t off = valid ? offsets[r] : 0xFFFFFFFFu;  // invalid lanes never own a pair
   uint4 tb = make_uint4(0u, 0u, 0u, 0u);
   if (cnt) {
-    if (src.boxes) {
+    if (BY_BOX) {
       const uint2 q = load_box(src.boxes, r, src.box4);
       tb = make_uint4(r / src.n * src.tiles_per_view + (q.x >> 16) * src.tiles_x + (q.x & 0xFFFFu), q.y, src.depth[r],
                       src.tiles_x);
@@ -99,8 +100,8 @@ hipError_t launch_duplicate(const uint32_t* n_tiles, const uint32_t* offsets, co
                             uint32_t n_rec, const uint32_t* counters, uint32_t pair_capacity,
                             uint64_t* keys, uint32_t* vals, uint32_t* rec_of, const BoxSource& src, hipStream_t s) {
   if (n_rec == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_duplicate, dim3(div_up(n_rec, 256u)), dim3(256), 0, s, n_tiles, offsets, tile_box,
-                     n_rec, counters, pair_capacity, keys, vals, rec_of, src);
+  hipLaunchKernelGGL(src.boxes ? k_duplicate<true> : k_duplicate<false>, dim3(div_up(n_rec, 256u)), dim3(256), 0, s,
+                     n_tiles, offsets, tile_box, n_rec, counters, pair_capacity, keys, vals, rec_of, src);
   return hipGetLastError();
 }
 
