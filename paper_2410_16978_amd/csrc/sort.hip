@@ -1061,11 +1061,15 @@ static_assert(kSegWaveMax == 512 && kSegBlockClasses < kTileClasses, "size class
 // between two per block, one per 512-thread half, the halves in lockstep.
 // A segment is a chain of ranking steps, one per key a lane holds and pass,
 // so blocks to spare are used to shorten it: while every item still has a
-// block of its own, smaller classes are sorted by halves too, then by whole
-// blocks, and the tiles left are spread over the blocks left, as few waves
-// in each as that takes (before and after, us: 64 tiles of up to 461 pairs
-// 16.9 / 13.0; 672 of up to 2787 21.5 / 16.9; 2500 of up to 6966 33 / 30.5;
-// a 6669-pair tile alone bounds the 3042 of a three-view step, 29.0 / 28.8).
+// block of its own, the classes in between are sorted by whole blocks, the
+// larger ones first, and the small tiles are spread over the blocks left, as
+// few waves in each as that takes (before and after, us: 64 tiles of up to 461
+// pairs 16.9 / 13.0; 672 of up to 2787 21.5 / 16.9; 2500 of up to 6966 33 /
+// 30.5; a 6669-pair tile alone bounds the 3042 of a three-view step, 29.0 /
+// 28.8).  Small tiles stay with their wave: a block's barriers and digit
+// offsets cost more than it saves (whole frames with tiles of 62 pairs at
+// most by half blocks / by waves, 62.3 / 57.6 for 435 tiles and 56.9 / 51.0
+// for 254; with 256 pairs or more at most the two are level).
 // Block b starts with item b; later items go to whichever block is free
 // first, so a block holding one of the largest tiles takes nothing else.
 __global__ void __launch_bounds__(1024) k_sort_segments(SegArgs a) {
@@ -1076,32 +1080,26 @@ __global__ void __launch_bounds__(1024) k_sort_segments(SegArgs a) {
     SegLdsP<kSegHalfThreads, kSegBlockDigitBits> half[2];
   } L;
   __shared__ uint32_t s_end[kTileClasses];  // inclusive prefix of the class counts (empty tiles left out)
-  __shared__ uint32_t s_next, s_passes, s_single, s_big;
+  __shared__ uint32_t s_next, s_passes, s_single;
   const uint32_t K = min(a.counters[kCntPairs], a.cap);
   if (threadIdx.x < 64) {
     const uint32_t k = threadIdx.x;
     const uint32_t cnt = k + 1 < kTileClasses ? min(a.class_count[k], a.n_tiles) : 0u;
     const uint32_t inc = wave_scan_add(cnt);
     if (k < kTileClasses) s_end[k] = inc;
-    // lane k: the tiles of the first k + 1 classes by halves (or blocks), then
-    // by blocks; the last lane whose items fit the grid decides
+    // lane k: the tiles of the first k + 1 classes by blocks; the last lane
+    // whose items fit the grid decides
     auto at = [&](uint32_t c) { return (uint32_t)__shfl((int)inc, (int)c, 64); };
-    const uint32_t all = at(kTileClasses - 1);
-    uint32_t single = at(kSegSingleClasses - 1), big = at(kSegBlockClasses - 1);
-    uint64_t fit = __ballot(k >= kSegBlockClasses && k < kTileClasses &&
-                            single + div_up(inc - single, 2u) + div_up(all - inc, (uint32_t)kSegSmallWaves) <= gridDim.x);
-    if (fit) big = at(63u - (uint32_t)__builtin_clzll(fit));
-    fit = __ballot(k >= kSegSingleClasses && k < kTileClasses && inc <= big &&
-                   inc + div_up(big - inc, 2u) + div_up(all - big, (uint32_t)kSegSmallWaves) <= gridDim.x);
+    const uint32_t all = at(kTileClasses - 1), big = at(kSegBlockClasses - 1);
+    uint32_t single = at(kSegSingleClasses - 1);
+    const uint64_t fit = __ballot(k >= kSegSingleClasses && k < kSegBlockClasses &&
+                                  inc + div_up(big - inc, 2u) + div_up(all - big, (uint32_t)kSegSmallWaves) <= gridDim.x);
     if (fit) single = at(63u - (uint32_t)__builtin_clzll(fit));
-    if (k == 0) {
-      s_single = single;
-      s_big = big;
-    }
+    if (k == 0) s_single = single;
   }
   __syncthreads();
   const uint32_t n_single = s_single;
-  const uint32_t n_big = s_big;
+  const uint32_t n_big = s_end[kSegBlockClasses - 1];
   const uint32_t n_all = s_end[kTileClasses - 1];
   const uint32_t n_pairs = div_up(n_big - n_single, 2u), n_blocks = n_single + n_pairs;
   const uint32_t group = n_blocks < gridDim.x ? min(div_up(n_all - n_big, gridDim.x - n_blocks), (uint32_t)kSegSmallWaves)
