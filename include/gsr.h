@@ -207,9 +207,10 @@ typedef struct {
  *                             calls that order their records before pairing
  *                             them (P >= 2 R and P >= 2^20 with more than
  *                             4096 tiles, else P >= 2^21; and full tiles,
- *                             P >= 3 * 2^16 and P >= 2048 X, with P >= R where
- *                             the views have at most 255 tiles a side and
- *                             P >= 2 R where not; also if such a call reads
+ *                             P >= 3 * 2^16 and P >= 2048 X up to 256 tiles,
+ *                             3072 X beyond, with P >= R where the views have
+ *                             at most 255 tiles a side and P >= 2 R where
+ *                             not; also if such a call reads
  *                             its pair count back, finds too few pairs and
  *                             sorts them by tile), each record's tile box,
  *                             from which the backward has the index: its

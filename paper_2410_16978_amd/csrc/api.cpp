@@ -115,17 +115,18 @@ struct OrderPlan {
 // With many pairs a tile the per-tile sort has few blocks at work, and a tile
 // beyond 8192 pairs passes through global memory in one of them; how uneven
 // the tiles are is not known here.  From 2048 pairs a tile on, order-first is
-// ahead of few evenly filled tiles (158 / 145 at 200, 223 / 172 at 72; of more
-// only well beyond, at 1024 169 / 201 with 2413 a tile and 343 / 321 with
-// 6035) and far ahead of layered shells (286 / 183 at 100 tiles of 1815 pairs
-// on average, 2606 / 1106 at 64 of 30k).  Below, evenly filled tiles are faster
-// sorted by tile (122 / 167 at 1024 tiles of 1208; a step of four views, 676
-// tiles of 1530, 298 / 345), shells are not (291 / 214 at 1024 of 1409): one
-// would lose more than it did before this path was there, the other only
-// stays what it was, so these are sorted by tile.  Up to 4096 tiles the same
-// holds above 2^21 pairs in a smaller measure (2500 tiles, evenly filled 158 /
-// 190 at 2.2M and 352 / 338 at 11M; shells 254 / 221 at 2.1M, 741 / 493 at
-// 7.9M).
+// ahead even of evenly filled tiles where there is at most one a compute unit
+// (158 / 145 at 200, 223 / 172 at 72), beyond that from about 3072 (a step of
+// 361 tiles of 1972 pairs 224 / 268, frames of 625 tiles of 2892 278 / 322
+// and of 3499 285 / 308, of 7516 381 / 322); it is far ahead of layered shells
+// (286 / 183 at 100 tiles of 1815 pairs on average, 2606 / 1106 at 64 of 30k).
+// Below, evenly filled tiles are faster sorted by tile (122 / 167 at 1024 tiles
+// of 1208; a step of four views, 676 tiles of 1530, 298 / 345), shells are not
+// (291 / 214 at 1024 of 1409): one would lose more than it did before this path
+// was there, the other only stays what it was, so these are sorted by tile.
+// Up to 4096 tiles the same holds above 2^21 pairs in a smaller measure (2500
+// tiles, evenly filled 158 / 190 at 2.2M and 352 / 338 at 11M; shells 254 / 221
+// at 2.1M, 741 / 493 at 7.9M).
 //
 // Below two pair slots a record the record passes outweigh the pairs, unless
 // tiles are that full; and the boxes of all records, which the backward reads
@@ -145,7 +146,7 @@ struct OrderPlan {
 // for the innermost of eight, 472k pairs in few of the tiles).
 constexpr uint32_t kOrderMinPairs = 1u << 20, kOrderMinPairsFull = 3u << 16, kOrderFewTiles = 256;
 bool order_full(uint64_t X, uint64_t pairs) {
-  return pairs >= kOrderMinPairsFull && pairs >= 2048 * X;
+  return pairs >= kOrderMinPairsFull && pairs >= (X <= kOrderFewTiles ? 2048 : 3072) * X;
 }
 bool order_pays(uint64_t X, uint32_t pairs) {
   return order_full(X, pairs) || pairs >= (tile_sort12(X, pairs) ? 2 * kOrderMinPairs : kOrderMinPairs);

@@ -51,7 +51,9 @@ def _inputs(n, n_views, W, H, ls, mask):
     (500, 1, 160, 160, 3 << 16, True),                                               # not quite
     (500, 1, 800, 800, (1 << 21) - 1, True), (500, 1, 800, 800, 1 << 21, False),     # 2500 tiles
     (500, 1, 1100, 1000, (1 << 20) - 1, True), (500, 1, 1100, 1000, 1 << 20, False),  # 4347 tiles
-    (99_000, 4, 200, 200, 1_142_854, True), (500, 4, 200, 200, 2048 * 676, False),   # 676 tiles of 1691 and 2048 slots
+    (500, 1, 256, 256, 2048 * 256 - 1, True), (500, 1, 256, 256, 2048 * 256, False),  # 256 tiles
+    (200_000, 1, 300, 300, 787_326, True), (99_000, 4, 200, 200, 1_142_854, True),   # 361 and 676 tiles
+    (500, 4, 200, 200, 3072 * 676 - 1, True), (500, 4, 200, 200, 3072 * 676, False),
     (200_000, 1, 160, 160, 200_000, True), (200_000, 1, 160, 160, 2048 * 100, False),  # boxes fit from a slot a record
     (500_000, 1, 1100, 1000, 999_999, True), (600_000, 1, 1100, 1000, 1_200_000, False),
 ])
@@ -111,7 +113,7 @@ def test_a_call_that_stays(n, n_views, W, H, ls):
     args = _inputs(n, n_views, W, H, ls, 3)
     by_tile, K, synced = _run(*args, ORDER_CAP, True)
     tiles = n_views * ((W + 15) // 16) * ((H + 15) // 16)
-    assert not by_tile and (tiles <= 256 or (K >= 3 << 16 and K >= 2048 * tiles))
+    assert not by_tile and (tiles <= 256 or K >= 3072 * tiles)
     by_tile, _, by_slots = _run(*args, ORDER_CAP, False)
     assert not by_tile
     _assert_same(synced, by_slots, "by slots")
@@ -121,12 +123,12 @@ def test_without_a_workspace():
     """The no-allocation forward's layout has no backward behind it."""
     import torch
     from paper_2410_16978_amd import rasterizer as rz
-    model, cams, views = _inputs(20000, 2, 300, 200, -4.5, 3)
-    cap = 1_200_000  # full by its slots: 494 tiles, two slots a record and more
+    model, cams, views = _inputs(20000, 2, 300, 150, -4.5, 3)
+    cap = 1_200_000  # full by its slots: 380 tiles, two slots a record and more
     got = []
     for sync in (True, False):
-        st = rz.make_state(20000, 2, 300, 200, cap)
-        out = (torch.empty((2, 3, 200, 300), device="cuda"), torch.empty((2, 200, 300), device="cuda"))
+        st = rz.make_state(20000, 2, 300, 150, cap)
+        out = (torch.empty((2, 3, 150, 300), device="cuda"), torch.empty((2, 150, 300), device="cuda"))
         rgb, alpha, st = rz.rasterize_forward_noalloc(model, cams, views, st, out, n_pairs=sync)
         g = rz.rasterize_backward(model, cams, views, st, torch.ones_like(rgb), torch.ones_like(alpha))
         assert 0 < rz.forward_check(st) < 3 << 16
