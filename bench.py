@@ -312,8 +312,8 @@ def bench_serving(rz, scenes, torch, seconds, rates=(200.0,), budgets=(16 << 30,
         entry = {"mode": mode, "budget_gib": budget / (1 << 30), "rate_hz": rate, "requests": len(trace)}
         max_pix = max(sum(c["width"] * c["height"] for c in t["cams"]) for t in trace)
         for name, batched in (("batched", True), ("plain", False)):
-            # a batch's workspace can exceed the sum of its requests' costs a
-            # little (per-call sort words): the slots get a quarter more
+            # (a batch's workspace is at most the sum of its requests' costs;
+            # the slots get a quarter more all the same)
             ex = GpuExecutor(models, slots=2 if batched else 1, pair_table=table, ws_bytes=budget * 5 // 4,
                              keep_results=False, out_pixels=(16 if batched else 1) * max_pix)
             warm = requests_from_trace(trace[:400])

@@ -331,6 +331,9 @@ gsr_status gsr_activate(const gsr_model* model, float* scale_out, float* opacity
  * GSR_ENOSPACE without rendering when K > state->pair_capacity, or
  * GSR_EDEVICE without rendering when the state's error word is set (by this
  * call's scan or an earlier unchecked call; gsr_forward_check clears it).
+ * The call also chooses between its two paths by that count then, and by
+ * pair_capacity alone where it is NULL: a capacity several times the pairs
+ * may take the path for more of them, which costs up to a fifth of the call.
  * If NULL the call never synchronises; on overflow the pairs beyond the
  * capacity are dropped, state->counters[1] is set and the image is
  * incomplete - check with gsr_forward_check after synchronising.

@@ -105,8 +105,9 @@ struct OrderPlan {
 // Whether a call orders its records before it pairs them (one that shares an
 // order always does).  Ordering first moves about 12 bytes a record four
 // times and 6 a pair twice, where the per-tile path moves 12 a pair twice (up
-// to 4096 tiles once) and then sorts every tile; its 12 launches cost about
-// 30 us more than the other's on small calls.  Measured, per-tile against
+// to 4096 tiles once) and then sorts every tile; its 14 launches between the
+// projection and the blend (two tile digits) cost about 30 us more than the
+// other's 6 on small calls.  Measured, per-tile against
 // order-first, whole frames, us: beyond 4096 tiles 197 / 192 at 1.0M pairs and
 // 158 / 169 at 0.5M (1100 x 1000), 1141 / 860 at 12.5M (2 x 1M records); up
 // to 4096 tiles 165 / 190 at 1.0M, 247 / 241 at 2.0M and 870 / 621 at 10M

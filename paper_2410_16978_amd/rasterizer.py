@@ -476,7 +476,8 @@ def rasterize_forward(model, cams, views, state=None, capacity=None, sync=True, 
     sync=True: the library reads the pair count once; when the pair buffers
     are too small they are regrown to the exact need and the call repeats.
     sync=False: no host synchronisation (the caller checks state later with
-    forward_check).  Returns (rgb [V,3,H,W], alpha [V,H,W], state[, debug]).
+    forward_check); the library then chooses its path by the capacity, which
+    is best sized near the pairs.  Returns (rgb [V,3,H,W], alpha [V,H,W], state[, debug]).
     """
     L = lib()
     V = len(cams)

@@ -215,7 +215,7 @@ class GpuExecutor:
     launch whose batch needs more regrows it; `regrows` counts those), so
     that no device allocation happens while serving; a request's budget cost
     is the workspace of a batch holding it alone (the library's own size
-    function) plus its images.  out_pixels: each slot carves its requests'
+    function; a batch of several needs at most their sum) plus its images.  out_pixels: each slot carves its requests'
     images from an arena of that many pixels allocated once (the images of a
     launch stay valid until its slot's next launch; a batch that does not
     fit gets fresh tensors).  keep_results=False drops a request's images
